@@ -258,6 +258,78 @@ __device__ inline void block_sum(double (&v)[N], double *__restrict__ out) {
     }
 }
 
+// Density deviation and velocity of one node from its shifted populations
+// (Eqs. s2-density, s2-fv).
+template <class C>
+struct NodeMoments {
+    using R = typename C::R;
+    R drho, ux, uy, uz;
+};
+
+template <class C>
+__device__ inline NodeMoments<C> node_moments(const typename C::R (&gv)[C::V::Q]) {
+#pragma clang fp contract(on)
+    using R = typename C::R;
+    using V = typename C::V;
+    NodeMoments<C> m{R(0), R(0), R(0), R(0)};
+    static_for<0, V::Q>([&](auto ac) {
+        constexpr int a = decltype(ac)::value;
+        m.drho += gv[a];
+        if constexpr (V::ex[a] != 0) m.ux += V::ex[a] > 0 ? gv[a] : -gv[a];
+        if constexpr (V::ey[a] != 0) m.uy += V::ey[a] > 0 ? gv[a] : -gv[a];
+        if constexpr (V::ez[a] != 0) m.uz += V::ez[a] > 0 ? gv[a] : -gv[a];
+    });
+    return m;
+}
+
+// BGK relaxation of one node to the equilibrium of Eq. s2-eq plus the forcing
+// term 3 w e.F, one opposite pair (a, a + 1) at a time: e_{a+1} = -e_a, so the
+// even part of the equilibrium, w (drho + 4.5 (e.u)^2 - 1.5 u.u), is shared,
+// and its odd part 3 w e.u and the forcing change sign.  put(a, value)
+// receives the post-collision populations.
+// Multiply-adds fuse only within one expression: fusion across statements
+// depends on how the compiler lays out the blocks, which differs between the
+// kernels that call this, and all of them must round a node the same way.
+// FORCE = false leaves the forcing term out (no force at the node; the results
+// are equal, a sum with zero).
+template <class C, bool FORCE = true, typename Put>
+__device__ inline void node_relax(const typename C::R (&gv)[C::V::Q], const NodeMoments<C> &m,
+                                  typename C::R omega, typename C::R Fx, typename C::R Fy,
+                                  typename C::R Fz, Put &&put) {
+#pragma clang fp contract(on)
+    using R = typename C::R;
+    using V = typename C::V;
+    const R ux = m.ux, uy = m.uy, uz = m.uz;
+    const R uu = ux * ux + uy * uy + uz * uz;
+    const R base = m.drho - R(1.5) * uu;
+    put(0, gv[0] + omega * (V::template w<R>(0) * base - gv[0]));
+    static_for<0, (V::Q - 1) / 2>([&](auto pc) {
+        constexpr int a = 1 + 2 * decltype(pc)::value;
+        constexpr int cx = V::ex[a], cy = V::ey[a], cz = V::ez[a];
+        static_assert(V::ex[a + 1] == -cx && V::ey[a + 1] == -cy && V::ez[a + 1] == -cz,
+                      "opposite velocities are adjacent");
+        constexpr R w = V::template w<R>(a);
+        constexpr R w3 = R(3) * w;
+        R eu = R(0), eF = R(0);
+        if constexpr (cx != 0) eu += cx > 0 ? ux : -ux;
+        if constexpr (cy != 0) eu += cy > 0 ? uy : -uy;
+        if constexpr (cz != 0) eu += cz > 0 ? uz : -uz;
+        if constexpr (cx != 0) eF += cx > 0 ? Fx : -Fx;
+        if constexpr (cy != 0) eF += cy > 0 ? Fy : -Fy;
+        if constexpr (cz != 0) eF += cz > 0 ? Fz : -Fz;
+        const R sym = w * (base + R(4.5) * eu * eu);
+        const R anti = w3 * eu;
+        if constexpr (FORCE) {
+            const R fa = w3 * eF;
+            put(a, gv[a] + omega * ((sym + anti) - gv[a]) + fa);
+            put(a + 1, gv[a + 1] + omega * ((sym - anti) - gv[a + 1]) - fa);
+        } else {
+            put(a, gv[a] + omega * ((sym + anti) - gv[a]));
+            put(a + 1, gv[a + 1] + omega * ((sym - anti) - gv[a + 1]));
+        }
+    });
+}
+
 // The nodes of one lane: lane_cell < ncell / CPT indexes the first band of
 // ny/CPT rows; the lane also takes the same (x, z) in the CPT - 1 bands below.
 // With MOMENTS the FP64 sums of (rho~ - 1, u) over these nodes are added to acc.
@@ -271,11 +343,7 @@ __device__ inline void collide_lane(const typename C::T *__restrict__ A,
                                     typename C::R omega, typename C::R enc_s, typename C::R dec_s,
                                     const ForceField &ff, typename C::R Gx, typename C::R Gy,
                                     typename C::R Gz, uint32_t lane_cell, double (&acc)[4]) {
-    // Multiply-adds fuse only within one expression: fusion across statements
-    // depends on how the compiler lays out the blocks, which differs between
-    // launch configurations, and every configuration must round each node the
-    // same way.
-#pragma clang fp contract(on)
+#pragma clang fp contract(on)  // as node_relax
     using T = typename C::T;
     using R = typename C::R;
     using V = typename C::V;
@@ -316,20 +384,12 @@ __device__ inline void collide_lane(const typename C::T *__restrict__ A,
             constexpr int a = decltype(ac)::value;
             gv[a] = C::dec(raw[c][a], dec_s);
         });
-        R drho = R(0), ux = R(0), uy = R(0), uz = R(0);
-        static_for<0, V::Q>([&](auto ac) {
-            constexpr int a = decltype(ac)::value;
-            drho += gv[a];
-            if constexpr (V::ex[a] != 0) ux += V::ex[a] > 0 ? gv[a] : -gv[a];
-            if constexpr (V::ey[a] != 0) uy += V::ey[a] > 0 ? gv[a] : -gv[a];
-            if constexpr (V::ez[a] != 0) uz += V::ez[a] > 0 ? gv[a] : -gv[a];
-        });
-        const R uu = ux * ux + uy * uy + uz * uz;
+        const NodeMoments<C> m = node_moments<C>(gv);
         if constexpr (MOMENTS) {
-            acc[0] += double(drho);
-            acc[1] += double(ux);
-            acc[2] += double(uy);
-            acc[3] += double(uz);
+            acc[0] += double(m.drho);
+            acc[1] += double(m.ux);
+            acc[2] += double(m.uy);
+            acc[3] += double(m.uz);
         }
         R Fx = Gx, Fy = Gy, Fz = Gz;
         if constexpr (FORCED) {
@@ -353,32 +413,7 @@ __device__ inline void collide_lane(const typename C::T *__restrict__ A,
             else
                 *p = C::enc(gn, enc_s);
         };
-        // BGK relaxation to the equilibrium of Eq. s2-eq plus the forcing term
-        // 3 w e.F, one opposite pair (a, a + 1) at a time: e_{a+1} = -e_a, so
-        // the even part of the equilibrium, w (drho + 4.5 (e.u)^2 - 1.5 u.u),
-        // is shared, and its odd part 3 w e.u and the forcing change sign.
-        const R base = drho - R(1.5) * uu;
-        put(0, gv[0] + omega * (V::template w<R>(0) * base - gv[0]));
-        static_for<0, (V::Q - 1) / 2>([&](auto pc) {
-            constexpr int a = 1 + 2 * decltype(pc)::value;
-            constexpr int cx = V::ex[a], cy = V::ey[a], cz = V::ez[a];
-            static_assert(V::ex[a + 1] == -cx && V::ey[a + 1] == -cy && V::ez[a + 1] == -cz,
-                          "opposite velocities are adjacent");
-            constexpr R w = V::template w<R>(a);
-            constexpr R w3 = R(3) * w;
-            R eu = R(0), eF = R(0);
-            if constexpr (cx != 0) eu += cx > 0 ? ux : -ux;
-            if constexpr (cy != 0) eu += cy > 0 ? uy : -uy;
-            if constexpr (cz != 0) eu += cz > 0 ? uz : -uz;
-            if constexpr (cx != 0) eF += cx > 0 ? Fx : -Fx;
-            if constexpr (cy != 0) eF += cy > 0 ? Fy : -Fy;
-            if constexpr (cz != 0) eF += cz > 0 ? Fz : -Fz;
-            const R sym = w * (base + R(4.5) * eu * eu);
-            const R anti = w3 * eu;
-            const R fa = w3 * eF;
-            put(a, gv[a] + omega * ((sym + anti) - gv[a]) + fa);
-            put(a + 1, gv[a + 1] + omega * ((sym - anti) - gv[a + 1]) - fa);
-        });
+        node_relax<C>(gv, m, omega, Fx, Fy, Fz, put);
     }
 }
 

@@ -35,14 +35,20 @@
 #include "adjoint.hpp"
 #include "codec.hpp"
 #include "collide.hpp"
+#include "collide_launch.hpp"
 #include "velocities.hpp"
 #include "pairs.hpp"
 #include "particle.hpp"
 #include "philox.hpp"
+#include "twostep_launch.hpp"
 
 namespace lbmbp {
 
 constexpr int kRedBlocks = 1024;
+// Node-force fields of a box: step n spreads into field n mod 3.  A two-step
+// sweep reads the fields of both its steps, so neither can be cleared before
+// it; the next particle update clears both and writes the third.
+constexpr int kForceFields = 3;
 
 // ---------------------------------------------------------------------------
 // Ensembles of independent boxes (replicas) of different sizes, stepped
@@ -143,11 +149,13 @@ __global__ __launch_bounds__(kParticleBlock) void k_ens_particle(
                                rp.g,
                                ForceField{force_cur + 3 * rp.cell_off, mask_cur + rp.mask_off},
                                ForceField{force_old + 3 * rp.cell_off, mask_old + rp.mask_off},
+                               ForceField{nullptr, nullptr},
                                rp.seed,
                                rp.replica_id,
                                uint32_t(ii) - rp.part_off,
                                rp.R};
-    particle_lane<C>(site, dec_s, pa, i, p, valid, r, V);
+    LatticeGather<C> gather{site.A, {}};
+    particle_lane<C>(site, gather, dec_s, pa, i, p, valid, r, V);
 }
 
 // ---------------------------------------------------------------------------
@@ -366,8 +374,8 @@ struct lbm_ctx {
     double enc_s, dec_s;
     double body[3];  // uniform body force on every node (lbm_set_body_force)
     // grid scratch
-    uint32_t *mask[2];
-    long long *force[2];  // [ncell][3] fixed-point node forces, alternating steps
+    uint32_t *mask[kForceFields];
+    long long *force[kForceFields];  // [ncell][3] fixed-point node forces, step n in field n mod 3
     uint32_t mask_words;
     double *partials;
     double *result;
@@ -377,7 +385,8 @@ struct lbm_ctx {
     lbm_particle_desc pdesc;
     double R;
     double *r, *v;
-    uint32_t *prev_cell;
+    uint32_t *cells[2];  // [n][8] nodes spread to in even and odd steps
+    int after_two;       // the last sweep was a two-step one: two fields to release
     double *fh, *fr;
     const double *fext;  // given force on each particle (lbm_set_particle_force) or null
     uint32_t warnings;   // LBM_WARN_* of the attached particles
@@ -401,6 +410,9 @@ struct lbm_ctx {
     int order;   // block order of the sweep (kOrderLinear / kOrderXcdSlabs)
     int cap;     // residency cap of the sweep: index into kResidencyCaps
     int lds_cu, lds_block;  // LDS bytes per compute unit and per block (device limits)
+    int two;     // two-step sweep: 0 never, else candidate two - 1 of two_step_candidates
+    int two_nts; // its populations written with non-temporal stores
+    TwoStepTiles two_tiles;
     int device;  // device current at lbm_init (autotune cache key)
     // recorded observables (lbm_series_config)
     int32_t series_every;
@@ -487,8 +499,8 @@ size_t fluid_partials_bytes(const lbm_grid_desc *g) {
 size_t grid_scratch_size(const lbm_grid_desc *g) {
     const size_t words = mask_words(ncell_of(g));
     size_t s = 0;
-    s += 2 * align_up(words * 4, kAlign);            // two bitmasks
-    s += 2 * force_field_bytes(g);                   // two node-force fields
+    s += kForceFields * align_up(words * 4, kAlign);  // bitmasks
+    s += kForceFields * force_field_bytes(g);         // node-force fields
     s += fluid_partials_bytes(g);                    // recorded-moment partials
     s += align_up(size_t(kSeriesBlocks) * 7 * 8, kAlign);
     s += align_up(size_t(kRedBlocks) * 4 * 8, kAlign);  // partials
@@ -549,7 +561,7 @@ PairList pair_list_at(char *s, int32_t n) {
 size_t particle_scratch_size(int32_t n) {
     if (n <= 0) return 0;
     size_t s = 0;
-    s += align_up(size_t(n) * 8 * 4, kAlign);  // prev cell
+    s += 2 * align_up(size_t(n) * 8 * 4, kAlign);  // nodes spread to, two steps
     s += align_up(particle_blocks(n) * 3 * 8, kAlign);  // momentum partials
     s += 2 * align_up(size_t(n) * 3 * 8, kAlign);  // fh, fr
     s += pair_list_bytes(n);                       // pair cell list
@@ -565,22 +577,6 @@ lbm_status launch_status() {
 }
 
 unsigned blocks_for(uint64_t n) { return unsigned((n + kBlock - 1) / kBlock); }
-// Launch configuration k of the stream-collide: CALL(nodes per lane, block,
-// non-temporal stores, row-aligned mapping).  Ensembles take k < 8 only.
-#define LBM_CONFIG_SWITCH(k, CALL)                  \
-    switch (k) {                                    \
-        case 1: CALL(1, 256, false, false); break;  \
-        case 2: CALL(2, 512, false, false); break;  \
-        case 3: CALL(2, 256, false, false); break;  \
-        case 4: CALL(1, 512, true, false); break;   \
-        case 5: CALL(1, 256, true, false); break;   \
-        case 6: CALL(2, 512, true, false); break;   \
-        case 7: CALL(2, 256, true, false); break;   \
-        case 8: CALL(1, 256, false, true); break;   \
-        case 9: CALL(1, 256, true, true); break;    \
-        default: CALL(1, 512, false, false); break; \
-    }
-
 // The row-aligned mapping places lanes exactly as configurations 1 and 5 do
 // when every 256-lane block holds whole rows that fill it (64 | nx and nx
 // divides 256) or every row fills whole blocks (256 | nx).
@@ -616,69 +612,36 @@ long residency_lds(int lds_cu, int lds_block, int cap, int bs) {
 
 long sweep_lds(const lbm_ctx *c, int cap, int bs) { return residency_lds(c->lds_cu, c->lds_block, cap, bs); }
 
-// Addressing of the sweep (kAddr* in collide.hpp).  The row-aligned mapping
-// always addresses by wavefront rows.  The flat mapping does so for 16-bit
-// storage when rows are whole wavefronts: there the per-lane index arithmetic
-// competes with the collision for the vector unit (FP16 step 1.8%, BF16 0.4%
-// faster by rows, measured A/B on one device).  FP32 and FP64 sweeps are
-// memory-bound, and per-lane indices measured as fast or faster (FP32 step
-// 0.9%: its sum-carrying launches run longer by rows); those are in 32 bits
-// unless the lattice holds 2^32 or more elements (Q nx ny nz; boxes beyond
-// about 226M nodes).
-int sweep_addr(const lbm_ctx *c, bool row_mapping) {
-    if (row_mapping || (c->elem == 2 && c->g.nx % 64 == 0)) return kAddrRow;
-    return uint64_t(c->q) * c->g.ncell >= (uint64_t(1) << 32) ? kAddrLane64 : kAddrLane32;
-}
-
-template <class C, bool FORCED, bool MOMENTS, int CPT, int BS, bool NTS, bool ROW, int ADDR>
-void launch_collide_addr(lbm_ctx *c, const typename C::T *A, typename C::T *B, ForceField ff,
-                         double *mom, unsigned grid, int order, size_t dyn) {
-    using R = typename C::R;
-    hipLaunchKernelGGL((k_stream_collide<C, FORCED, MOMENTS, CPT, BS, NTS, ROW, ADDR>), dim3(grid),
-                       dim3(BS), dyn, c->stream, A, B, c->g, R(c->omega), R(c->enc_s), R(c->dec_s),
-                       ff, R(c->body[0]), R(c->body[1]), R(c->body[2]), mom, uint32_t(order));
-}
-
-template <class C, bool FORCED, bool MOMENTS, int CPT, int BS, bool NTS, bool ROW>
-void launch_collide_shape(lbm_ctx *c, const typename C::T *A, typename C::T *B, ForceField ff,
-                          double *mom, unsigned grid, int order, int cap) {
-    const long lds = sweep_lds(c, cap, BS);
-    const size_t dyn = lds > 0 ? size_t(lds) : 0;
-    const int addr = sweep_addr(c, ROW);
-    if constexpr (ROW) {
-        launch_collide_addr<C, FORCED, MOMENTS, CPT, BS, NTS, ROW, kAddrRow>(c, A, B, ff, mom, grid, order, dyn);
-    } else {
-        if (addr == kAddrRow)
-            launch_collide_addr<C, FORCED, MOMENTS, CPT, BS, NTS, ROW, kAddrRow>(c, A, B, ff, mom, grid, order, dyn);
-        else if (addr == kAddrLane64)
-            launch_collide_addr<C, FORCED, MOMENTS, CPT, BS, NTS, ROW, kAddrLane64>(c, A, B, ff, mom, grid, order, dyn);
-        else
-            launch_collide_addr<C, FORCED, MOMENTS, CPT, BS, NTS, ROW, kAddrLane32>(c, A, B, ff, mom, grid, order, dyn);
-    }
-}
-
-// mom != nullptr: also leave the per-wavefront FP64 moment sums there.  order,
-// cap: block order and residency cap (-1: the context's).
+// One stream-collide launch A -> B.  mom != nullptr: also leave the
+// per-wavefront FP64 moment sums there.  order, cap: block order and residency
+// cap (-1: the context's).
 template <class C, bool FORCED>
 void launch_collide(lbm_ctx *c, const typename C::T *A, typename C::T *B, ForceField ff, int shape,
                     double *mom = nullptr, int order = -1, int cap = -1) {
-    const unsigned grid = collide_grid(c, shape);
-    if (order < 0) order = c->order;
-    if (cap < 0) cap = c->cap;
-#define LBM_SHAPE(CPT, BS, NTS, ROW)                                                           \
-    do {                                                                                       \
-        if (mom)                                                                               \
-            launch_collide_shape<C, FORCED, true, CPT, BS, NTS, ROW>(c, A, B, ff, mom, grid,    \
-                                                                     order, cap);              \
-        else                                                                                   \
-            launch_collide_shape<C, FORCED, false, CPT, BS, NTS, ROW>(c, A, B, ff, mom, grid,   \
-                                                                      order, cap);             \
-    } while (0)
-    LBM_CONFIG_SWITCH(shape, LBM_SHAPE)
-#undef LBM_SHAPE
+    CollideArgs a;
+    a.A = A;
+    a.B = B;
+    a.g = c->g;
+    a.omega = c->omega;
+    a.enc_s = c->enc_s;
+    a.dec_s = c->dec_s;
+    for (int k = 0; k < 3; ++k) a.body[k] = c->body[k];
+    a.ff = ff;
+    a.mom = mom;
+    a.shape = shape;
+    a.grid = collide_grid(c, shape);
+    a.order = order < 0 ? c->order : order;
+    const long lds = sweep_lds(c, cap < 0 ? c->cap : cap, config_block(shape));
+    a.dyn = lds > 0 ? size_t(lds) : 0;
+    a.stream = c->stream;
+    launch_stream_collide<C, FORCED>(a);
 }
 
-ForceField field(lbm_ctx *c, int par) { return ForceField{c->force[par], c->mask[par]}; }
+// Node-force field of step n.
+ForceField field(lbm_ctx *c, int64_t n) {
+    const int k = int(n % kForceFields);
+    return ForceField{c->force[k], c->mask[k]};
+}
 
 // Blocks for the neighbour sums: kPairLanes lanes per particle.
 dim3 pair_group_blocks(int32_t n) {
@@ -727,73 +690,93 @@ void prof_stop(lbm_ctx *c, int32_t k) {
     if (k >= 0) (void)hipEventRecord(c->prof_ev[2 * k + 1], c->stream);
 }
 
+// Whether the state at the start of the step `ahead` steps from now is to be
+// recorded (no recording in between).
+bool sample_at(const lbm_ctx *c, int64_t ahead) {
+    return c->series_every > 0 && (c->series_t + ahead) % c->series_every == 0 && c->series_count < c->series_cap;
+}
+
+// Arguments of this step's particle update; advances the VACF clock.
+ParticleArgs step_particle_args(lbm_ctx *c) {
+    ParticleArgs pa;
+    pa.pmom = nullptr;
+    pa.acc = nullptr;
+    pa.origins = nullptr;
+    pa.t = pa.k_lo = 0;
+    pa.k_hi = -1;
+    pa.nslot = pa.stride = 1;
+    pa.max_lag = 0;
+    pa.slot_lo = 0;
+    if (c->vacf_on) {
+        // active origins k*stride with t - max_lag <= k*stride <= t
+        const int64_t t = c->vacf_t;
+        pa.acc = c->acc;
+        pa.origins = c->origins;
+        pa.t = t;
+        pa.k_hi = t / c->stride;
+        pa.k_lo = t > c->max_lag ? (t - c->max_lag + c->stride - 1) / c->stride : 0;
+        pa.nslot = c->nslot;
+        pa.slot_lo = int32_t(pa.k_lo % c->nslot);
+        pa.stride = c->stride;
+        pa.max_lag = c->max_lag;
+        c->vacf_t += 1;
+    }
+    pa.r = c->r;
+    pa.v = c->v;
+    pa.fh = c->fh;
+    pa.fr = c->fr;
+    // this step's nodes, and those still to be released: the last step's, and
+    // after a two-step sweep the one's before it (kept where this step's go)
+    pa.cells = c->cells[c->step & 1];
+    pa.last_cells = c->cells[(c->step & 1) ^ 1];
+    pa.older_cells = c->after_two ? pa.cells : nullptr;
+    pa.err = c->err;
+    pa.n = c->np;
+    pa.friction = c->pdesc.friction;
+    pa.mass = c->pdesc.mass;
+    pa.gamma = c->pdesc.gamma;
+    pa.sig = c->pdesc.kT > 0.0 ? sqrt(2.0 * c->pdesc.gamma * c->pdesc.kT) : 0.0;
+    pa.R = c->R;
+    pa.seed = c->pdesc.seed;
+    pa.replica = c->pdesc.replica;
+    pa.step = uint32_t(c->step);
+    pa.fext = c->fext;
+    pa.fpair = nullptr;
+    if (c->pair_on) {
+        launch_pairs(c->stream, c->r, c->np, c->pg, c->plist, c->fpair);
+        pa.fpair = c->fpair;
+    }
+    return pa;
+}
+
+template <class C>
+void launch_particle(lbm_ctx *c, const typename C::T *A, const ParticleArgs &pa, int64_t n) {
+    hipLaunchKernelGGL(k_particle<C>, dim3(unsigned(particle_blocks(c->np))), dim3(kParticleBlock), 0, c->stream, A,
+                       c->g, typename C::R(c->dec_s), pa, field(c, n), field(c, n + 2), field(c, n + 1));
+}
+
 template <class C>
 void launch_step(lbm_ctx *c) {
     using T = typename C::T;
-    using R = typename C::R;
     const T *A = static_cast<const T *>(c->pop[c->cur]);
     T *B = static_cast<T *>(c->pop[c->cur ^ 1]);
-    const int par = int(c->step & 1);
     // Record the observables of the state at the start of this step?
-    const bool sample = c->series_every > 0 && c->series_t % c->series_every == 0 &&
-                        c->series_count < c->series_cap;
+    const bool sample = sample_at(c, 0);
     if (c->series_every > 0) c->series_t += 1;
     double *mom = sample ? c->fluid_partials : nullptr;
     if (c->np > 0) {
         const int32_t pk = prof_start(c, 1);
-        ParticleArgs pa;
+        ParticleArgs pa = step_particle_args(c);
         pa.pmom = sample ? c->part_partials : nullptr;
-        pa.acc = nullptr;
-        pa.origins = nullptr;
-        pa.t = pa.k_lo = 0;
-        pa.k_hi = -1;
-        pa.nslot = pa.stride = 1;
-        pa.max_lag = 0;
-        pa.slot_lo = 0;
-        if (c->vacf_on) {
-            // active origins k*stride with t - max_lag <= k*stride <= t
-            const int64_t t = c->vacf_t;
-            pa.acc = c->acc;
-            pa.origins = c->origins;
-            pa.t = t;
-            pa.k_hi = t / c->stride;
-            pa.k_lo = t > c->max_lag ? (t - c->max_lag + c->stride - 1) / c->stride : 0;
-            pa.nslot = c->nslot;
-            pa.slot_lo = int32_t(pa.k_lo % c->nslot);
-            pa.stride = c->stride;
-            pa.max_lag = c->max_lag;
-            c->vacf_t += 1;
-        }
-        pa.r = c->r;
-        pa.v = c->v;
-        pa.fh = c->fh;
-        pa.fr = c->fr;
-        pa.prev_cell = c->prev_cell;
-        pa.err = c->err;
-        pa.n = c->np;
-        pa.friction = c->pdesc.friction;
-        pa.mass = c->pdesc.mass;
-        pa.gamma = c->pdesc.gamma;
-        pa.sig = c->pdesc.kT > 0.0 ? sqrt(2.0 * c->pdesc.gamma * c->pdesc.kT) : 0.0;
-        pa.R = c->R;
-        pa.seed = c->pdesc.seed;
-        pa.replica = c->pdesc.replica;
-        pa.step = uint32_t(c->step);
-        pa.fext = c->fext;
-        pa.fpair = nullptr;
-        if (c->pair_on) {
-            launch_pairs(c->stream, c->r, c->np, c->pg, c->plist, c->fpair);
-            pa.fpair = c->fpair;
-        }
-        hipLaunchKernelGGL(k_particle<C>, dim3(unsigned((uint64_t(c->np) * 8 + kParticleBlock - 1) / kParticleBlock)), dim3(kParticleBlock), 0,
-                           c->stream, A, c->g, R(c->dec_s), pa, field(c, par), field(c, par ^ 1));
+        launch_particle<C>(c, A, pa, c->step);
+        c->after_two = 0;
         prof_stop(c, pk);
         const int32_t ck = prof_start(c, 0);
-        launch_collide<C, true>(c, A, B, field(c, par), c->shape, mom);
+        launch_collide<C, true>(c, A, B, field(c, c->step), c->shape, mom);
         prof_stop(c, ck);
     } else {
         const int32_t ck = prof_start(c, 0);
-        launch_collide<C, false>(c, A, B, field(c, par), c->shape, mom);
+        launch_collide<C, false>(c, A, B, field(c, c->step), c->shape, mom);
         prof_stop(c, ck);
     }
     if (sample) {
@@ -807,6 +790,57 @@ void launch_step(lbm_ctx *c) {
                            double(c->g.ncell), double(c->step), c->series + 8 * c->series_count);
         c->series_count += 1;
     }
+    c->cur ^= 1;
+    c->step += 1;
+}
+
+TwoStepArgs two_step_args(lbm_ctx *c, const TwoStepTiles &tl, bool nts, ForceField f0, ForceField f1) {
+    TwoStepArgs a;
+    a.A = c->pop[c->cur];
+    a.B = c->pop[c->cur ^ 1];
+    a.g = c->g;
+    a.omega = c->omega;
+    a.enc_s = c->enc_s;
+    a.dec_s = c->dec_s;
+    for (int k = 0; k < 3; ++k) a.body[k] = c->body[k];
+    a.f0 = f0;
+    a.f1 = f1;
+    a.tl = tl;
+    a.forced = c->np > 0;
+    a.nts = nts;
+    a.stream = c->stream;
+    return a;
+}
+
+// Steps n and n + 1 in one sweep, neither of them recorded: both particle
+// updates first (the second on the fluid around the particles one step ahead),
+// then the two-step sweep.
+template <class C>
+void launch_two_step(lbm_ctx *c) {
+    const TwoStepArgs a = two_step_args(c, c->two_tiles, c->two_nts != 0, field(c, c->step), field(c, c->step + 1));
+    if (c->series_every > 0) c->series_t += 2;
+    if (c->np > 0) {
+        const typename C::T *A = static_cast<const typename C::T *>(a.A);
+        int32_t pk = prof_start(c, 1);
+        launch_particle<C>(c, A, step_particle_args(c), c->step);
+        prof_stop(c, pk);
+        c->step += 1;
+        c->after_two = 0;
+        pk = prof_start(c, 1);
+        ParticleArgs pa = step_particle_args(c);
+        pa.last_cells = nullptr;  // the field of step n is still to be read
+        if (c->pdesc.friction == LBM_FRICTION_BD)
+            launch_particle<C>(c, A, pa, c->step);  // reads no fluid
+        else
+            launch_particle_ahead<C>(a, pa);
+        prof_stop(c, pk);
+        c->after_two = 1;
+    } else {
+        c->step += 1;
+    }
+    const int32_t ck = prof_start(c, 0);
+    launch_two_steps<C>(a);
+    prof_stop(c, ck);
     c->cur ^= 1;
     c->step += 1;
 }
@@ -827,7 +861,7 @@ void time_launches(lbm_ctx *c, int32_t iters, int n, const int *ks, const int *o
     if (*err == hipSuccess) *err = hipEventCreate(&e1);
     if (*err != hipSuccess) return;
     const bool forced = c->np > 0;
-    const ForceField last = field(c, int((c->step + 1) & 1));
+    const ForceField last = field(c, c->step + 2);  // of step - 1
     for (int j = 0; j < n && *err == hipSuccess; ++j) {
         const int k = ks[j], order = orders[j], cap = caps[j];
         ms[j] = -1.0;
@@ -858,15 +892,18 @@ void time_launches(lbm_ctx *c, int32_t iters, int n, const int *ks, const int *o
 template <class C, int CPT, int BS, bool NTS, bool ROW>
 void stream_only_shape(lbm_ctx *c, const typename C::T *A, typename C::T *B, unsigned grid,
                        uint32_t order, size_t dyn) {
-    const int addr = sweep_addr(c, ROW);
+    const int addr = sweep_addr<C>(c->g, ROW);
     if constexpr (ROW) {
         hipLaunchKernelGGL((k_stream_only<C, CPT, BS, NTS, ROW, kAddrRow>), dim3(grid), dim3(BS), dyn,
                            c->stream, A, B, c->g, order);
     } else {
-        if (addr == kAddrRow)
-            hipLaunchKernelGGL((k_stream_only<C, CPT, BS, NTS, ROW, kAddrRow>), dim3(grid), dim3(BS), dyn,
-                               c->stream, A, B, c->g, order);
-        else if (addr == kAddrLane64)
+        if constexpr (sizeof(typename C::T) == 2)
+            if (addr == kAddrRow) {
+                hipLaunchKernelGGL((k_stream_only<C, CPT, BS, NTS, ROW, kAddrRow>), dim3(grid), dim3(BS), dyn,
+                                   c->stream, A, B, c->g, order);
+                return;
+            }
+        if (addr == kAddrLane64)
             hipLaunchKernelGGL((k_stream_only<C, CPT, BS, NTS, ROW, kAddrLane64>), dim3(grid), dim3(BS),
                                dyn, c->stream, A, B, c->g, order);
         else
@@ -896,6 +933,28 @@ void time_stream_only(lbm_ctx *c, int k, int32_t iters, double *ms, hipError_t *
     for (int w = 0; w < 2; ++w) launch();
     (void)hipEventRecord(e0, c->stream);
     for (int it = 0; it < iters; ++it) launch();
+    (void)hipEventRecord(e1, c->stream);
+    *err = hipEventSynchronize(e1);
+    float t = 0.0f;
+    if (*err == hipSuccess) *err = hipEventElapsedTime(&t, e0, e1);
+    *ms = double(t) / iters;
+    (void)hipEventDestroy(e0);
+    (void)hipEventDestroy(e1);
+}
+
+// Mean time per two-step sweep with these tiles and store policy over iters
+// launches (A -> B, as time_launches).
+template <class C>
+void time_two_steps(lbm_ctx *c, const TwoStepTiles &tl, bool nts, int32_t iters, double *ms, hipError_t *err) {
+    const ForceField last = field(c, c->step + 2);
+    const TwoStepArgs a = two_step_args(c, tl, nts, last, last);
+    hipEvent_t e0, e1;
+    *err = hipEventCreate(&e0);
+    if (*err == hipSuccess) *err = hipEventCreate(&e1);
+    if (*err != hipSuccess) return;
+    for (int w = 0; w < 2; ++w) launch_two_steps<C>(a);
+    (void)hipEventRecord(e0, c->stream);
+    for (int it = 0; it < iters; ++it) launch_two_steps<C>(a);
     (void)hipEventRecord(e1, c->stream);
     *err = hipEventSynchronize(e1);
     float t = 0.0f;
@@ -1122,6 +1181,85 @@ lbm_status set_layout(lbm_ctx *c, uint32_t Y) {
     return err != hipSuccess ? LBM_E_DEVICE : st;
 }
 
+// ---- two-step sweep: tiles and when it is used ----
+
+// Tiles of the two-step sweep for a box, best first by a cost model: a block
+// takes lz + 2 planes, a plane costs a fixed part (its barrier and the latency
+// it exposes) plus the wavefronts' arithmetic and the 128-byte lines its row
+// pieces touch; blocks run one per compute unit (the LDS and registers of a
+// block this size allow no second one), so whole rounds of 256 count.
+// Fitted to probe timings (FP32, us per plane: 128 x 4 tiles 3.7, 64 x 8 3.9,
+// 64 x 10 4.3, 96 x 6 3.95).
+constexpr int kTwoStepCandidates = 4;
+constexpr uint32_t kTwoStepUnits = 256;
+
+int two_step_candidates(const lbm_grid_desc *g, TwoStepTiles *out) {
+    const uint32_t nx = uint32_t(g->nx), ny = uint32_t(g->ny), nz = uint32_t(g->nz);
+    const size_t elem = elem_size(g->storage);
+    const uint32_t most = two_step_nodes(elem);
+    // 32-bit byte offsets within a plane
+    if (uint64_t(nx) * ny * uint64_t(velocity_count(g)) * elem >= (uint64_t(1) << 32)) return 0;
+    struct Cand {
+        TwoStepTiles tl;
+        double cost;
+    };
+    std::vector<Cand> all;
+    for (uint32_t ntx = 1; ntx <= nx; ++ntx) {
+        const uint32_t tx = (nx + ntx - 1) / ntx;
+        if (tx < 16 && ntx > 1) break;
+        if ((tx + 2) * 3 > most || (nx + tx - 1) / tx != ntx) continue;
+        for (uint32_t nty = 1; nty <= ny; ++nty) {
+            const uint32_t ty = (ny + nty - 1) / nty;
+            if ((tx + 2) * (ty + 2) > most || (ny + ty - 1) / ty != nty) continue;
+            const double lines = (ty + 2) * ((tx + 2) * double(elem) / 128.0 + 1.5);
+            const double waves = ((tx + 2) * (ty + 2) + 63) / 64 + (tx * ty + 63) / 64;
+            const double plane = 10.0 + 0.6 * lines + 0.6 * waves;
+            Cand best{{}, -1.0};
+            for (uint32_t ns = 1; ns <= nz; ++ns) {
+                const uint32_t lz = (nz + ns - 1) / ns;
+                if ((nz + lz - 1) / lz != ns) continue;
+                const uint64_t blocks = uint64_t(ntx) * nty * ns;
+                const double rounds = double((blocks + kTwoStepUnits - 1) / kTwoStepUnits);
+                const double cost = rounds * (lz + 2.0) * plane;
+                if (best.cost < 0.0 || cost < best.cost) best = Cand{{tx, ty, lz, ntx, nty, ns}, cost};
+                if (blocks > 16 * kTwoStepUnits) break;
+            }
+            if (best.cost > 0.0) all.push_back(best);
+        }
+    }
+    std::sort(all.begin(), all.end(), [](const Cand &x, const Cand &y) { return x.cost < y.cost; });
+    const int n = int(std::min<size_t>(kTwoStepCandidates, all.size()));
+    for (int k = 0; k < n; ++k) out[k] = all[k].tl;
+    return n;
+}
+
+// Boxes of fewer nodes than this take single steps until tuned.
+constexpr uint64_t kTwoStepMinNodes = uint64_t(1) << 17;
+
+int two_step_default(const lbm_grid_desc *g) {
+    TwoStepTiles tl[kTwoStepCandidates];
+    return (ncell_of(g) >= kTwoStepMinNodes && two_step_candidates(g, tl) > 0) ? 1 : 0;
+}
+
+TwoStepTiles two_step_tiles(const lbm_grid_desc *g, int &two) {
+    TwoStepTiles tl[kTwoStepCandidates] = {};
+    if (two > two_step_candidates(g, tl)) two = 0;
+    return tl[two > 0 ? two - 1 : 0];
+}
+
+// Nodes per particle from which a two-step sweep pays for its particle update
+// one step ahead.
+constexpr double kTwoStepNodesPerParticle = 300.0;
+
+bool two_step_pays(const lbm_ctx *c) {
+    return c->np == 0 || c->pdesc.friction == LBM_FRICTION_BD ||
+           double(c->g.ncell) >= kTwoStepNodesPerParticle * double(c->np);
+}
+
+// The remembered code of a box holds, above the single-step launch, the
+// two-step choice: 2 * candidate + store policy, plus one.
+constexpr int kTuneTwo = kNumShapes * int(kNumOrders) * kNumCaps * (kMaxRowsLog2 + 1);
+
 TuneKey ctx_tune_key(const lbm_ctx *c) {
     return TuneKey{0, c->device, c->desc.storage, c->q, {c->desc.nx, c->desc.ny, c->desc.nz}};
 }
@@ -1162,7 +1300,11 @@ lbm_status lbm_init(const lbm_grid_desc *grid, void *pop_a, void *pop_b, void *g
         c->order = (code / kNumShapes) % int(kNumOrders);
         c->cap = (code / (kNumShapes * int(kNumOrders))) % kNumCaps;
         // the remembered layout, applied once the lattices are at rest below
-        init_rows = uint32_t(1) << (code / (kNumShapes * int(kNumOrders) * kNumCaps));
+        init_rows = uint32_t(1) << ((code / (kNumShapes * int(kNumOrders) * kNumCaps)) % (kMaxRowsLog2 + 1));
+        const int two = code / kTuneTwo;  // remembered two-step choice + 1, 0: none
+        c->two = two > 0 ? (two - 1) / 2 : two_step_default(grid);
+        c->two_nts = two > 0 ? (two - 1) % 2 : lat >= kStreamStoreBytes;
+        c->two_tiles = two_step_tiles(grid, c->two);
         if (grid->ny % int32_t(init_rows) != 0) init_rows = 1;
         // LDS limits of the device, for the residency caps (none if unknown)
         int v = 0;
@@ -1186,14 +1328,14 @@ lbm_status lbm_init(const lbm_grid_desc *grid, void *pop_a, void *pop_b, void *g
     }
     char *s = static_cast<char *>(grid_scratch);
     c->mask_words = mask_words(c->g.ncell);
-    c->mask[0] = reinterpret_cast<uint32_t *>(s);
-    s += align_up(size_t(c->mask_words) * 4, kAlign);
-    c->mask[1] = reinterpret_cast<uint32_t *>(s);
-    s += align_up(size_t(c->mask_words) * 4, kAlign);
-    c->force[0] = reinterpret_cast<long long *>(s);
-    s += force_field_bytes(grid);
-    c->force[1] = reinterpret_cast<long long *>(s);
-    s += force_field_bytes(grid);
+    for (int k = 0; k < kForceFields; ++k) {
+        c->mask[k] = reinterpret_cast<uint32_t *>(s);
+        s += align_up(size_t(c->mask_words) * 4, kAlign);
+    }
+    for (int k = 0; k < kForceFields; ++k) {
+        c->force[k] = reinterpret_cast<long long *>(s);
+        s += force_field_bytes(grid);
+    }
     c->fluid_partials = reinterpret_cast<double *>(s);
     s += fluid_partials_bytes(grid);
     // every configuration's grid must fit the per-wavefront partials
@@ -1278,14 +1420,12 @@ lbm_status particles_couple(lbm_ctx *ctx, const lbm_particle_desc *d, double *r,
             return LBM_E_INVAL;
     }
     // Node forces left by any previous particle set are cleared.
-    hipError_t e = hipMemsetAsync(ctx->mask[0], 0, size_t(ctx->mask_words) * 4, ctx->stream);
+    // (the fields lie back to back: the masks, then the forces)
+    hipError_t e = hipMemsetAsync(ctx->mask[0], 0, kForceFields * align_up(size_t(ctx->mask_words) * 4, kAlign), ctx->stream);
     if (e == hipSuccess)
-        e = hipMemsetAsync(ctx->mask[1], 0, size_t(ctx->mask_words) * 4, ctx->stream);
-    if (e == hipSuccess)
-        e = hipMemsetAsync(ctx->force[0], 0, force_field_bytes(&ctx->desc), ctx->stream);
-    if (e == hipSuccess)
-        e = hipMemsetAsync(ctx->force[1], 0, force_field_bytes(&ctx->desc), ctx->stream);
+        e = hipMemsetAsync(ctx->force[0], 0, kForceFields * force_field_bytes(&ctx->desc), ctx->stream);
     if (e != hipSuccess) return LBM_E_DEVICE;
+    ctx->after_two = 0;
     ctx->vacf_on = 0;
     ctx->fext = nullptr;
     ctx->pair_on = 0;
@@ -1303,8 +1443,10 @@ lbm_status particles_couple(lbm_ctx *ctx, const lbm_particle_desc *d, double *r,
     ctx->r = r;
     ctx->v = v;
     char *s = static_cast<char *>(particle_scratch);
-    ctx->prev_cell = reinterpret_cast<uint32_t *>(s);
-    s += align_up(size_t(d->n) * 8 * 4, kAlign);
+    for (int k = 0; k < 2; ++k) {
+        ctx->cells[k] = reinterpret_cast<uint32_t *>(s);
+        s += align_up(size_t(d->n) * 8 * 4, kAlign);
+    }
     ctx->part_partials = reinterpret_cast<double *>(s);
     s += align_up(particle_blocks(d->n) * 3 * 8, kAlign);
     ctx->fh = reinterpret_cast<double *>(s);
@@ -1314,8 +1456,8 @@ lbm_status particles_couple(lbm_ctx *ctx, const lbm_particle_desc *d, double *r,
     ctx->plist = pair_list_at(s, d->n);
     s += pair_list_bytes(d->n);
     ctx->fpair = reinterpret_cast<double *>(s);
-    // prev_cell -> kNoNode (all ones); forces and bucket counts zero.
-    e = hipMemsetAsync(ctx->prev_cell, 0xFF, size_t(d->n) * 8 * 4, ctx->stream);
+    // nodes spread to -> kNoNode (all ones); forces and bucket counts zero.
+    e = hipMemsetAsync(ctx->cells[0], 0xFF, 2 * align_up(size_t(d->n) * 8 * 4, kAlign), ctx->stream);
     if (e == hipSuccess)
         e = hipMemsetAsync(ctx->plist.count, 0, size_t(pair_buckets(d->n)) * 4, ctx->stream);
     if (e == hipSuccess) e = hipMemsetAsync(ctx->fh, 0, size_t(d->n) * 3 * 8, ctx->stream);
@@ -1411,9 +1553,48 @@ lbm_status lbm_vacf_counts(const lbm_ctx *ctx, int64_t *cnt) {
     return LBM_OK;
 }
 
+}  // extern "C"
+
+namespace {
+
+// Takes n steps, two at a time where the box has a two-step sweep, its
+// particles are few enough (two_step_pays) and neither step is recorded.  An
+// even number of two-step sweeps per call keeps the rule that n steps leave
+// the state in the lattice n swaps away.
+void advance(lbm_ctx *c, int32_t n) {
+    int32_t twos = 0;
+    if (c->two > 0 && two_step_pays(c)) {
+        int64_t count = c->series_count;
+        auto sampled = [&](int32_t s) {
+            return c->series_every > 0 && (c->series_t + s) % c->series_every == 0 && count < c->series_cap;
+        };
+        for (int32_t s = 0; s + 1 < n;) {
+            const bool now = sampled(s), two = !now && !sampled(s + 1);
+            count += now;
+            twos += two;
+            s += two ? 2 : 1;
+        }
+        twos &= ~1;
+    }
+    for (int32_t left = n; left > 0;) {
+        if (twos > 0 && left >= 2 && !sample_at(c, 0) && !sample_at(c, 1)) {
+            LBM_DISPATCH(c, launch_two_step);
+            --twos;
+            left -= 2;
+        } else {
+            LBM_DISPATCH(c, launch_step);
+            --left;
+        }
+    }
+}
+
+}  // namespace
+
+extern "C" {
+
 lbm_status lbm_step(lbm_ctx *ctx, int32_t nsteps) {
     if (!ctx || nsteps < 0) return LBM_E_INVAL;
-    for (int32_t s = 0; s < nsteps; ++s) LBM_DISPATCH(ctx, launch_step);
+    advance(ctx, nsteps);
     return launch_status();
 }
 
@@ -1584,7 +1765,27 @@ lbm_status lbm_autotune(lbm_ctx *ctx, int32_t iters, double *ms, int32_t *chosen
     ctx->shape = best.k;
     ctx->order = best.o;
     ctx->cap = best.c;
-    tune_store(ctx_tune_key(ctx), tune_code(best.k, best.o, best.c, rows_log2(ctx->g)));
+    // Two-step sweep: the fastest of its tiles and store policies, if two
+    // steps in it are faster than two launches of the choice above.
+    {
+        TwoStepTiles tl[kTwoStepCandidates];
+        const int nt = two_step_candidates(&ctx->desc, tl);
+        double two_best = 2.0 * total[jb] / 2.0;  // total: two timings of one step each
+        ctx->two = 0;
+        for (int j = 0; j < 2 * nt; ++j) {
+            double v = 0.0;
+            LBM_DISPATCH(ctx, time_two_steps, tl[j / 2], (j & 1) != 0, iters, &v, &err);
+            if (err != hipSuccess || launch_status() != LBM_OK) return LBM_E_DEVICE;
+            if (v > 0.0 && v < two_best) {
+                two_best = v;
+                ctx->two = j / 2 + 1;
+                ctx->two_nts = j & 1;
+                ctx->two_tiles = tl[j / 2];
+            }
+        }
+    }
+    tune_store(ctx_tune_key(ctx), tune_code(best.k, best.o, best.c, rows_log2(ctx->g)) +
+                                      kTuneTwo * (2 * ctx->two + ctx->two_nts + 1));
     if (ms)
         for (int k = 0; k < kNumShapes; ++k) ms[k] = best_k[k];
     if (chosen) *chosen = best.k;
@@ -1852,7 +2053,8 @@ ParticleArgs ens_particle_args(lbm_ens *e) {
     pa.v = e->v;
     pa.fh = e->fh;
     pa.fr = e->fr;
-    pa.prev_cell = e->prev_cell;
+    pa.cells = e->prev_cell;
+    pa.last_cells = e->prev_cell;
     pa.err = e->err;
     pa.n = e->n;
     pa.friction = e->desc.friction;
@@ -2742,7 +2944,9 @@ hipError_t adjoint_run(lbm_ctx *c, char *tape, char *work, double *adj_pop, doub
     ParticleArgs pa{};
     pa.fh = reinterpret_cast<double *>(at(L.fh));
     pa.fr = reinterpret_cast<double *>(at(L.fr));
-    pa.prev_cell = prev_fwd;
+    pa.cells = prev_fwd;
+    pa.last_cells = prev_fwd;
+    pa.older_cells = nullptr;
     pa.err = c->err;
     pa.n = np;
     pa.friction = pd.friction;
@@ -2815,7 +3019,7 @@ hipError_t adjoint_run(lbm_ctx *c, char *tape, char *work, double *adj_pop, doub
                     pa.fpair = fpair;
                 }
                 hipLaunchKernelGGL(k_particle<C>, dim3(pgrid), dim3(kParticleBlock), 0, st, seg(k),
-                                   c->g, R(c->dec_s), pa, ff[par], ff[par ^ 1]);
+                                   c->g, R(c->dec_s), pa, ff[par], ff[par ^ 1], ff[par]);
                 launch_collide<C, true>(c, seg(k), seg(k + 1), ff[par], c->shape);
             } else {
                 launch_collide<C, false>(c, seg(k), seg(k + 1), ff[0], c->shape);
@@ -2903,23 +3107,18 @@ lbm_status lbm_record(lbm_ctx *ctx, int32_t nsteps, int32_t every, void *tape) {
     ctx->rec_rows = ctx->g.ymask + 1;
     const size_t pbytes = size_t(ctx->np) * 3 * 8;
     char *tp = static_cast<char *>(tape);
-    for (int32_t s = 0; s < nsteps; ++s) {
-        if (s % every == 0) {
-            char *slot = tp + size_t(s / every) * t.slot;
-            hipError_t e = hipMemcpyAsync(slot, ctx->pop[ctx->cur], t.lat,
-                                          hipMemcpyDeviceToDevice, ctx->stream);
-            if (e == hipSuccess && pbytes)
-                e = hipMemcpyAsync(slot + t.lat, ctx->r, pbytes, hipMemcpyDeviceToDevice,
-                                   ctx->stream);
-            if (e == hipSuccess && pbytes)
-                e = hipMemcpyAsync(slot + t.lat + pbytes, ctx->v, pbytes,
-                                   hipMemcpyDeviceToDevice, ctx->stream);
-            if (e != hipSuccess) {
-                ctx->rec_tape = nullptr;
-                return LBM_E_DEVICE;
-            }
+    for (int64_t s = 0; s < nsteps; s += every) {
+        char *slot = tp + size_t(s / every) * t.slot;
+        hipError_t e = hipMemcpyAsync(slot, ctx->pop[ctx->cur], t.lat, hipMemcpyDeviceToDevice, ctx->stream);
+        if (e == hipSuccess && pbytes)
+            e = hipMemcpyAsync(slot + t.lat, ctx->r, pbytes, hipMemcpyDeviceToDevice, ctx->stream);
+        if (e == hipSuccess && pbytes)
+            e = hipMemcpyAsync(slot + t.lat + pbytes, ctx->v, pbytes, hipMemcpyDeviceToDevice, ctx->stream);
+        if (e != hipSuccess) {
+            ctx->rec_tape = nullptr;
+            return LBM_E_DEVICE;
         }
-        LBM_DISPATCH(ctx, launch_step);
+        advance(ctx, int32_t(std::min<int64_t>(every, nsteps - s)));
     }
     return launch_status();
 }

@@ -28,7 +28,10 @@ constexpr uint32_t kNoNode = 0xFFFFFFFFu;
 struct ParticleArgs {
     double *r, *v;
     double *fh, *fr;
-    uint32_t *prev_cell;  // [n][8] node each lane spread to last step, or kNoNode
+    uint32_t *cells;  // [n][8] out: node each lane spread to this step, or kNoNode
+    // [n][8] nodes spread to in the last step and in the one before (nullptr:
+    // nothing to release there); either may be `cells` itself
+    const uint32_t *last_cells, *older_cells;
     uint32_t *err;
     int32_t n;
     int32_t friction;
@@ -165,35 +168,59 @@ template <class C>
 struct ParticleSite {
     const typename C::T *A;
     Grid g;
-    ForceField cur, old;
+    ForceField cur, last, older;  // this step's node forces, the last step's, those before
     uint64_t seed;
     uint32_t replica;  // third counter word
     uint32_t index;    // second counter word: particle index within its box
     double R;          // particle radius used by the fit
 };
 
+// Clears one node of a consumed node-force field.
+__device__ inline void release_node(const ForceField &old, uint32_t pc) {
+    if (pc == kNoNode) return;
+    old.f[3 * uint64_t(pc) + 0] = 0;
+    old.f[3 * uint64_t(pc) + 1] = 0;
+    old.f[3 * uint64_t(pc) + 2] = 0;
+    atomicAnd(&old.mask[pc >> 5], ~(1u << (pc & 31)));
+}
+
+// The gather of a plain step: f^n at the lane's fitting node, read from the
+// lattice as soon as the node is known and consumed when it is needed.
+template <class C>
+struct LatticeGather {
+    const typename C::T *__restrict__ A;
+    typename C::T raw[C::V::Q];
+    __device__ inline void issue(const uint32_t (&node)[3], const Grid &g) {
+        const Neighbours nb(node[0], node[1], node[2], g);
+        static_for<1, C::V::Q>([&](auto ac) {
+            constexpr int a = decltype(ac)::value;
+            raw[a] = A[nb.template pop<typename C::V, a>(g)];
+        });
+    }
+    __device__ inline void wait() {}
+    template <int a>
+    __device__ inline typename C::T get() const {
+        return raw[a];
+    }
+};
+
 // One lane (node p of particle i) of the coupled particle update.  r, V are
 // the particle's position and velocity at the start of the step; the whole
 // 8-lane group must call this together (it shuffles within the group).
-template <class C>
-__device__ inline void particle_lane(const ParticleSite<C> &site, typename C::R dec_s,
+// gather supplies f^n at the lane's fitting node (every wavefront that calls
+// this reaches its wait()).
+template <class C, class Gather>
+__device__ inline void particle_lane(const ParticleSite<C> &site, Gather &gather, typename C::R dec_s,
                                      const ParticleArgs &pa, int32_t i, int p, bool valid,
                                      const double (&r)[3], const double (&V)[3]) {
     using Vs = typename C::V;
-    const typename C::T *__restrict__ A = site.A;
     const Grid &g = site.g;
     const ForceField &cur = site.cur;
-    const ForceField &old = site.old;
-    // Release this lane's node from the field used one step ago (that step's
-    // stream-collide has consumed it).  Issued first, so that its stores are
+    // Release this lane's nodes from the fields of earlier steps (their
+    // stream-collide has consumed them).  Issued first, so that the stores are
     // in flight together with the gather below.
-    const uint32_t pc = valid ? pa.prev_cell[8 * i + p] : kNoNode;
-    if (pc != kNoNode) {
-        old.f[3 * uint64_t(pc) + 0] = 0;
-        old.f[3 * uint64_t(pc) + 1] = 0;
-        old.f[3 * uint64_t(pc) + 2] = 0;
-        atomicAnd(&old.mask[pc >> 5], ~(1u << (pc & 31)));
-    }
+    if (valid && pa.last_cells) release_node(site.last, pa.last_cells[8 * i + p]);
+    if (valid && pa.older_cells) release_node(site.older, pa.older_cells[8 * i + p]);
     const uint32_t Ln[3] = {g.nx, g.ny, g.nz};
     const int b[3] = {p & 1, (p >> 1) & 1, (p >> 2) & 1};
     double d[3];
@@ -231,14 +258,7 @@ __device__ inline void particle_lane(const ParticleSite<C> &site, typename C::R 
     // Brownian force, which overlap the load latency.  Plain loads: the
     // following sweep reads these lines again, and non-temporal ones, though
     // 1.2 us faster here, cost the sweep as much or more.
-    typename C::T raw[Vs::Q];
-    if (coupled) {
-        const Neighbours nb(fnode[0], fnode[1], fnode[2], g);
-        static_for<1, Vs::Q>([&](auto ac) {
-            constexpr int a = decltype(ac)::value;
-            raw[a] = A[nb.template pop<Vs, a>(g)];
-        });
-    }
+    if (coupled) gather.issue(fnode, g);
 
     // Loads whose results are needed only at the end: the given and pair forces.
     double fc[3] = {0.0, 0.0, 0.0};
@@ -323,11 +343,12 @@ __device__ inline void particle_lane(const ParticleSite<C> &site, typename C::R 
 
     double FH[3];
     double u[3] = {0.0, 0.0, 0.0};
+    gather.wait();
     if (coupled) {
         // u^n at this lane's node: u = sum_a e_a f_a = sum_a e_a g_a (Eq. s2-fv).
         static_for<1, Vs::Q>([&](auto ac) {
             constexpr int a = decltype(ac)::value;
-            const double gvl = double(C::dec(raw[a], dec_s));
+            const double gvl = double(C::dec(gather.template get<a>(), dec_s));
             if constexpr (Vs::ex[a] != 0) u[0] += Vs::ex[a] > 0 ? gvl : -gvl;
             if constexpr (Vs::ey[a] != 0) u[1] += Vs::ey[a] > 0 ? gvl : -gvl;
             if constexpr (Vs::ez[a] != 0) u[2] += Vs::ez[a] > 0 ? gvl : -gvl;
@@ -359,7 +380,7 @@ __device__ inline void particle_lane(const ParticleSite<C> &site, typename C::R 
         atomicOr(&cur.mask[scell >> 5], 1u << (scell & 31));
         my_cell = scell;
     }
-    pa.prev_cell[8 * i + p] = my_cell;
+    pa.cells[8 * i + p] = my_cell;
 
     if (p != 0) return;
     // Eqs. s2-langevin, s2-langevin2 with dt = 1; F_C is the given force (or 0).
@@ -377,7 +398,7 @@ template <class C>
 __global__ __launch_bounds__(kParticleBlock) void k_particle(const typename C::T *__restrict__ A,
                                                              Grid g, typename C::R dec_s,
                                                              ParticleArgs pa, ForceField cur,
-                                                             ForceField old) {
+                                                             ForceField last, ForceField older) {
     const uint32_t gt = blockIdx.x * kParticleBlock + threadIdx.x;
     const int32_t i = int32_t(gt >> 3);
     const int p = int(gt & 7u);
@@ -397,8 +418,144 @@ __global__ __launch_bounds__(kParticleBlock) void k_particle(const typename C::T
         for (int k = 0; k < 3; ++k) pm[k] = (valid && p == 0) ? pa.mass * V[k] : 0.0;
         block_sum<3, kParticleBlock>(pm, pa.pmom + 3 * uint64_t(blockIdx.x));
     }
-    const ParticleSite<C> site{A, g, cur, old, pa.seed, pa.replica, uint32_t(i), pa.R};
-    particle_lane<C>(site, dec_s, pa, i, p, valid, r, V);
+    const ParticleSite<C> site{A, g, cur, last, older, pa.seed, pa.replica, uint32_t(i), pa.R};
+    LatticeGather<C> gather{A, {}};
+    particle_lane<C>(site, gather, dec_s, pa, i, p, valid, r, V);
+}
+
+// ---------------------------------------------------------------------------
+// The second particle update of a two-step sweep: step n + 1, run before that
+// sweep, when the lattice still holds step n.  f^{n+1} at a fitting node x is
+// the post-collision value of step n at x - e_a, which one wavefront per
+// particle computes for every node within one link of the particle's fitting
+// nodes (a 4^3 neighbourhood, 5^3 for the (2 dx)^3 cube), with the node forces
+// of step n, exactly as the sweep does; a ninth wavefront of the block runs
+// the eight particles' update on them.
+// ---------------------------------------------------------------------------
+constexpr int kAheadParticles = 8;
+constexpr int kAheadBlock = 64 * (kAheadParticles + 1);
+
+// Bit x + N (y + N z) of word i / 64: node (x, y, z) of the N^3 neighbourhood
+// is one link from a fitting node (corners 1 and N - 2 per axis).
+template <class Vs, int N>
+struct AheadNodes {
+    uint64_t word[(N * N * N + 63) / 64] = {};
+    constexpr AheadNodes() {
+        for (int p = 0; p < 8; ++p)
+            for (int a = 1; a < Vs::Q; ++a) {
+                const int x = ((p & 1) ? N - 2 : 1) - Vs::ex[a];
+                const int y = ((p & 2) ? N - 2 : 1) - Vs::ey[a];
+                const int z = ((p & 4) ? N - 2 : 1) - Vs::ez[a];
+                const int i = x + N * (y + N * z);
+                word[i / 64] |= uint64_t(1) << (i % 64);
+            }
+    }
+};
+
+template <class C, int N>
+struct AheadGather {
+    const typename C::T (*post)[N * N * N];  // [Q] of this lane's particle, in LDS
+    int p;
+    __device__ inline void issue(const uint32_t (&)[3], const Grid &) {}
+    __device__ inline void wait() { __syncthreads(); }
+    template <int a>
+    __device__ inline typename C::T get() const {
+        using Vs = typename C::V;
+        constexpr int de = Vs::ex[a] + N * (Vs::ey[a] + N * Vs::ez[a]);
+        const int corner = ((p & 1) ? N - 2 : 1) + N * (((p & 2) ? N - 2 : 1) + N * ((p & 4) ? N - 2 : 1));
+        return post[a][corner - de];
+    }
+};
+
+// One step's fluid around particle position r (one wavefront): post-collision
+// values of step n into post.
+template <class C, int N>
+__device__ inline void ahead_nodes(const typename C::T *__restrict__ A, const Grid &g,
+                                   typename C::R omega, typename C::R enc_s, typename C::R dec_s,
+                                   typename C::R Gx, typename C::R Gy, typename C::R Gz,
+                                   const ForceField &f0, const double (&r)[3],
+                                   typename C::T (*post)[N * N * N]) {
+#pragma clang fp contract(on)  // as node_relax
+    using Vs = typename C::V;
+    using R = typename C::R;
+    constexpr AheadNodes<Vs, N> need;
+    const uint32_t Ln[3] = {g.nx, g.ny, g.nz};
+    int32_t c0[3];  // node (0, 0, 0) of the neighbourhood
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const double L = double(Ln[k]);
+        const double s = r[k] - L * floor(r[k] / L);
+        // the particle update's corner, with its clamp for non-finite positions
+        if constexpr (N == 4)
+            c0[k] = min(max(int32_t(floor(s)), -1), int32_t(Ln[k])) - 1;
+        else
+            c0[k] = min(max(int32_t(floor(s + 0.5) - 1.0), -1), int32_t(Ln[k]) - 1) - 1;
+    }
+    const int lane = int(threadIdx.x & 63u);
+#pragma unroll
+    for (int q = 0; q < (N * N * N + 63) / 64; ++q) {
+        if (!((need.word[q] >> lane) & 1u)) continue;
+        const int i = 64 * q + lane;
+        const int o[3] = {i % N, (i / N) % N, i / (N * N)};
+        uint32_t x[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const int32_t L = int32_t(Ln[k]), c = (c0[k] + o[k]) % L;  // a few periods off at most
+            x[k] = uint32_t(c < 0 ? c + L : c);
+        }
+        const Neighbours nb(x[0], x[1], x[2], g);
+        typename C::T raw[Vs::Q];
+        static_for<0, Vs::Q>([&](auto ac) {
+            constexpr int a = decltype(ac)::value;
+            raw[a] = A[nb.template pop<Vs, a>(g)];
+        });
+        const uint32_t cell = (x[2] * g.ny + x[1]) * g.nx + x[0];
+        const bool flag = (f0.mask[cell >> 5] >> (cell & 31)) & 1u;
+        R Fx = Gx, Fy = Gy, Fz = Gz;
+        if (flag) {
+            Fx += R(double(f0.f[3 * uint64_t(cell) + 0]) * kFixInv);
+            Fy += R(double(f0.f[3 * uint64_t(cell) + 1]) * kFixInv);
+            Fz += R(double(f0.f[3 * uint64_t(cell) + 2]) * kFixInv);
+        }
+        R gv[Vs::Q];
+        static_for<0, Vs::Q>([&](auto ac) {
+            constexpr int a = decltype(ac)::value;
+            gv[a] = C::dec(raw[a], dec_s);
+        });
+        const NodeMoments<C> m = node_moments<C>(gv);
+        node_relax<C>(gv, m, omega, Fx, Fy, Fz, [&](int a, R gn) { post[a][i] = C::enc(gn, enc_s); });
+    }
+}
+
+template <class C, int N>
+__global__ __launch_bounds__(kAheadBlock) void k_particle_ahead(
+    const typename C::T *__restrict__ A, Grid g, typename C::R omega, typename C::R enc_s,
+    typename C::R dec_s, typename C::R Gx, typename C::R Gy, typename C::R Gz, ParticleArgs pa,
+    ForceField f0, ForceField cur) {
+    __shared__ typename C::T post[kAheadParticles][C::V::Q][N * N * N];
+    const int wave = int(threadIdx.x >> 6), lane = int(threadIdx.x & 63u);
+    if (wave < kAheadParticles) {
+        const int32_t i = int32_t(blockIdx.x) * kAheadParticles + wave;
+        if (i < pa.n) {
+            const double r[3] = {pa.r[3 * i + 0], pa.r[3 * i + 1], pa.r[3 * i + 2]};
+            ahead_nodes<C, N>(A, g, omega, enc_s, dec_s, Gx, Gy, Gz, f0, r, post[wave]);
+        }
+        __syncthreads();
+        return;
+    }
+    const int p = lane & 7;
+    const int32_t i = int32_t(blockIdx.x) * kAheadParticles + (lane >> 3);
+    const bool valid = i < pa.n;
+    const int32_t ii = valid ? i : pa.n - 1;
+    double r[3], V[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        r[k] = pa.r[3 * ii + k];
+        V[k] = pa.v[3 * ii + k];
+    }
+    const ParticleSite<C> site{A, g, cur, cur, cur, pa.seed, pa.replica, uint32_t(i), pa.R};
+    AheadGather<C, N> gather{post[lane >> 3], p};
+    particle_lane<C>(site, gather, dec_s, pa, i, p, valid, r, V);
 }
 
 }  // namespace lbmbp
