@@ -168,6 +168,10 @@ __device__ inline void lane_coords(const Grid &g, uint32_t lane_cell, uint32_t r
 struct ForceField {
     long long *f;    // [ncell][3] fixed-point force
     uint32_t *mask;  // one bit per node: node carries a force this step
+    // the part of one box of an ensemble
+    __device__ inline ForceField box(uint64_t cell_off, uint32_t mask_off) const {
+        return ForceField{f + 3 * cell_off, mask + mask_off};
+    }
 };
 
 // Source node of direction a for a pull at (x, y, z): x - e_a, periodic.

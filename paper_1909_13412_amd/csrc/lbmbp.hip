@@ -38,6 +38,7 @@
 #include "collide_launch.hpp"
 #include "velocities.hpp"
 #include "pairs.hpp"
+#include "replica.hpp"
 #include "particle.hpp"
 #include "philox.hpp"
 #include "twostep_launch.hpp"
@@ -49,32 +50,10 @@ constexpr int kRedBlocks = 1024;
 // sweep reads the fields of both its steps, so neither can be cleared before
 // it; the next particle update clears both and writes the third.
 constexpr int kForceFields = 3;
-
-// ---------------------------------------------------------------------------
-// Ensembles of independent boxes (replicas) of different sizes, stepped
-// together: one stream-collide launch covers every replica's nodes (a block
-// never straddles two replicas) and one particle launch covers every
-// particle.  Step-dependent values come from a device clock so that a
-// captured graph of several steps can be replayed.
-// ---------------------------------------------------------------------------
-struct Replica {
-    Grid g;
-    uint64_t pop_off;              // first element of this box in the lattices
-    uint64_t cell_off;             // first node in the node-force fields
-    uint32_t mask_off;             // first word of its forcing flags
-    uint32_t first_block[4];       // first stream-collide block, per launch shape
-    uint32_t part_off, npart;      // its particles in the concatenated arrays
-    uint32_t replica_id;           // Philox third counter word
-    uint32_t pad;
-    uint64_t seed;                 // Philox key
-    double omega;                  // 1 / tau
-    double R;                      // particle radius
-};
-
-struct EnsClock {
-    int64_t step;    // Philox first counter word and field parity
-    int64_t vacf_t;  // VACF sample clock
-};
+// A captured graph of an ensemble's steps names the fields (n mod 3) and the
+// particles' node lists (n mod 2), so there is one for each even step number
+// mod 6.
+constexpr int kEnsGraphs = 3;
 
 template <class C, int CPT, int BS, bool NTS>
 __global__ __launch_bounds__(BS) void k_ens_collide(const typename C::T *__restrict__ A,
@@ -116,46 +95,6 @@ __global__ __launch_bounds__(BS) void k_ens_stream_only(const typename C::T *__r
     const uint32_t lane_cell = (b - rp.first_block[shape]) * BS + threadIdx.x;
     if (lane_cell >= rp.g.ncell / CPT) return;
     stream_only_lane<C, CPT, NTS>(A + rp.pop_off, B + rp.pop_off, rp.g, lane_cell);
-}
-
-template <class C>
-__global__ __launch_bounds__(kParticleBlock) void k_ens_particle(
-    const typename C::T *__restrict__ A, const Replica *__restrict__ reps,
-    const uint16_t *__restrict__ part_rep, typename C::R dec_s, ParticleArgs pa,
-    const EnsClock *__restrict__ clock, long long *force_cur, uint32_t *mask_cur,
-    long long *force_old, uint32_t *mask_old) {
-    const uint32_t gt = blockIdx.x * kParticleBlock + threadIdx.x;
-    const int32_t i = int32_t(gt >> 3);
-    const int p = int(gt & 7u);
-    const bool valid = i < pa.n;
-    const int32_t ii = valid ? i : pa.n - 1;
-    // step-dependent values from the device clock
-    pa.step = uint32_t(clock->step);
-    if (pa.acc) {
-        const int64_t t = clock->vacf_t;
-        pa.t = t;
-        pa.k_hi = t / pa.stride;
-        pa.k_lo = t > pa.max_lag ? (t - pa.max_lag + pa.stride - 1) / pa.stride : 0;
-        pa.slot_lo = int32_t(pa.k_lo % pa.nslot);
-    }
-    double r[3], V[3];
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        r[k] = pa.r[3 * ii + k];
-        V[k] = pa.v[3 * ii + k];
-    }
-    const Replica &rp = reps[part_rep[ii]];
-    const ParticleSite<C> site{A + rp.pop_off,
-                               rp.g,
-                               ForceField{force_cur + 3 * rp.cell_off, mask_cur + rp.mask_off},
-                               ForceField{force_old + 3 * rp.cell_off, mask_old + rp.mask_off},
-                               ForceField{nullptr, nullptr},
-                               rp.seed,
-                               rp.replica_id,
-                               uint32_t(ii) - rp.part_off,
-                               rp.R};
-    LatticeGather<C> gather{site.A, {}};
-    particle_lane<C>(site, gather, dec_s, pa, i, p, valid, r, V);
 }
 
 // ---------------------------------------------------------------------------
@@ -386,6 +325,7 @@ struct lbm_ctx {
     double R;
     double *r, *v;
     uint32_t *cells[2];  // [n][8] nodes spread to in even and odd steps
+    int fields_used;     // a particle update has run since the fields were cleared
     int after_two;       // the last sweep was a two-step one: two fields to release
     double *fh, *fr;
     const double *fext;  // given force on each particle (lbm_set_particle_force) or null
@@ -751,6 +691,7 @@ ParticleArgs step_particle_args(lbm_ctx *c) {
 
 template <class C>
 void launch_particle(lbm_ctx *c, const typename C::T *A, const ParticleArgs &pa, int64_t n) {
+    c->fields_used = 1;
     hipLaunchKernelGGL(k_particle<C>, dim3(unsigned(particle_blocks(c->np))), dim3(kParticleBlock), 0, c->stream, A,
                        c->g, typename C::R(c->dec_s), pa, field(c, n), field(c, n + 2), field(c, n + 1));
 }
@@ -1191,7 +1132,31 @@ lbm_status set_layout(lbm_ctx *c, uint32_t Y) {
 // Fitted to probe timings (FP32, us per plane: 128 x 4 tiles 3.7, 64 x 8 3.9,
 // 64 x 10 4.3, 96 x 6 3.95).
 constexpr int kTwoStepCandidates = 4;
+
+double two_step_plane_cost(uint32_t tx, uint32_t ty, size_t elem) {
+    const double lines = (ty + 2) * ((tx + 2) * double(elem) / 128.0 + 1.5);
+    const double waves = ((tx + 2) * (ty + 2) + 63) / 64 + (tx * ty + 63) / 64;
+    return 10.0 + 0.6 * lines + 0.6 * waves;
+}
+
 constexpr uint32_t kTwoStepUnits = 256;
+
+// Calls fn(tx, ty, ntx, nty) for every even split of an nx x ny plane into tiles
+// that fit a block (rows of 16 nodes at least, unless nx is shorter).
+template <typename Fn>
+void two_step_each_tile(uint32_t nx, uint32_t ny, uint32_t most, Fn &&fn) {
+    for (uint32_t ntx = 1; ntx <= nx; ++ntx) {
+        const uint32_t tx = (nx + ntx - 1) / ntx;
+        if (tx < 16 && ntx > 1) break;
+        if ((tx + 2) * 3 > most || (nx + tx - 1) / tx != ntx) continue;
+        uint32_t last = 0;
+        for (uint32_t top = std::min(ny, most / (tx + 2) - 2); top >= 1; --top) {
+            const uint32_t nty = (ny + top - 1) / top, ty = (ny + nty - 1) / nty;
+            if (ty != last) fn(tx, ty, ntx, nty);
+            last = ty;
+        }
+    }
+}
 
 int two_step_candidates(const lbm_grid_desc *g, TwoStepTiles *out) {
     const uint32_t nx = uint32_t(g->nx), ny = uint32_t(g->ny), nz = uint32_t(g->nz);
@@ -1204,46 +1169,39 @@ int two_step_candidates(const lbm_grid_desc *g, TwoStepTiles *out) {
         double cost;
     };
     std::vector<Cand> all;
-    for (uint32_t ntx = 1; ntx <= nx; ++ntx) {
-        const uint32_t tx = (nx + ntx - 1) / ntx;
-        if (tx < 16 && ntx > 1) break;
-        if ((tx + 2) * 3 > most || (nx + tx - 1) / tx != ntx) continue;
-        for (uint32_t nty = 1; nty <= ny; ++nty) {
-            const uint32_t ty = (ny + nty - 1) / nty;
-            if ((tx + 2) * (ty + 2) > most || (ny + ty - 1) / ty != nty) continue;
-            const double lines = (ty + 2) * ((tx + 2) * double(elem) / 128.0 + 1.5);
-            const double waves = ((tx + 2) * (ty + 2) + 63) / 64 + (tx * ty + 63) / 64;
-            const double plane = 10.0 + 0.6 * lines + 0.6 * waves;
-            Cand best{{}, -1.0};
-            for (uint32_t ns = 1; ns <= nz; ++ns) {
-                const uint32_t lz = (nz + ns - 1) / ns;
-                if ((nz + lz - 1) / lz != ns) continue;
-                const uint64_t blocks = uint64_t(ntx) * nty * ns;
-                const double rounds = double((blocks + kTwoStepUnits - 1) / kTwoStepUnits);
-                const double cost = rounds * (lz + 2.0) * plane;
-                if (best.cost < 0.0 || cost < best.cost) best = Cand{{tx, ty, lz, ntx, nty, ns}, cost};
-                if (blocks > 16 * kTwoStepUnits) break;
-            }
-            if (best.cost > 0.0) all.push_back(best);
+    two_step_each_tile(nx, ny, most, [&](uint32_t tx, uint32_t ty, uint32_t ntx, uint32_t nty) {
+        const double plane = two_step_plane_cost(tx, ty, elem);
+        const uint64_t tiles = uint64_t(ntx) * nty;
+        const uint64_t r0 = (tiles + kTwoStepUnits - 1) / kTwoStepUnits;
+        Cand best{{}, -1.0};
+        for (uint64_t r = r0; r < r0 + 8; ++r) {  // rounds of blocks
+            const uint32_t ns = uint32_t(std::min<uint64_t>(nz, r * kTwoStepUnits / tiles));
+            const uint32_t lz = (nz + ns - 1) / ns;
+            const double cost = double(r) * (lz + 2.0) * plane;
+            if (best.cost < 0.0 || cost < best.cost) best = Cand{{tx, ty, lz, ntx, nty, (nz + lz - 1) / lz}, cost};
         }
-    }
+        all.push_back(best);
+    });
     std::sort(all.begin(), all.end(), [](const Cand &x, const Cand &y) { return x.cost < y.cost; });
     const int n = int(std::min<size_t>(kTwoStepCandidates, all.size()));
     for (int k = 0; k < n; ++k) out[k] = all[k].tl;
     return n;
 }
 
+// Store policy of the two-step sweep: non-temporal once the two lattices
+// outgrow the 256 MB last-level cache (probe, two sweeps in turn, ms plain /
+// non-temporal: BF16 128^3, 80 MB a lattice, 0.0437 / 0.0488; FP32 128^3,
+// 159 MB, 0.0717 / 0.0673; FP32 256^3 0.502 / 0.486).
+constexpr size_t kTwoStepStreamBytes = size_t(128) << 20;
+
 // Boxes of fewer nodes than this take single steps until tuned.
-constexpr uint64_t kTwoStepMinNodes = uint64_t(1) << 17;
+// (64^3 with 16 particles, 60 recorded steps: 12.2 us a step against 12.9.)
+constexpr uint64_t kTwoStepMinNodes = uint64_t(1) << 19;
 
-int two_step_default(const lbm_grid_desc *g) {
-    TwoStepTiles tl[kTwoStepCandidates];
-    return (ncell_of(g) >= kTwoStepMinNodes && two_step_candidates(g, tl) > 0) ? 1 : 0;
-}
-
+// The tiles of choice `two` (1: the model's first); 0 where the box has none.
 TwoStepTiles two_step_tiles(const lbm_grid_desc *g, int &two) {
     TwoStepTiles tl[kTwoStepCandidates] = {};
-    if (two > two_step_candidates(g, tl)) two = 0;
+    if (two > 0 && two > two_step_candidates(g, tl)) two = 0;
     return tl[two > 0 ? two - 1 : 0];
 }
 
@@ -1257,7 +1215,7 @@ bool two_step_pays(const lbm_ctx *c) {
 }
 
 // The remembered code of a box holds, above the single-step launch, the
-// two-step choice: 2 * candidate + store policy, plus one.
+// two-step choice plus one.
 constexpr int kTuneTwo = kNumShapes * int(kNumOrders) * kNumCaps * (kMaxRowsLog2 + 1);
 
 TuneKey ctx_tune_key(const lbm_ctx *c) {
@@ -1302,8 +1260,8 @@ lbm_status lbm_init(const lbm_grid_desc *grid, void *pop_a, void *pop_b, void *g
         // the remembered layout, applied once the lattices are at rest below
         init_rows = uint32_t(1) << ((code / (kNumShapes * int(kNumOrders) * kNumCaps)) % (kMaxRowsLog2 + 1));
         const int two = code / kTuneTwo;  // remembered two-step choice + 1, 0: none
-        c->two = two > 0 ? (two - 1) / 2 : two_step_default(grid);
-        c->two_nts = two > 0 ? (two - 1) % 2 : lat >= kStreamStoreBytes;
+        c->two = two > 0 ? two - 1 : ncell_of(grid) >= kTwoStepMinNodes;
+        c->two_nts = lat >= kTwoStepStreamBytes;
         c->two_tiles = two_step_tiles(grid, c->two);
         if (grid->ny % int32_t(init_rows) != 0) init_rows = 1;
         // LDS limits of the device, for the residency caps (none if unknown)
@@ -1419,12 +1377,16 @@ lbm_status particles_couple(lbm_ctx *ctx, const lbm_particle_desc *d, double *r,
         if (d->friction < LBM_FRICTION_STOKESLET || d->friction > LBM_FRICTION_STOKESLET_CUBE)
             return LBM_E_INVAL;
     }
-    // Node forces left by any previous particle set are cleared.
-    // (the fields lie back to back: the masks, then the forces)
-    hipError_t e = hipMemsetAsync(ctx->mask[0], 0, kForceFields * align_up(size_t(ctx->mask_words) * 4, kAlign), ctx->stream);
-    if (e == hipSuccess)
-        e = hipMemsetAsync(ctx->force[0], 0, kForceFields * force_field_bytes(&ctx->desc), ctx->stream);
-    if (e != hipSuccess) return LBM_E_DEVICE;
+    // Node forces left by any previous particle set are cleared (the fields lie
+    // back to back: the masks, then the forces; lbm_init cleared them first).
+    hipError_t e = hipSuccess;
+    if (ctx->fields_used) {
+        e = hipMemsetAsync(ctx->mask[0], 0, kForceFields * align_up(size_t(ctx->mask_words) * 4, kAlign), ctx->stream);
+        if (e == hipSuccess)
+            e = hipMemsetAsync(ctx->force[0], 0, kForceFields * force_field_bytes(&ctx->desc), ctx->stream);
+        if (e != hipSuccess) return LBM_E_DEVICE;
+    }
+    ctx->fields_used = 0;
     ctx->after_two = 0;
     ctx->vacf_on = 0;
     ctx->fext = nullptr;
@@ -1770,22 +1732,21 @@ lbm_status lbm_autotune(lbm_ctx *ctx, int32_t iters, double *ms, int32_t *chosen
     {
         TwoStepTiles tl[kTwoStepCandidates];
         const int nt = two_step_candidates(&ctx->desc, tl);
-        double two_best = 2.0 * total[jb] / 2.0;  // total: two timings of one step each
+        double two_best = total[jb];  // two timings of one step each
         ctx->two = 0;
-        for (int j = 0; j < 2 * nt; ++j) {
+        for (int j = 0; j < nt; ++j) {
             double v = 0.0;
-            LBM_DISPATCH(ctx, time_two_steps, tl[j / 2], (j & 1) != 0, iters, &v, &err);
+            LBM_DISPATCH(ctx, time_two_steps, tl[j], ctx->two_nts != 0, iters, &v, &err);
             if (err != hipSuccess || launch_status() != LBM_OK) return LBM_E_DEVICE;
             if (v > 0.0 && v < two_best) {
                 two_best = v;
-                ctx->two = j / 2 + 1;
-                ctx->two_nts = j & 1;
-                ctx->two_tiles = tl[j / 2];
+                ctx->two = j + 1;
+                ctx->two_tiles = tl[j];
             }
         }
     }
-    tune_store(ctx_tune_key(ctx), tune_code(best.k, best.o, best.c, rows_log2(ctx->g)) +
-                                      kTuneTwo * (2 * ctx->two + ctx->two_nts + 1));
+    tune_store(ctx_tune_key(ctx),
+               tune_code(best.k, best.o, best.c, rows_log2(ctx->g)) + kTuneTwo * (ctx->two + 1));
     if (ms)
         for (int k = 0; k < kNumShapes; ++k) ms[k] = best_k[k];
     if (chosen) *chosen = best.k;
@@ -1920,10 +1881,10 @@ struct lbm_ens {
     Replica *reps;
     uint16_t *blk_rep[kNumGeomShapes];
     uint16_t *part_rep;
-    uint32_t *mask[2];
-    long long *force[2];
+    uint32_t *mask[kForceFields];
+    long long *force[kForceFields];
     uint64_t total_mask_words;
-    uint32_t *prev_cell;
+    uint32_t *cells[2];  // [n][8] nodes spread to in even and odd steps
     double *fh, *fr;
     EnsClock *clock;
     uint32_t *err;
@@ -1938,13 +1899,17 @@ struct lbm_ens {
     int shape;
     int order, cap;         // block order and residency cap of the stream-collide
     int lds_cu, lds_block;  // LDS bytes per compute unit and per block (device limits)
+    int two, two_nts;       // two-step sweeps, and their store policy
+    int two_possible;
+    uint32_t two_blocks, two_threads;
+    uint16_t *two_rep;      // block -> box of the two-step sweep
     int rows;    // requested rows per group: each box takes the largest power of two <= rows dividing its ny
     int device;  // device current at lbm_ens_init (autotune cache key)
     // graph of LBM_ENS_GRAPH_STEPS steps, captured on a private stream and
     // replayed on `stream`
     int use_graph;
-    hipGraphExec_t graph;
-    int graph_valid;
+    hipGraphExec_t graph[kEnsGraphs];  // from a step number 0, 2 and 4 mod 6
+    int graph_valid[kEnsGraphs];
     hipStream_t cap_stream;
     int graph_replays;  // number of graph launches so far
 };
@@ -1964,14 +1929,37 @@ TuneKey ens_tune_key(const lbm_ens *e) {
 
 uint32_t ens_chunk(int32_t nx) { return uint32_t(nx); }  // unpadded, as row_chunk
 
+// Two-step tiles of one box of an ensemble: the boxes' blocks share the units,
+// so the tile is the one of least total cost, and slabs stay at about 24
+// planes (two planes and a start more per slab, against some thousand blocks
+// to even the units out).
+TwoStepTiles ens_two_tiles(const lbm_replica_desc &r, size_t elem) {
+    const uint32_t nx = uint32_t(r.nx), ny = uint32_t(r.ny), nz = uint32_t(r.nz);
+    const uint32_t most = two_step_nodes(elem);
+    TwoStepTiles best{};
+    double cost = -1.0;
+    // 32-bit byte offsets within a plane
+    if (uint64_t(nx) * ny * D3Q19::Q * elem >= (uint64_t(1) << 32)) return best;
+    two_step_each_tile(nx, ny, most, [&](uint32_t tx, uint32_t ty, uint32_t ntx, uint32_t nty) {
+        const double c = two_step_plane_cost(tx, ty, elem) * ntx * nty;
+        if (cost > 0.0 && c >= cost) return;
+        const uint32_t ns = (nz + 23) / 24, lz = (nz + ns - 1) / ns;
+        best = TwoStepTiles{tx, ty, lz, ntx, nty, (nz + lz - 1) / lz};
+        cost = c;
+    });
+    return best;
+}
+
 struct EnsLayout {
     uint64_t total_cells = 0, total_pop = 0, total_mask_words = 0;
     uint32_t total_blocks[kNumGeomShapes] = {0, 0, 0, 0};
+    uint32_t two_blocks = 0, two_threads = 0;  // two-step sweep
+    bool two_ok = true;                        // every box has tiles for it
     int32_t n = 0;
     size_t lattice_bytes = 0, scratch_bytes = 0;
     // scratch offsets
-    size_t o_reps, o_blk[kNumGeomShapes], o_part, o_mask[2], o_force[2], o_prev, o_fh, o_fr, o_clock,
-        o_err, o_partials, o_result;
+    size_t o_reps, o_blk[kNumGeomShapes], o_two, o_part, o_mask[kForceFields], o_force[kForceFields],
+        o_cells[2], o_fh, o_fr, o_clock, o_err, o_partials, o_result;
 };
 
 bool ens_desc_ok(const lbm_ensemble_desc *d, const lbm_replica_desc *reps) {
@@ -2008,6 +1996,10 @@ EnsLayout ens_layout(const lbm_ensemble_desc *d, const lbm_replica_desc *reps) {
             const uint64_t band = (r.ny % kShapes[s].cpt == 0) ? cells / kShapes[s].cpt : 0;
             L.total_blocks[s] += uint32_t((band + kShapes[s].bs - 1) / kShapes[s].bs);
         }
+        const TwoStepTiles tl = ens_two_tiles(r, elem);
+        L.two_ok = L.two_ok && tl.lz > 0;
+        L.two_blocks += tl.ntx * tl.nty * tl.nslab;
+        L.two_threads = std::max(L.two_threads, two_step_threads(tl));
         L.n += r.n;
     }
     L.lattice_bytes = align_up(L.total_pop * elem, kAlign);
@@ -2018,18 +2010,22 @@ EnsLayout ens_layout(const lbm_ensemble_desc *d, const lbm_replica_desc *reps) {
         L.o_blk[s] = o;
         o += align_up(size_t(L.total_blocks[s]) * 2 + 2, kAlign);
     }
+    L.o_two = o;
+    o += align_up(size_t(L.two_blocks) * 2, kAlign);
     L.o_part = o;
     o += align_up(size_t(L.n) * 2, kAlign);
-    for (int k = 0; k < 2; ++k) {
+    for (int k = 0; k < kForceFields; ++k) {
         L.o_mask[k] = o;
         o += align_up(L.total_mask_words * 4, kAlign);
     }
-    for (int k = 0; k < 2; ++k) {
+    for (int k = 0; k < kForceFields; ++k) {
         L.o_force[k] = o;
         o += align_up(L.total_cells * 3 * 8, kAlign);
     }
-    L.o_prev = o;
-    o += align_up(size_t(L.n) * 8 * 4, kAlign);
+    for (int k = 0; k < 2; ++k) {
+        L.o_cells[k] = o;
+        o += align_up(size_t(L.n) * 8 * 4, kAlign);
+    }
     L.o_fh = o;
     o += align_up(size_t(L.n) * 3 * 8, kAlign);
     L.o_fr = o;
@@ -2046,6 +2042,9 @@ EnsLayout ens_layout(const lbm_ensemble_desc *d, const lbm_replica_desc *reps) {
     return L;
 }
 
+// Every box has tiles, and the block table's first block numbers fit.
+bool ens_two_possible(const EnsLayout &L) { return L.two_ok && L.two_blocks > 0; }
+
 ParticleArgs ens_particle_args(lbm_ens *e) {
     ParticleArgs pa;
     memset(&pa, 0, sizeof(pa));
@@ -2053,8 +2052,6 @@ ParticleArgs ens_particle_args(lbm_ens *e) {
     pa.v = e->v;
     pa.fh = e->fh;
     pa.fr = e->fr;
-    pa.cells = e->prev_cell;
-    pa.last_cells = e->prev_cell;
     pa.err = e->err;
     pa.n = e->n;
     pa.friction = e->desc.friction;
@@ -2080,40 +2077,102 @@ ParticleArgs ens_particle_args(lbm_ens *e) {
 // SIMD for blocks of bs lanes (0: no cap; -1: not possible on this device).
 long ens_sweep_lds(const lbm_ens *e, int cap, int bs) { return residency_lds(e->lds_cu, e->lds_block, cap, bs); }
 
+// Node-force field of step n.
+ForceField ens_field(const lbm_ens *e, int64_t n) {
+    const int k = int(n % kForceFields);
+    return ForceField{e->force[k], e->mask[k]};
+}
+
 template <class C, int CPT, int BS, bool NTS>
-void ens_collide_shape(lbm_ens *e, const typename C::T *A, typename C::T *B, int par) {
+void ens_collide_shape(lbm_ens *e, const typename C::T *A, typename C::T *B, const ForceField &ff) {
     using R = typename C::R;
     const int sh = e->shape & 3;
     const long lds = ens_sweep_lds(e, e->cap, BS);
     hipLaunchKernelGGL((k_ens_collide<C, CPT, BS, NTS>), dim3(e->total_blocks[sh]), dim3(BS),
                        lds > 0 ? size_t(lds) : 0, e->stream, A, B, e->reps, e->blk_rep[sh], sh,
-                       e->force[par], e->mask[par], R(e->enc_s), R(e->dec_s), e->clock, e->vacf_on,
+                       ff.f, ff.mask, R(e->enc_s), R(e->dec_s), e->clock, e->vacf_on,
                        uint32_t(e->order));
 }
 
-// One step of every replica; par = field parity of this step.
+// The particle update of step n (`ahead` steps after the device clock), and the
+// nodes it has to release: those of the last two steps.  (Where the step two
+// back was released already its nodes are cleared again; its field is idle.)
 template <class C>
-void ens_launch_step(lbm_ens *e, int cur, int par) {
+void ens_launch_particle(lbm_ens *e, const typename C::T *A, int64_t n, int ahead) {
+    ParticleArgs pa = ens_particle_args(e);
+    pa.cells = e->cells[n & 1];
+    if (!ahead) {
+        pa.last_cells = e->cells[(n & 1) ^ 1];
+        pa.older_cells = pa.cells;
+    }
+    hipLaunchKernelGGL(k_ens_particle<C>, dim3(unsigned(particle_blocks(e->n))), dim3(kParticleBlock), 0, e->stream, A,
+                       e->reps, e->part_rep, typename C::R(e->dec_s), pa, e->clock, ahead, ens_field(e, n),
+                       ens_field(e, n + 2), ens_field(e, n + 1));
+}
+
+// Step n of every replica, from lattice cur.
+template <class C>
+void ens_launch_step(lbm_ens *e, int cur, int64_t n) {
     using T = typename C::T;
-    using R = typename C::R;
     const T *A = static_cast<const T *>(e->pop[cur]);
     T *B = static_cast<T *>(e->pop[cur ^ 1]);
-    const ParticleArgs pa = ens_particle_args(e);
-    hipLaunchKernelGGL(k_ens_particle<C>,
-                       dim3(unsigned((uint64_t(e->n) * 8 + kParticleBlock - 1) / kParticleBlock)),
-                       dim3(kParticleBlock), 0, e->stream, A, e->reps, e->part_rep, R(e->dec_s), pa,
-                       e->clock, e->force[par], e->mask[par], e->force[par ^ 1], e->mask[par ^ 1]);
-#define LBM_ENS_CALL(CPT, BS, NTS, ROW) ens_collide_shape<C, CPT, BS, NTS>(e, A, B, par)
+    ens_launch_particle<C>(e, A, n, 0);
+#define LBM_ENS_CALL(CPT, BS, NTS, ROW) ens_collide_shape<C, CPT, BS, NTS>(e, A, B, ens_field(e, n))
     LBM_CONFIG_SWITCH(e->shape, LBM_ENS_CALL)
 #undef LBM_ENS_CALL
 }
 
-void ens_dispatch_step(lbm_ens *e, int cur, int par) {
+EnsTwoStepArgs ens_two_step_args(lbm_ens *e, int cur, const ForceField &f0, const ForceField &f1) {
+    EnsTwoStepArgs a;
+    a.A = e->pop[cur];
+    a.B = e->pop[cur ^ 1];
+    a.reps = e->reps;
+    a.blk_rep = e->two_rep;
+    a.part_rep = e->part_rep;
+    a.blocks = e->two_blocks;
+    a.threads = e->two_threads;
+    a.enc_s = e->enc_s;
+    a.dec_s = e->dec_s;
+    a.f0 = f0;
+    a.f1 = f1;
+    a.clock = e->clock;
+    a.vacf_on = e->vacf_on;
+    a.nts = e->two_nts != 0;
+    a.stream = e->stream;
+    return a;
+}
+
+// Steps n and n + 1 of every replica in one sweep (see launch_two_step).
+template <class C>
+void ens_launch_two_step(lbm_ens *e, int cur, int64_t n) {
+    const EnsTwoStepArgs a = ens_two_step_args(e, cur, ens_field(e, n), ens_field(e, n + 1));
+    const typename C::T *A = static_cast<const typename C::T *>(a.A);
+    ens_launch_particle<C>(e, A, n, 0);
+    if (e->desc.friction == LBM_FRICTION_BD) {
+        ens_launch_particle<C>(e, A, n + 1, 1);  // reads no fluid
+    } else {
+        ParticleArgs pa = ens_particle_args(e);
+        pa.cells = e->cells[(n + 1) & 1];
+        launch_ens_particle_ahead<C>(a, pa);
+    }
+    launch_ens_two_steps<C>(a);
+}
+
+template <class C>
+void ens_launch_any(lbm_ens *e, int cur, int64_t n, bool two) {
+    if (two)
+        ens_launch_two_step<C>(e, cur, n);
+    else
+        ens_launch_step<C>(e, cur, n);
+}
+
+// Step n, or steps n and n + 1 in one sweep, from lattice cur.
+void ens_dispatch_step(lbm_ens *e, int cur, int64_t n, bool two) {
     switch (e->desc.storage) {
-        case LBM_STORE_F64: ens_launch_step<F64Q19>(e, cur, par); break;
-        case LBM_STORE_F32: ens_launch_step<F32Q19>(e, cur, par); break;
-        case LBM_STORE_BF16: ens_launch_step<BF16Q19>(e, cur, par); break;
-        case LBM_STORE_F16: ens_launch_step<F16Q19>(e, cur, par); break;
+        case LBM_STORE_F64: ens_launch_any<F64Q19>(e, cur, n, two); break;
+        case LBM_STORE_F32: ens_launch_any<F32Q19>(e, cur, n, two); break;
+        case LBM_STORE_BF16: ens_launch_any<BF16Q19>(e, cur, n, two); break;
+        case LBM_STORE_F16: ens_launch_any<F16Q19>(e, cur, n, two); break;
     }
 }
 
@@ -2167,24 +2226,24 @@ lbm_status ens_set_layout(lbm_ens *e, int rows) {
 }
 
 void ens_drop_graph(lbm_ens *e) {
-    if (e->graph_valid) (void)hipGraphExecDestroy(e->graph);
-    e->graph_valid = 0;
+    for (int k = 0; k < kEnsGraphs; ++k) {
+        if (e->graph_valid[k]) (void)hipGraphExecDestroy(e->graph[k]);
+        e->graph_valid[k] = 0;
+    }
 }
 
-// Steps per graph replay: kGraphPairs pairs of steps (the lattice parity and
-// the force-field parity both return to their start after every pair).  Two
-// steps per graph cost about 1.5% over plain launches on the 64-box
+// Two steps per graph cost about 1.5% over plain launches on the 64-box
 // workload; sixteen amortise the graph launch.
-constexpr int kGraphPairs = LBM_ENS_GRAPH_STEPS / 2;
-static_assert(LBM_ENS_GRAPH_STEPS % 2 == 0, "whole pairs of steps");
+static_assert(LBM_ENS_GRAPH_STEPS % 4 == 0, "an even number of two-step sweeps, so that the lattices return to their start");
 
-// Capture kGraphPairs pairs of steps with parity (0, 1) starting from lattice
-// e->cur into a graph.
+// Capture LBM_ENS_GRAPH_STEPS steps from step number 2 * phase mod 6, starting
+// from lattice e->cur, into a graph.
 // Capture runs on a private non-blocking stream (the caller's stream may be
 // the null stream, which cannot be captured); the graph is then launched on
 // the caller's stream.  Returns false when no graph could be made.
-bool ens_capture(lbm_ens *e) {
-    ens_drop_graph(e);
+bool ens_capture(lbm_ens *e, int phase) {
+    if (e->graph_valid[phase]) (void)hipGraphExecDestroy(e->graph[phase]);
+    e->graph_valid[phase] = 0;
     if (!e->cap_stream && hipStreamCreateWithFlags(&e->cap_stream, hipStreamNonBlocking) != hipSuccess) {
         e->cap_stream = nullptr;
         return false;
@@ -2193,9 +2252,10 @@ bool ens_capture(lbm_ens *e) {
     if (hipStreamBeginCapture(e->cap_stream, hipStreamCaptureModeThreadLocal) != hipSuccess)
         return false;
     e->stream = e->cap_stream;
-    for (int k = 0; k < kGraphPairs; ++k) {
-        ens_dispatch_step(e, e->cur, 0);
-        ens_dispatch_step(e, e->cur ^ 1, 1);
+    int cur = e->cur;
+    for (int k = 0; k < LBM_ENS_GRAPH_STEPS; k += e->two ? 2 : 1) {
+        ens_dispatch_step(e, cur, 2 * phase + k, e->two != 0);
+        cur ^= 1;
     }
     e->stream = user;
     hipGraph_t g = nullptr;
@@ -2204,13 +2264,13 @@ bool ens_capture(lbm_ens *e) {
         (void)hipGetLastError();
         return false;
     }
-    const hipError_t err = hipGraphInstantiate(&e->graph, g, nullptr, nullptr, 0);
+    const hipError_t err = hipGraphInstantiate(&e->graph[phase], g, nullptr, nullptr, 0);
     (void)hipGraphDestroy(g);
     if (err != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
-    e->graph_valid = 1;
+    e->graph_valid[phase] = 1;
     return true;
 }
 
@@ -2224,7 +2284,7 @@ void ens_time_shape(lbm_ens *e, int k, int o, int c) {
     e->cap = c;
     ens_collide_shape<C, CPT, BS, NTS>(e, static_cast<const typename C::T *>(e->pop[e->cur]),
                                        static_cast<typename C::T *>(e->pop[e->cur ^ 1]),
-                                       int((e->step + 1) & 1));  // last step's node forces
+                                       ens_field(e, e->step + 2));  // last step's node forces
     e->shape = saved[0];
     e->order = saved[1];
     e->cap = saved[2];
@@ -2281,6 +2341,30 @@ bool ens_launch_ok(const lbm_ens *e, int k, int c) {
     return ens_sweep_lds(e, c, config_block(k)) >= 0;
 }
 
+void ens_two_steps_any(lbm_ens *e, const EnsTwoStepArgs &a) {
+    switch (e->desc.storage) {
+        case LBM_STORE_F64: launch_ens_two_steps<F64Q19>(a); break;
+        case LBM_STORE_F32: launch_ens_two_steps<F32Q19>(a); break;
+        case LBM_STORE_BF16: launch_ens_two_steps<BF16Q19>(a); break;
+        case LBM_STORE_F16: launch_ens_two_steps<F16Q19>(a); break;
+    }
+}
+
+// Mean ms per two-step sweep (A -> B, as ens_time_launch).
+double ens_time_two_steps(lbm_ens *e, int32_t iters, hipEvent_t e0, hipEvent_t e1) {
+    const ForceField last = ens_field(e, e->step + 2);
+    const EnsTwoStepArgs a = ens_two_step_args(e, e->cur, last, last);
+    for (int w = 0; w < 2; ++w) ens_two_steps_any(e, a);
+    (void)hipEventRecord(e0, e->stream);
+    for (int32_t it = 0; it < iters; ++it) ens_two_steps_any(e, a);
+    (void)hipEventRecord(e1, e->stream);
+    float f = 0.0f;
+    if (hipEventSynchronize(e1) != hipSuccess || hipEventElapsedTime(&f, e0, e1) != hipSuccess ||
+        launch_status() != LBM_OK)
+        return -1.0;
+    return double(f) / iters;
+}
+
 // Mean ms per launch of configuration k with block order o and cap c over
 // iters launches (after two unrecorded ones); < 0 on a device error.
 double ens_time_launch(lbm_ens *e, int k, int o, int c, int32_t iters, hipEvent_t e0, hipEvent_t e1) {
@@ -2325,11 +2409,13 @@ lbm_status lbm_ens_init(const lbm_ensemble_desc *desc, const lbm_replica_desc *r
     for (int s = 0; s < kNumGeomShapes; ++s)
         blk[s] = static_cast<uint16_t *>(malloc(size_t(L.total_blocks[s]) * 2 + 2));
     uint16_t *prep = static_cast<uint16_t *>(malloc(size_t(L.n) * 2));
-    bool ok = e->host_reps && e->host_table && prep;
+    uint16_t *two = static_cast<uint16_t *>(malloc(size_t(L.two_blocks) * 2 + 2));
+    bool ok = e->host_reps && e->host_table && prep && two;
     for (int s = 0; s < kNumGeomShapes; ++s) ok = ok && blk[s];
     if (!ok) {
         for (int s = 0; s < kNumGeomShapes; ++s) free(blk[s]);
         free(prep);
+        free(two);
         free(e->host_reps);
         free(e->host_table);
         free(e);
@@ -2357,7 +2443,12 @@ lbm_status lbm_ens_init(const lbm_ensemble_desc *desc, const lbm_replica_desc *r
         e->order = (code / kNumShapes) % int(kNumOrders);
         e->cap = (code / (kNumShapes * int(kNumOrders))) % kNumCaps;
         // applied to every box below (the rest state is all zeros)
-        e->rows = 1 << (code / (kNumShapes * int(kNumOrders) * kNumCaps));
+        e->rows = 1 << ((code / (kNumShapes * int(kNumOrders) * kNumCaps)) % (kMaxRowsLog2 + 1));
+        const int two = code / kTuneTwo;  // remembered two-step choice + 1, 0: none
+        e->two_possible = ens_two_possible(L);
+        e->two = e->two_possible && (two > 0 ? two - 1 > 0 : L.total_cells >= kTwoStepMinNodes &&
+                                                       double(L.total_cells) >= kTwoStepNodesPerParticle * double(L.n));
+        e->two_nts = L.lattice_bytes >= kTwoStepStreamBytes;
         int v = 0;
         e->lds_cu = (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor,
                                            e->device) == hipSuccess) ? v : 0;
@@ -2371,11 +2462,14 @@ lbm_status lbm_ens_init(const lbm_ensemble_desc *desc, const lbm_replica_desc *r
     e->reps = reinterpret_cast<Replica *>(base + L.o_reps);
     for (int s = 0; s < kNumGeomShapes; ++s) e->blk_rep[s] = reinterpret_cast<uint16_t *>(base + L.o_blk[s]);
     e->part_rep = reinterpret_cast<uint16_t *>(base + L.o_part);
-    for (int k = 0; k < 2; ++k) {
+    e->two_rep = reinterpret_cast<uint16_t *>(base + L.o_two);
+    e->two_blocks = L.two_blocks;
+    e->two_threads = L.two_threads;
+    for (int k = 0; k < kForceFields; ++k) {
         e->mask[k] = reinterpret_cast<uint32_t *>(base + L.o_mask[k]);
         e->force[k] = reinterpret_cast<long long *>(base + L.o_force[k]);
     }
-    e->prev_cell = reinterpret_cast<uint32_t *>(base + L.o_prev);
+    for (int k = 0; k < 2; ++k) e->cells[k] = reinterpret_cast<uint32_t *>(base + L.o_cells[k]);
     e->fh = reinterpret_cast<double *>(base + L.o_fh);
     e->fr = reinterpret_cast<double *>(base + L.o_fr);
     e->clock = reinterpret_cast<EnsClock *>(base + L.o_clock);
@@ -2388,7 +2482,7 @@ lbm_status lbm_ens_init(const lbm_ensemble_desc *desc, const lbm_replica_desc *r
     // replica table, block and particle maps
     uint64_t pop_off = 0, cell_off = 0, mask_off = 0;
     uint32_t first[kNumGeomShapes] = {0, 0, 0, 0};
-    uint32_t part_off = 0;
+    uint32_t part_off = 0, first_two = 0;
     for (int32_t k = 0; k < e->nrep; ++k) {
         const lbm_replica_desc &rd = reps[k];
         Replica &t = e->host_table[k];
@@ -2415,6 +2509,9 @@ lbm_status lbm_ens_init(const lbm_ensemble_desc *desc, const lbm_replica_desc *r
             for (uint32_t b = 0; b < nb; ++b) blk[s][first[s] + b] = uint16_t(k);
             first[s] += nb;
         }
+        t.two = ens_two_tiles(rd, e->elem);
+        t.first_two = first_two;
+        for (uint32_t b = 0; b < t.two.ntx * t.two.nty * t.two.nslab; ++b) two[first_two++] = uint16_t(k);
         for (int32_t q = 0; q < rd.n; ++q) prep[part_off + q] = uint16_t(k);
         pop_off += uint64_t(t.g.chunk) * D3Q19::Q * rd.ny * rd.nz;
         cell_off += t.g.ncell;
@@ -2425,7 +2522,7 @@ lbm_status lbm_ens_init(const lbm_ensemble_desc *desc, const lbm_replica_desc *r
     if (err == hipSuccess) err = hipMemsetAsync(pop_b, 0, L.lattice_bytes, e->stream);
     if (err == hipSuccess) err = hipMemsetAsync(scratch, 0, L.scratch_bytes, e->stream);
     if (err == hipSuccess)
-        err = hipMemsetAsync(e->prev_cell, 0xFF, size_t(L.n) * 8 * 4, e->stream);
+        err = hipMemsetAsync(e->cells[0], 0xFF, 2 * align_up(size_t(L.n) * 8 * 4, kAlign), e->stream);
     if (err == hipSuccess)
         err = hipMemcpyAsync(e->reps, e->host_table, sizeof(Replica) * e->nrep,
                              hipMemcpyHostToDevice, e->stream);
@@ -2435,9 +2532,12 @@ lbm_status lbm_ens_init(const lbm_ensemble_desc *desc, const lbm_replica_desc *r
                                  hipMemcpyHostToDevice, e->stream);
     if (err == hipSuccess)
         err = hipMemcpyAsync(e->part_rep, prep, size_t(L.n) * 2, hipMemcpyHostToDevice, e->stream);
+    if (err == hipSuccess && L.two_blocks > 0)
+        err = hipMemcpyAsync(e->two_rep, two, size_t(L.two_blocks) * 2, hipMemcpyHostToDevice, e->stream);
     if (err == hipSuccess) err = hipStreamSynchronize(e->stream);  // host staging is freed below
     for (int s = 0; s < kNumGeomShapes; ++s) free(blk[s]);
     free(prep);
+    free(two);
     if (err != hipSuccess) {
         free(e->host_reps);
         free(e->host_table);
@@ -2492,30 +2592,40 @@ lbm_status lbm_ens_vacf_counts(const lbm_ens *e, int64_t *cnt) {
 lbm_status lbm_ens_step(lbm_ens *e, int32_t nsteps) {
     if (!e || nsteps < 0) return LBM_E_INVAL;
     int32_t left = nsteps;
-    auto eager = [&]() {
-        ens_dispatch_step(e, e->cur, int(e->step & 1));
+    auto eager = [&](bool two) {
+        const int32_t k = two ? 2 : 1;
+        ens_dispatch_step(e, e->cur, e->step, two);
         e->cur ^= 1;
-        e->step += 1;
-        if (e->vacf_on) e->vacf_t += 1;
-        --left;
+        e->step += k;
+        if (e->vacf_on) e->vacf_t += k;
+        left -= k;
     };
     if (e->use_graph) {
-        if (left > 0 && (e->step & 1)) eager();
-        constexpr int32_t per = 2 * kGraphPairs;
-        if (left >= per && !e->graph_valid && !ens_capture(e)) e->use_graph = 0;  // plain launches
-        if (left >= per && e->graph_valid) {
-            // the graph was captured from lattice parity cur at an even step;
-            // cur and the step parity change together, so they still match
-            while (left >= per) {
-                if (hipGraphLaunch(e->graph, e->stream) != hipSuccess) return LBM_E_DEVICE;
-                e->graph_replays += 1;
-                e->step += per;
-                if (e->vacf_on) e->vacf_t += per;
-                left -= per;
+        if (left > 0 && (e->step & 1)) eager(false);
+        constexpr int32_t per = LBM_ENS_GRAPH_STEPS;
+        while (left >= per && e->use_graph) {
+            const int phase = int(e->step % (2 * kEnsGraphs)) / 2;
+            if (!e->graph_valid[phase] && !ens_capture(e, phase)) {
+                e->use_graph = 0;  // plain launches
+                break;
             }
+            // the graph was captured from lattice parity cur at an even step of
+            // this phase; cur and the step parity change together, so they
+            // still match
+            if (hipGraphLaunch(e->graph[phase], e->stream) != hipSuccess) return LBM_E_DEVICE;
+            e->graph_replays += 1;
+            e->step += per;
+            if (e->vacf_on) e->vacf_t += per;
+            left -= per;
         }
     }
-    while (left > 0) eager();
+    // an even number of two-step sweeps, so that n steps leave the state in the
+    // lattice n swaps away
+    while (e->two && left >= 4) {
+        eager(true);
+        eager(true);
+    }
+    while (left > 0) eager(false);
     return launch_status();
 }
 
@@ -2609,6 +2719,14 @@ lbm_status lbm_ens_autotune(lbm_ens *e, int32_t iters, double *ms, int32_t *chos
         if (m > 0) best = trials[jb];
     }
     if (ok && ens_set_layout(e, 1 << best.l) != LBM_OK) ok = false;
+    // Two-step sweeps, if two steps in one are faster than two of that launch.
+    int two = 0;
+    if (ok && e->two_possible) {
+        const double one = ens_time_launch(e, best.k, best.o, best.c, 2 * iters, e0, e1);
+        const double both = ens_time_two_steps(e, 2 * iters, e0, e1);
+        ok = one > 0.0 && both > 0.0;
+        two = ok && both < 2.0 * one && double(e->total_cells) >= kTwoStepNodesPerParticle * double(e->n);
+    }
     if (ok) {
         err = hipMemcpyAsync(e->clock, &saved, sizeof(saved), hipMemcpyHostToDevice, e->stream);
         if (err == hipSuccess) err = hipStreamSynchronize(e->stream);
@@ -2617,11 +2735,12 @@ lbm_status lbm_ens_autotune(lbm_ens *e, int32_t iters, double *ms, int32_t *chos
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (!ok) return LBM_E_DEVICE;
-    if (best.k != e->shape || best.o != e->order || best.c != e->cap) ens_drop_graph(e);
+    if (best.k != e->shape || best.o != e->order || best.c != e->cap || two != e->two) ens_drop_graph(e);
     e->shape = best.k;
     e->order = best.o;
     e->cap = best.c;
-    tune_store(ens_tune_key(e), tune_code(best.k, best.o, best.c, best.l));
+    e->two = two;
+    tune_store(ens_tune_key(e), tune_code(best.k, best.o, best.c, best.l) + kTuneTwo * (two + 1));
     if (ms)
         for (int k = 0; k < kNumShapes; ++k) ms[k] = best_k[k];
     if (chosen) *chosen = best.k;

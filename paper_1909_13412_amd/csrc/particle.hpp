@@ -12,6 +12,7 @@
 #include "lbmbp.h"
 #include "codec.hpp"
 #include "collide.hpp"
+#include "replica.hpp"
 #include "velocities.hpp"
 #include "philox.hpp"
 
@@ -554,6 +555,95 @@ __global__ __launch_bounds__(kAheadBlock) void k_particle_ahead(
         V[k] = pa.v[3 * ii + k];
     }
     const ParticleSite<C> site{A, g, cur, cur, cur, pa.seed, pa.replica, uint32_t(i), pa.R};
+    AheadGather<C, N> gather{post[lane >> 3], p};
+    particle_lane<C>(site, gather, dec_s, pa, i, p, valid, r, V);
+}
+
+// ---------------------------------------------------------------------------
+// The same two kernels over the particles of every box of an ensemble.
+// ---------------------------------------------------------------------------
+
+// Step-dependent values from the device clock, `ahead` steps after it.
+__device__ inline void clock_args(ParticleArgs &pa, const EnsClock *__restrict__ clock, int ahead) {
+    pa.step = uint32_t(clock->step + ahead);
+    if (pa.acc) {
+        const int64_t t = clock->vacf_t + ahead;
+        pa.t = t;
+        pa.k_hi = t / pa.stride;
+        pa.k_lo = t > pa.max_lag ? (t - pa.max_lag + pa.stride - 1) / pa.stride : 0;
+        pa.slot_lo = int32_t(pa.k_lo % pa.nslot);
+    }
+}
+
+template <class C>
+__device__ inline ParticleSite<C> replica_site(const typename C::T *__restrict__ A, const Replica &rp, int32_t i,
+                                               const ForceField &cur, const ForceField &last,
+                                               const ForceField &older) {
+    return ParticleSite<C>{A + rp.pop_off,
+                           rp.g,
+                           cur.box(rp.cell_off, rp.mask_off),
+                           last.box(rp.cell_off, rp.mask_off),
+                           older.box(rp.cell_off, rp.mask_off),
+                           rp.seed,
+                           rp.replica_id,
+                           uint32_t(i) - rp.part_off,
+                           rp.R};
+}
+
+// ahead: steps after the device clock (1: a second step that reads no fluid).
+template <class C>
+__global__ __launch_bounds__(kParticleBlock) void k_ens_particle(
+    const typename C::T *__restrict__ A, const Replica *__restrict__ reps,
+    const uint16_t *__restrict__ part_rep, typename C::R dec_s, ParticleArgs pa,
+    const EnsClock *__restrict__ clock, int ahead, ForceField cur, ForceField last, ForceField older) {
+    const uint32_t gt = blockIdx.x * kParticleBlock + threadIdx.x;
+    const int32_t i = int32_t(gt >> 3);
+    const int p = int(gt & 7u);
+    const bool valid = i < pa.n;
+    const int32_t ii = valid ? i : pa.n - 1;
+    clock_args(pa, clock, ahead);
+    double r[3], V[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        r[k] = pa.r[3 * ii + k];
+        V[k] = pa.v[3 * ii + k];
+    }
+    const ParticleSite<C> site = replica_site<C>(A, reps[part_rep[ii]], ii, cur, last, older);
+    LatticeGather<C> gather{site.A, {}};
+    particle_lane<C>(site, gather, dec_s, pa, i, p, valid, r, V);
+}
+
+template <class C, int N>
+__global__ __launch_bounds__(kAheadBlock) void k_ens_particle_ahead(
+    const typename C::T *__restrict__ A, const Replica *__restrict__ reps,
+    const uint16_t *__restrict__ part_rep, typename C::R enc_s, typename C::R dec_s, ParticleArgs pa,
+    const EnsClock *__restrict__ clock, ForceField f0, ForceField cur) {
+    using R = typename C::R;
+    __shared__ typename C::T post[kAheadParticles][C::V::Q][N * N * N];
+    const int wave = int(threadIdx.x >> 6), lane = int(threadIdx.x & 63u);
+    if (wave < kAheadParticles) {
+        const int32_t i = int32_t(blockIdx.x) * kAheadParticles + wave;
+        if (i < pa.n) {
+            const Replica &rp = reps[part_rep[i]];
+            const double r[3] = {pa.r[3 * i + 0], pa.r[3 * i + 1], pa.r[3 * i + 2]};
+            ahead_nodes<C, N>(A + rp.pop_off, rp.g, R(rp.omega), enc_s, dec_s, R(0), R(0), R(0),
+                              f0.box(rp.cell_off, rp.mask_off), r, post[wave]);
+        }
+        __syncthreads();
+        return;
+    }
+    const int p = lane & 7;
+    const int32_t i = int32_t(blockIdx.x) * kAheadParticles + (lane >> 3);
+    const bool valid = i < pa.n;
+    const int32_t ii = valid ? i : pa.n - 1;
+    clock_args(pa, clock, 1);
+    double r[3], V[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        r[k] = pa.r[3 * ii + k];
+        V[k] = pa.v[3 * ii + k];
+    }
+    const ParticleSite<C> site = replica_site<C>(A, reps[part_rep[ii]], ii, cur, cur, cur);
     AheadGather<C, N> gather{post[lane >> 3], p};
     particle_lane<C>(site, gather, dec_s, pa, i, p, valid, r, V);
 }

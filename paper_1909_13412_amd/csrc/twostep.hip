@@ -41,6 +41,47 @@ void launch_particle_ahead(const TwoStepArgs &a, const ParticleArgs &pa) {
         launch_ahead_as<C, 4>(a, pa);
 }
 
+template <class C, bool NTS>
+static void launch_ens_two_steps_as(const EnsTwoStepArgs &a) {
+    using T = typename C::T;
+    using R = typename C::R;
+    using S = TwoStepShape<T>;
+    hipLaunchKernelGGL((k_ens_two_steps<C, NTS, S::kNodes, S::kBuffers, S::kEarly>), dim3(a.blocks), dim3(a.threads), 0,
+                       a.stream, static_cast<const T *>(a.A), static_cast<T *>(a.B), a.reps, a.blk_rep, a.f0, a.f1,
+                       R(a.enc_s), R(a.dec_s), a.clock, a.vacf_on);
+}
+
+template <class C>
+void launch_ens_two_steps(const EnsTwoStepArgs &a) {
+    a.nts ? launch_ens_two_steps_as<C, true>(a) : launch_ens_two_steps_as<C, false>(a);
+}
+
+template <class C, int N>
+static void launch_ens_ahead_as(const EnsTwoStepArgs &a, const ParticleArgs &pa) {
+    using T = typename C::T;
+    using R = typename C::R;
+    const dim3 grid(unsigned((pa.n + kAheadParticles - 1) / kAheadParticles));
+    hipLaunchKernelGGL((k_ens_particle_ahead<C, N>), grid, dim3(kAheadBlock), 0, a.stream, static_cast<const T *>(a.A),
+                       a.reps, a.part_rep, R(a.enc_s), R(a.dec_s), pa, a.clock, a.f0, a.f1);
+}
+
+template <class C>
+void launch_ens_particle_ahead(const EnsTwoStepArgs &a, const ParticleArgs &pa) {
+    if (pa.friction == LBM_FRICTION_STOKESLET_2DX || pa.friction == LBM_FRICTION_STOKESLET_CUBE)
+        launch_ens_ahead_as<C, 5>(a, pa);
+    else
+        launch_ens_ahead_as<C, 4>(a, pa);
+}
+
+#define LBM_ENS_TWO_STEP(CODEC)                                                   \
+    template void launch_ens_two_steps<Cfg<CODEC, D3Q19>>(const EnsTwoStepArgs &); \
+    template void launch_ens_particle_ahead<Cfg<CODEC, D3Q19>>(const EnsTwoStepArgs &, const ParticleArgs &);
+LBM_ENS_TWO_STEP(CodecF64)
+LBM_ENS_TWO_STEP(CodecF32)
+LBM_ENS_TWO_STEP(CodecBF16)
+LBM_ENS_TWO_STEP(CodecF16)
+#undef LBM_ENS_TWO_STEP
+
 #define LBM_TWO_STEP(CODEC, VEL)                                       \
     template void launch_two_steps<Cfg<CODEC, VEL>>(const TwoStepArgs &); \
     template void launch_particle_ahead<Cfg<CODEC, VEL>>(const TwoStepArgs &, const ParticleArgs &);

@@ -8,16 +8,10 @@
 
 #include "codec.hpp"
 #include "collide.hpp"
+#include "replica.hpp"
 #include "velocities.hpp"
 
 namespace lbmbp {
-
-// The blocks of a sweep: tiles of tx x ty nodes in (x, y), lz planes deep (the
-// last ones may be smaller).
-struct TwoStepTiles {
-    uint32_t tx, ty, lz;
-    uint32_t ntx, nty, nslab;  // ceil(n / extent)
-};
 
 // Nodes of a padded tile (lanes of a block and LDS nodes) at most, LDS buffers,
 // and whether the loads of the next plane go out before the first step's
@@ -49,23 +43,18 @@ __device__ inline uint32_t held_copy(uint32_t v) {
 __device__ inline uint16_t held_copy(uint16_t v) { return v; }  // decoding moves it
 __device__ inline double held_copy(double v) { return v; }
 
+// One block: the nodes [x0, x0 + w) x [y0, y0 + h) x [z0, z0 + d).
 template <class C, bool FORCED, bool NTS, int NMAX, int BUF, bool EARLY>
-__global__ __launch_bounds__(NMAX) void k_two_steps(
-    const typename C::T *__restrict__ A, typename C::T *__restrict__ B, Grid g, typename C::R omega,
-    typename C::R enc_s, typename C::R dec_s, ForceField f0, ForceField f1, typename C::R Gx,
-    typename C::R Gy, typename C::R Gz, TwoStepTiles tl, uint32_t order) {
+__device__ inline void two_steps_block(const typename C::T *__restrict__ A, typename C::T *__restrict__ B,
+                                       const Grid &g, typename C::R omega, typename C::R enc_s,
+                                       typename C::R dec_s, const ForceField &f0, const ForceField &f1,
+                                       typename C::R Gx, typename C::R Gy, typename C::R Gz, uint32_t x0,
+                                       uint32_t y0, uint32_t z0, uint32_t w, uint32_t h, uint32_t d,
+                                       typename C::T (&post)[BUF][C::V::Q][NMAX]) {
 #pragma clang fp contract(on)  // as node_relax
     using T = typename C::T;
     using R = typename C::R;
     using V = typename C::V;
-    __shared__ T post[BUF][V::Q][NMAX];
-
-    const uint32_t blk = sweep_block(order);
-    const uint32_t per = tl.ntx * tl.nty;
-    const uint32_t slab = blk / per, tile = blk - slab * per;
-    const uint32_t by = tile / tl.ntx, bx = tile - by * tl.ntx;
-    const uint32_t x0 = bx * tl.tx, y0 = by * tl.ty, z0 = slab * tl.lz;
-    const uint32_t w = min(tl.tx, g.nx - x0), h = min(tl.ty, g.ny - y0), d = min(tl.lz, g.nz - z0);
     const uint32_t pw = w + 2;  // row pitch of the padded tile in LDS
 
     auto up = [&](uint32_t z) { return z + 1 == g.nz ? 0u : z + 1; };
@@ -221,6 +210,55 @@ __global__ __launch_bounds__(NMAX) void k_two_steps(
             flip();
         }
     }
+}
+
+// Block b of a box's sweep: tiles in x, then y, then slabs of planes.
+struct TwoStepBlock {
+    uint32_t x0, y0, z0, w, h, d;
+    __device__ inline TwoStepBlock(const TwoStepTiles &tl, const Grid &g, uint32_t b) {
+        const uint32_t per = tl.ntx * tl.nty;
+        const uint32_t slab = b / per, tile = b - slab * per;
+        const uint32_t by = tile / tl.ntx, bx = tile - by * tl.ntx;
+        x0 = bx * tl.tx;
+        y0 = by * tl.ty;
+        z0 = slab * tl.lz;
+        w = min(tl.tx, g.nx - x0);
+        h = min(tl.ty, g.ny - y0);
+        d = min(tl.lz, g.nz - z0);
+    }
+};
+
+template <class C, bool FORCED, bool NTS, int NMAX, int BUF, bool EARLY>
+__global__ __launch_bounds__(NMAX) void k_two_steps(
+    const typename C::T *__restrict__ A, typename C::T *__restrict__ B, Grid g, typename C::R omega,
+    typename C::R enc_s, typename C::R dec_s, ForceField f0, ForceField f1, typename C::R Gx,
+    typename C::R Gy, typename C::R Gz, TwoStepTiles tl, uint32_t order) {
+    __shared__ typename C::T post[BUF][C::V::Q][NMAX];
+    const TwoStepBlock t(tl, g, sweep_block(order));
+    two_steps_block<C, FORCED, NTS, NMAX, BUF, EARLY>(A, B, g, omega, enc_s, dec_s, f0, f1, Gx, Gy, Gz, t.x0, t.y0,
+                                                      t.z0, t.w, t.h, t.d, post);
+}
+
+// Every box of an ensemble (block -> box table); advances the device clock by
+// the two steps.
+template <class C, bool NTS, int NMAX, int BUF, bool EARLY>
+__global__ __launch_bounds__(NMAX) void k_ens_two_steps(
+    const typename C::T *__restrict__ A, typename C::T *__restrict__ B, const Replica *__restrict__ reps,
+    const uint16_t *__restrict__ blk_rep, ForceField f0, ForceField f1, typename C::R enc_s,
+    typename C::R dec_s, EnsClock *clock, int vacf_on) {
+    using R = typename C::R;
+    __shared__ typename C::T post[BUF][C::V::Q][NMAX];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        // the steps' last reader of the clock has finished (previous kernel)
+        clock->step += 2;
+        if (vacf_on) clock->vacf_t += 2;
+    }
+    const Replica &rp = reps[blk_rep[blockIdx.x]];
+    const Grid g = rp.g;
+    const TwoStepBlock t(rp.two, g, blockIdx.x - rp.first_two);
+    two_steps_block<C, true, NTS, NMAX, BUF, EARLY>(A + rp.pop_off, B + rp.pop_off, g, R(rp.omega), enc_s, dec_s,
+                                                    f0.box(rp.cell_off, rp.mask_off), f1.box(rp.cell_off, rp.mask_off),
+                                                    R(0), R(0), R(0), t.x0, t.y0, t.z0, t.w, t.h, t.d, post);
 }
 
 }  // namespace lbmbp

@@ -30,4 +30,24 @@ void launch_two_steps(const TwoStepArgs &a);
 template <class C>
 void launch_particle_ahead(const TwoStepArgs &a, const ParticleArgs &pa);
 
+// The same over an ensemble's boxes.
+struct EnsTwoStepArgs {
+    const void *A;
+    void *B;
+    const Replica *reps;
+    const uint16_t *blk_rep, *part_rep;
+    unsigned blocks, threads;
+    double enc_s, dec_s;
+    ForceField f0, f1;
+    EnsClock *clock;
+    int vacf_on;
+    bool nts;
+    hipStream_t stream;
+};
+
+template <class C>
+void launch_ens_two_steps(const EnsTwoStepArgs &a);
+template <class C>
+void launch_ens_particle_ahead(const EnsTwoStepArgs &a, const ParticleArgs &pa);
+
 }  // namespace lbmbp
