@@ -149,8 +149,9 @@ __global__ __launch_bounds__(kParticleBlock) void k_adj_particle(
         const uint32_t wb = q == 2 ? x.v[3] : x.v[1];
         double zq;
         box_muller_one(wa, wb, q == 1, &zq);
-#pragma unroll
-        for (int k = 0; k < 3; ++k) xi[k] = __shfl(zq, k, 8);
+        xi[0] = from8<0>(zq, p);
+        xi[1] = from8<1>(zq, p);
+        xi[2] = from8<2>(zq, p);
     }
     double FH[3];
     FitTrace tr;

@@ -451,6 +451,9 @@ size_t grid_scratch_size(const lbm_grid_desc *g) {
 
 size_t particle_blocks(int32_t n) { return (size_t(n) * 8 + kParticleBlock - 1) / kParticleBlock; }
 
+// Lanes of a particle block: a second wavefront takes the VACF sample.
+unsigned particle_threads(const ParticleArgs &pa) { return pa.acc ? 2 * kParticleBlock : kParticleBlock; }
+
 // Advisory conditions of a particle set (section 2.2's parameter ranges and
 // the sign of the fit's gain); see LBM_WARN_* in the header.
 uint32_t coupling_warnings(int32_t friction, double R, int32_t n, double ncell) {
@@ -475,27 +478,13 @@ uint32_t pair_buckets(int32_t n) {
 }
 
 size_t pair_list_bytes(int32_t n) {
-    const size_t T = pair_buckets(n);
-    return align_up(size_t(n) * 8, kAlign) + 3 * align_up(size_t(n) * 4, kAlign) +
-           align_up(T * 4, kAlign) + align_up((T + 1) * 4, kAlign);
+    return align_up(size_t(n) * sizeof(PairLink), kAlign) + align_up(size_t(pair_buckets(n)) * 4, kAlign);
 }
 
 // Carves the cell list out of pair_list_bytes(n) bytes at s.
 PairList pair_list_at(char *s, int32_t n) {
-    const size_t T = pair_buckets(n);
-    PairList pl;
-    pl.cell = reinterpret_cast<uint64_t *>(s);
-    s += align_up(size_t(n) * 8, kAlign);
-    pl.bucket = reinterpret_cast<uint32_t *>(s);
-    s += align_up(size_t(n) * 4, kAlign);
-    pl.slot = reinterpret_cast<uint32_t *>(s);
-    s += align_up(size_t(n) * 4, kAlign);
-    pl.list = reinterpret_cast<uint32_t *>(s);
-    s += align_up(size_t(n) * 4, kAlign);
-    pl.count = reinterpret_cast<uint32_t *>(s);
-    s += align_up(T * 4, kAlign);
-    pl.start = reinterpret_cast<uint32_t *>(s);
-    return pl;
+    return PairList{reinterpret_cast<PairLink *>(s),
+                    reinterpret_cast<uint32_t *>(s + align_up(size_t(n) * sizeof(PairLink), kAlign))};
 }
 
 size_t particle_scratch_size(int32_t n) {
@@ -588,17 +577,18 @@ dim3 pair_group_blocks(int32_t n) {
     return dim3(unsigned((size_t(n) * kPairLanes + kPairBlock - 1) / kPairBlock));
 }
 
-// Pair forces of the positions r: build the cell list (its counts start and
-// end at zero), then the neighbour sums.
+// Pair forces of the positions r: link the cell list, then the neighbour sums.
+// The list heads are none before; the particle update that follows sets them
+// back (its pair_list), or pair_list_clear does.
 void launch_pairs(hipStream_t st, const double *r, int32_t n, const PairGrid &pg, const PairList &pl,
                   double *F) {
     const dim3 pblocks(unsigned((n + kPairBlock - 1) / kPairBlock));
-    hipLaunchKernelGGL(k_pair_count, pblocks, dim3(kPairBlock), 0, st, r, n, pg, pl);
-    hipLaunchKernelGGL(k_pair_scan, dim3(1), dim3(kPairScanThreads), 0, st, pg, pl);
-    hipLaunchKernelGGL(k_pair_scatter, pblocks, dim3(kPairBlock), 0, st, n, pl);
-    hipLaunchKernelGGL(k_pair_bucket_sort, dim3((pg.T + kPairBlock - 1) / kPairBlock), dim3(kPairBlock), 0,
-                       st, pg, pl);
+    hipLaunchKernelGGL(k_pair_link, pblocks, dim3(kPairBlock), 0, st, r, n, pg, pl);
     hipLaunchKernelGGL(k_pair_force, pair_group_blocks(n), dim3(kPairBlock), 0, st, r, n, pg, pl, F);
+}
+
+hipError_t pair_list_clear(hipStream_t st, const PairList &pl, uint32_t T) {
+    return hipMemsetAsync(pl.head, 0xFF, size_t(T) * 4, st);
 }
 
 // Returns the start event of a new timing pair (or nullptr when profiling is
@@ -661,8 +651,8 @@ ParticleArgs step_particle_args(lbm_ctx *c) {
         pa.max_lag = c->max_lag;
         c->vacf_t += 1;
     }
-    pa.r = c->r;
-    pa.v = c->v;
+    pa.r = pa.r_out = c->r;
+    pa.v = pa.v_out = c->v;
     pa.fh = c->fh;
     pa.fr = c->fr;
     // this step's nodes, and those still to be released: the last step's, and
@@ -682,9 +672,11 @@ ParticleArgs step_particle_args(lbm_ctx *c) {
     pa.step = uint32_t(c->step);
     pa.fext = c->fext;
     pa.fpair = nullptr;
+    pa.pair_list = PairList{nullptr, nullptr};
     if (c->pair_on) {
         launch_pairs(c->stream, c->r, c->np, c->pg, c->plist, c->fpair);
         pa.fpair = c->fpair;
+        pa.pair_list = c->plist;
     }
     return pa;
 }
@@ -692,7 +684,7 @@ ParticleArgs step_particle_args(lbm_ctx *c) {
 template <class C>
 void launch_particle(lbm_ctx *c, const typename C::T *A, const ParticleArgs &pa, int64_t n) {
     c->fields_used = 1;
-    hipLaunchKernelGGL(k_particle<C>, dim3(unsigned(particle_blocks(c->np))), dim3(kParticleBlock), 0, c->stream, A,
+    hipLaunchKernelGGL(k_particle<C>, dim3(unsigned(particle_blocks(c->np))), dim3(particle_threads(pa)), 0, c->stream, A,
                        c->g, typename C::R(c->dec_s), pa, field(c, n), field(c, n + 2), field(c, n + 1));
 }
 
@@ -1418,10 +1410,10 @@ lbm_status particles_couple(lbm_ctx *ctx, const lbm_particle_desc *d, double *r,
     ctx->plist = pair_list_at(s, d->n);
     s += pair_list_bytes(d->n);
     ctx->fpair = reinterpret_cast<double *>(s);
-    // nodes spread to -> kNoNode (all ones); forces and bucket counts zero.
+    // nodes spread to -> kNoNode (all ones), list heads -> none; forces zero.
     e = hipMemsetAsync(ctx->cells[0], 0xFF, 2 * align_up(size_t(d->n) * 8 * 4, kAlign), ctx->stream);
     if (e == hipSuccess)
-        e = hipMemsetAsync(ctx->plist.count, 0, size_t(pair_buckets(d->n)) * 4, ctx->stream);
+        e = pair_list_clear(ctx->stream, ctx->plist, pair_buckets(d->n));
     if (e == hipSuccess) e = hipMemsetAsync(ctx->fh, 0, size_t(d->n) * 3 * 8, ctx->stream);
     if (e == hipSuccess) e = hipMemsetAsync(ctx->fr, 0, size_t(d->n) * 3 * 8, ctx->stream);
     return e == hipSuccess ? LBM_OK : LBM_E_DEVICE;
@@ -1445,6 +1437,7 @@ lbm_status lbm_set_pair_force(lbm_ctx *ctx, double a_f, double r_c) {
         pg.L[k] = double(Ln[k]);
     }
     pg.T = pair_buckets(ctx->np);
+    pg.n = uint32_t(ctx->np);
     pg.a = a_f;
     pg.rc = r_c;
     ctx->pg = pg;
@@ -2048,8 +2041,8 @@ bool ens_two_possible(const EnsLayout &L) { return L.two_ok && L.two_blocks > 0;
 ParticleArgs ens_particle_args(lbm_ens *e) {
     ParticleArgs pa;
     memset(&pa, 0, sizeof(pa));
-    pa.r = e->r;
-    pa.v = e->v;
+    pa.r = pa.r_out = e->r;
+    pa.v = pa.v_out = e->v;
     pa.fh = e->fh;
     pa.fr = e->fr;
     pa.err = e->err;
@@ -2105,7 +2098,7 @@ void ens_launch_particle(lbm_ens *e, const typename C::T *A, int64_t n, int ahea
         pa.last_cells = e->cells[(n & 1) ^ 1];
         pa.older_cells = pa.cells;
     }
-    hipLaunchKernelGGL(k_ens_particle<C>, dim3(unsigned(particle_blocks(e->n))), dim3(kParticleBlock), 0, e->stream, A,
+    hipLaunchKernelGGL(k_ens_particle<C>, dim3(unsigned(particle_blocks(e->n))), dim3(particle_threads(pa)), 0, e->stream, A,
                        e->reps, e->part_rep, typename C::R(e->dec_s), pa, e->clock, ahead, ens_field(e, n),
                        ens_field(e, n + 2), ens_field(e, n + 1));
 }
@@ -3054,7 +3047,7 @@ hipError_t adjoint_run(lbm_ctx *c, char *tape, char *work, double *adj_pop, doub
     memset_(prev_adj, 0xFF, size_t(np) * 8 * 4);
     memset_(pgrad, 0, size_t(np) * 4 * 8);
     memset_(wacc, 0, size_t(blocks_for(c->g.ncell)) * 8);
-    if (pairs) memset_(plist.count, 0, size_t(c->rec_pg.T) * 4);
+    if (pairs && e == hipSuccess) e = pair_list_clear(st, plist, c->rec_pg.T);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_adj_import<typename C::V>, dim3(blocks_for(c->g.ncell)), dim3(kBlock), 0, st, adj_pop,
                        abar[0], gd);
@@ -3128,14 +3121,16 @@ hipError_t adjoint_run(lbm_ctx *c, char *tape, char *work, double *adj_pop, doub
             const int64_t n = c->rec_n0 + int64_t(j) * K + k;
             const int par = int(n & 1);
             if (np > 0) {
-                copy_(seg_r(k + 1), seg_r(k), 2 * pbytes);
-                pa.r = seg_r(k + 1);
-                pa.v = seg_v(k + 1);
+                pa.r = seg_r(k);
+                pa.v = seg_v(k);
+                pa.r_out = seg_r(k + 1);
+                pa.v_out = seg_v(k + 1);
                 pa.step = uint32_t(n);
                 pa.fpair = nullptr;
                 if (pairs) {
                     launch_pairs(st, seg_r(k), np, c->rec_pg, plist, fpair);
                     pa.fpair = fpair;
+                    pa.pair_list = plist;
                 }
                 hipLaunchKernelGGL(k_particle<C>, dim3(pgrid), dim3(kParticleBlock), 0, st, seg(k),
                                    c->g, R(c->dec_s), pa, ff[par], ff[par ^ 1], ff[par]);
@@ -3160,9 +3155,11 @@ hipError_t adjoint_run(lbm_ctx *c, char *tape, char *work, double *adj_pop, doub
                 hipLaunchKernelGGL(k_adj_particle<C>, dim3(pgrid), dim3(kParticleBlock), 0, st,
                                    seg(k), c->g, R(c->dec_s), abar[cur], gd, ap, uf[par],
                                    uf[par ^ 1]);
-                if (pairs)
+                if (pairs) {
                     hipLaunchKernelGGL(k_adj_pair, pair_group_blocks(np), dim3(kPairBlock), 0, st,
                                        seg_r(k), np, c->rec_pg, plist, fcbar, adj_r);
+                    if (e == hipSuccess) e = pair_list_clear(st, plist, c->rec_pg.T);
+                }
                 if (stream_stores)
                     launch_adj_collide<C, true, true>(st, cgrid, seg(k), c->g, R(c->dec_s), abar[cur], abar[cur ^ 1], gd,
                                        1.0 / c->desc.tau, uf[par], wacc);

@@ -12,6 +12,7 @@
 #include "lbmbp.h"
 #include "codec.hpp"
 #include "collide.hpp"
+#include "pair_list.hpp"
 #include "replica.hpp"
 #include "velocities.hpp"
 #include "philox.hpp"
@@ -27,7 +28,8 @@ constexpr uint32_t kNoNode = 0xFFFFFFFFu;
 // floor(s) + (p & 1, p >> 1 & 1, p >> 2 & 1).
 // ---------------------------------------------------------------------------
 struct ParticleArgs {
-    double *r, *v;
+    const double *r, *v;    // state at the start of the step
+    double *r_out, *v_out;  // and after it (may be r and v)
     double *fh, *fr;
     uint32_t *cells;  // [n][8] out: node each lane spread to this step, or kNoNode
     // [n][8] nodes spread to in the last step and in the one before (nullptr:
@@ -54,13 +56,40 @@ struct ParticleArgs {
     const double *fext;
     // pair forces of this step, [n][3] (nullptr: none); F_C = fext + fpair
     const double *fpair;
+    // the cell list they came from, to be emptied (head nullptr: none)
+    PairList pair_list;
 };
 
+// v of another lane of the same eight, moved in the vector unit (DPP), without
+// the LDS round trip of a shuffle (some 100 cycles each; an update makes 15 to
+// 60 such exchanges one after another: reverse-mode particle kernel 9.3 -> 8.5
+// us, forward 5.9 -> 5.7 us at 64^3, 16 particles).
+template <int CTRL>
+__device__ inline double lane8_move(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = uint32_t(__builtin_amdgcn_update_dpp(0, int(uint32_t(b)), CTRL, 0xf, 0xf, true));
+    const uint32_t hi = uint32_t(__builtin_amdgcn_update_dpp(0, int(uint32_t(b >> 32)), CTRL, 0xf, 0xf, true));
+    return __builtin_bit_cast(double, uint64_t(hi) << 32 | lo);
+}
+constexpr int kQuadXor1 = 0xB1, kQuadXor2 = 0x4E;  // quad_perm [1,0,3,2] and [2,3,0,1]
+constexpr int kHalfMirror = 0x141;                 // lane l to 7 - l of every eight
+
+// Sum over the eight lanes of a particle, in every lane (the butterfly over 1,
+// 2, 4: after the first two every lane of a quad holds the same partial sum,
+// so the mirrored lane's is the other quad's).
 __device__ inline double sum8(double v) {
-    v += __shfl_xor(v, 1, 8);
-    v += __shfl_xor(v, 2, 8);
-    v += __shfl_xor(v, 4, 8);
+    v += lane8_move<kQuadXor1>(v);
+    v += lane8_move<kQuadXor2>(v);
+    v += lane8_move<kHalfMirror>(v);
     return v;
+}
+
+// Lane K's value (K < 4) in all eight lanes.
+template <int K>
+__device__ inline double from8(double v, int p) {
+    const double q = lane8_move<K * 0x55>(v);  // quad_perm [K,K,K,K]
+    const double other = lane8_move<kHalfMirror>(q);
+    return p < 4 ? q : other;
 }
 
 // Intermediates of the Stokeslet fit that its adjoint reuses.
@@ -189,6 +218,7 @@ __device__ inline void release_node(const ForceField &old, uint32_t pc) {
 // lattice as soon as the node is known and consumed when it is needed.
 template <class C>
 struct LatticeGather {
+    static constexpr bool kSample = false;  // another wavefront takes the VACF sample
     const typename C::T *__restrict__ A;
     typename C::T raw[C::V::Q];
     __device__ inline void issue(const uint32_t (&node)[3], const Grid &g) {
@@ -204,6 +234,64 @@ struct LatticeGather {
         return raw[a];
     }
 };
+
+// The VACF sample of lane p of particle i (V: its velocity V^n).
+__device__ inline void vacf_sample(const ParticleArgs &pa, int32_t i, int p, bool valid, const double (&V)[3]) {
+    // C_v(t) = <V(0).V(t)> (section 2.1): V^n against every active origin;
+    // lane p takes the origins k = k_lo + p, k_lo + p + 8, ...  The newest
+    // origin (lag 0) is stored by the lane that owns it.  Origins go in
+    // batches of kVacfBatch: all loads of a batch before any of its stores.
+    if (valid && pa.acc) {
+        // accumulators are lag-major (acc[lag][n]): the same lane of the eight
+        // particles of a wavefront updates eight consecutive doubles
+        double *acc_i = pa.acc + i;
+        const int64_t n = pa.n;
+        // origin k lives in slot k % nslot; this lane's origins k_lo + p,
+        // k_lo + p + 8, ... step through the slots by 8 (mod nslot)
+        const int32_t ns = pa.nslot;
+        const int32_t d8 = 8 % ns;
+        int32_t slot = pa.slot_lo + p % ns;
+        slot = slot >= ns ? slot - ns : slot;
+        for (int64_t k0 = pa.k_lo + p; k0 <= pa.k_hi; k0 += 8 * kVacfBatch) {
+            double ov[kVacfBatch][3], av[kVacfBatch];
+            int32_t sl[kVacfBatch];
+#pragma unroll
+            for (int c = 0; c < kVacfBatch; ++c) {
+                sl[c] = slot;
+                slot += d8;
+                slot = slot >= ns ? slot - ns : slot;
+            }
+#pragma unroll
+            for (int c = 0; c < kVacfBatch; ++c) {
+                const int64_t k = k0 + 8 * c;
+                const int64_t lag = pa.t - k * pa.stride;
+                ov[c][0] = ov[c][1] = ov[c][2] = av[c] = 0.0;
+                if (k <= pa.k_hi && lag != 0) {
+                    const double *o = pa.origins + (int64_t(sl[c]) * pa.n + i) * 3;
+                    ov[c][0] = o[0];
+                    ov[c][1] = o[1];
+                    ov[c][2] = o[2];
+                    av[c] = acc_i[lag * n];
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < kVacfBatch; ++c) {
+                const int64_t k = k0 + 8 * c;
+                if (k > pa.k_hi) break;
+                const int64_t lag = pa.t - k * pa.stride;
+                if (lag == 0) {
+                    double *o = pa.origins + (int64_t(sl[c]) * pa.n + i) * 3;
+                    o[0] = V[0];
+                    o[1] = V[1];
+                    o[2] = V[2];
+                    acc_i[0] += V[0] * V[0] + V[1] * V[1] + V[2] * V[2];
+                } else {
+                    acc_i[lag * n] = av[c] + (ov[c][0] * V[0] + ov[c][1] * V[1] + ov[c][2] * V[2]);
+                }
+            }
+        }
+    }
+}
 
 // One lane (node p of particle i) of the coupled particle update.  r, V are
 // the particle's position and velocity at the start of the step; the whole
@@ -271,60 +359,7 @@ __device__ inline void particle_lane(const ParticleSite<C> &site, Gather &gather
         }
     }
 
-    // C_v(t) = <V(0).V(t)> (section 2.1): V^n against every active origin;
-    // lane p takes the origins k = k_lo + p, k_lo + p + 8, ...  The newest
-    // origin (lag 0) is stored by the lane that owns it.  Origins go in
-    // batches of kVacfBatch: all loads of a batch before any of its stores.
-    if (valid && pa.acc) {
-        // accumulators are lag-major (acc[lag][n]): the same lane of the eight
-        // particles of a wavefront updates eight consecutive doubles
-        double *acc_i = pa.acc + i;
-        const int64_t n = pa.n;
-        // origin k lives in slot k % nslot; this lane's origins k_lo + p,
-        // k_lo + p + 8, ... step through the slots by 8 (mod nslot)
-        const int32_t ns = pa.nslot;
-        const int32_t d8 = 8 % ns;
-        int32_t slot = pa.slot_lo + p % ns;
-        slot = slot >= ns ? slot - ns : slot;
-        for (int64_t k0 = pa.k_lo + p; k0 <= pa.k_hi; k0 += 8 * kVacfBatch) {
-            double ov[kVacfBatch][3], av[kVacfBatch];
-            int32_t sl[kVacfBatch];
-#pragma unroll
-            for (int c = 0; c < kVacfBatch; ++c) {
-                sl[c] = slot;
-                slot += d8;
-                slot = slot >= ns ? slot - ns : slot;
-            }
-#pragma unroll
-            for (int c = 0; c < kVacfBatch; ++c) {
-                const int64_t k = k0 + 8 * c;
-                const int64_t lag = pa.t - k * pa.stride;
-                ov[c][0] = ov[c][1] = ov[c][2] = av[c] = 0.0;
-                if (k <= pa.k_hi && lag != 0) {
-                    const double *o = pa.origins + (int64_t(sl[c]) * pa.n + i) * 3;
-                    ov[c][0] = o[0];
-                    ov[c][1] = o[1];
-                    ov[c][2] = o[2];
-                    av[c] = acc_i[lag * n];
-                }
-            }
-#pragma unroll
-            for (int c = 0; c < kVacfBatch; ++c) {
-                const int64_t k = k0 + 8 * c;
-                if (k > pa.k_hi) break;
-                const int64_t lag = pa.t - k * pa.stride;
-                if (lag == 0) {
-                    double *o = pa.origins + (int64_t(sl[c]) * pa.n + i) * 3;
-                    o[0] = V[0];
-                    o[1] = V[1];
-                    o[2] = V[2];
-                    acc_i[0] += V[0] * V[0] + V[1] * V[1] + V[2] * V[2];
-                } else {
-                    acc_i[lag * n] = av[c] + (ov[c][0] * V[0] + ov[c][1] * V[1] + ov[c][2] * V[2]);
-                }
-            }
-        }
-    }
+    if (gather.kSample) vacf_sample(pa, i, p, valid, V);
 
     // Eqs. s2-rf1, s2-rf2: white noise of variance 2 gamma kT per step.  The
     // three Box-Muller outputs are computed by lanes 0, 1, 2 of the group
@@ -338,8 +373,9 @@ __device__ inline void particle_lane(const ParticleSite<C> &site, Gather &gather
         const uint32_t wb = q == 2 ? x.v[3] : x.v[1];
         double zq;
         box_muller_one(wa, wb, q == 1, &zq);
-#pragma unroll
-        for (int k = 0; k < 3; ++k) FR[k] = pa.sig * __shfl(zq, k, 8);
+        FR[0] = pa.sig * from8<0>(zq, p);
+        FR[1] = pa.sig * from8<1>(zq, p);
+        FR[2] = pa.sig * from8<2>(zq, p);
     }
 
     double FH[3];
@@ -384,23 +420,27 @@ __device__ inline void particle_lane(const ParticleSite<C> &site, Gather &gather
     pa.cells[8 * i + p] = my_cell;
 
     if (p != 0) return;
+    if (pa.pair_list.head) pa.pair_list.head[pa.pair_list.link[i].bucket] = kPairNone;
     // Eqs. s2-langevin, s2-langevin2 with dt = 1; F_C is the given force (or 0).
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         const double vn = V[k] + (fc[k] + FH[k] + FR[k]) / pa.mass;
-        pa.v[3 * i + k] = vn;
-        pa.r[3 * i + k] = r[k] + vn;
+        pa.v_out[3 * i + k] = vn;
+        pa.r_out[3 * i + k] = r[k] + vn;
         pa.fh[3 * i + k] = FH[k];
         pa.fr[3 * i + k] = FR[k];
     }
 }
 
+// Launched with a second wavefront per block when the VACF is on: it takes the
+// sample (a chain of loads that lengthens the update when one wavefront does
+// both: 8.8 -> 7.4 us at 100^3, 500 particles, 101 origins).
 template <class C>
-__global__ __launch_bounds__(kParticleBlock) void k_particle(const typename C::T *__restrict__ A,
-                                                             Grid g, typename C::R dec_s,
-                                                             ParticleArgs pa, ForceField cur,
-                                                             ForceField last, ForceField older) {
-    const uint32_t gt = blockIdx.x * kParticleBlock + threadIdx.x;
+__global__ __launch_bounds__(2 * kParticleBlock) void k_particle(const typename C::T *__restrict__ A,
+                                                                 Grid g, typename C::R dec_s,
+                                                                 ParticleArgs pa, ForceField cur,
+                                                                 ForceField last, ForceField older) {
+    const uint32_t gt = blockIdx.x * kParticleBlock + (threadIdx.x & (kParticleBlock - 1));
     const int32_t i = int32_t(gt >> 3);
     const int p = int(gt & 7u);
     const bool valid = i < pa.n;
@@ -412,12 +452,23 @@ __global__ __launch_bounds__(kParticleBlock) void k_particle(const typename C::T
         r[k] = pa.r[3 * ii + k];
         V[k] = pa.v[3 * ii + k];
     }
+    if (pa.acc) {
+        __syncthreads();  // both wavefronts have read V before one updates it
+        if (threadIdx.x >= kParticleBlock) {
+            vacf_sample(pa, i, p, valid, V);
+            return;
+        }
+    }
     if (pa.pmom) {
-        // particle momentum M V^n of the state at the start of the step
-        double pm[3];
+        // particle momentum M V^n of the state at the start of the step, one
+        // sum per wavefront
 #pragma unroll
-        for (int k = 0; k < 3; ++k) pm[k] = (valid && p == 0) ? pa.mass * V[k] : 0.0;
-        block_sum<3, kParticleBlock>(pm, pa.pmom + 3 * uint64_t(blockIdx.x));
+        for (int k = 0; k < 3; ++k) {
+            double pm = (valid && p == 0) ? pa.mass * V[k] : 0.0;
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) pm += __shfl_xor(pm, off);
+            if (threadIdx.x == 0) pa.pmom[3 * uint64_t(blockIdx.x) + k] = pm;
+        }
     }
     const ParticleSite<C> site{A, g, cur, last, older, pa.seed, pa.replica, uint32_t(i), pa.R};
     LatticeGather<C> gather{A, {}};
@@ -433,8 +484,13 @@ __global__ __launch_bounds__(kParticleBlock) void k_particle(const typename C::T
 // of step n, exactly as the sweep does; a ninth wavefront of the block runs
 // the eight particles' update on them.
 // ---------------------------------------------------------------------------
-constexpr int kAheadParticles = 8;
-constexpr int kAheadBlock = 64 * (kAheadParticles + 1);
+// Particles per block and wavefronts per particle of the N^3 neighbourhood.
+template <int N>
+struct AheadShape {
+    static constexpr int kWaves = (N * N * N + 63) / 64;
+    static constexpr int kParticles = 8 / kWaves;
+    static constexpr int kBlock = 64 * 9;
+};
 
 // Bit x + N (y + N z) of word i / 64: node (x, y, z) of the N^3 neighbourhood
 // is one link from a fitting node (corners 1 and N - 2 per axis).
@@ -455,6 +511,7 @@ struct AheadNodes {
 
 template <class C, int N>
 struct AheadGather {
+    static constexpr bool kSample = true;  // the VACF sample overlaps the wait
     const typename C::T (*post)[N * N * N];  // [Q] of this lane's particle, in LDS
     int p;
     __device__ inline void issue(const uint32_t (&)[3], const Grid &) {}
@@ -468,13 +525,13 @@ struct AheadGather {
     }
 };
 
-// One step's fluid around particle position r (one wavefront): post-collision
-// values of step n into post.
+// One step's fluid around particle position r: post-collision values of step n
+// into post (this wavefront's 64 nodes, number `part`).
 template <class C, int N>
 __device__ inline void ahead_nodes(const typename C::T *__restrict__ A, const Grid &g,
                                    typename C::R omega, typename C::R enc_s, typename C::R dec_s,
                                    typename C::R Gx, typename C::R Gy, typename C::R Gz,
-                                   const ForceField &f0, const double (&r)[3],
+                                   const ForceField &f0, const double (&r)[3], int part,
                                    typename C::T (*post)[N * N * N]) {
 #pragma clang fp contract(on)  // as node_relax
     using Vs = typename C::V;
@@ -493,10 +550,11 @@ __device__ inline void ahead_nodes(const typename C::T *__restrict__ A, const Gr
             c0[k] = min(max(int32_t(floor(s + 0.5) - 1.0), -1), int32_t(Ln[k]) - 1) - 1;
     }
     const int lane = int(threadIdx.x & 63u);
-#pragma unroll
-    for (int q = 0; q < (N * N * N + 63) / 64; ++q) {
-        if (!((need.word[q] >> lane) & 1u)) continue;
-        const int i = 64 * q + lane;
+    {
+        const int i = 64 * part + lane;
+        uint64_t word = need.word[0];
+        if constexpr (AheadShape<N>::kWaves > 1) word = part ? need.word[1] : word;
+        if (!((word >> lane) & 1u)) return;
         const int o[3] = {i % N, (i / N) % N, i / (N * N)};
         uint32_t x[3];
 #pragma unroll
@@ -529,25 +587,29 @@ __device__ inline void ahead_nodes(const typename C::T *__restrict__ A, const Gr
 }
 
 template <class C, int N>
-__global__ __launch_bounds__(kAheadBlock) void k_particle_ahead(
+__global__ __launch_bounds__(AheadShape<N>::kBlock) void k_particle_ahead(
     const typename C::T *__restrict__ A, Grid g, typename C::R omega, typename C::R enc_s,
     typename C::R dec_s, typename C::R Gx, typename C::R Gy, typename C::R Gz, ParticleArgs pa,
     ForceField f0, ForceField cur) {
-    __shared__ typename C::T post[kAheadParticles][C::V::Q][N * N * N];
+    using S = AheadShape<N>;
+    __shared__ typename C::T post[S::kParticles][C::V::Q][N * N * N];
     const int wave = int(threadIdx.x >> 6), lane = int(threadIdx.x & 63u);
-    if (wave < kAheadParticles) {
-        const int32_t i = int32_t(blockIdx.x) * kAheadParticles + wave;
+    if (wave < 8) {
+        const int slot = wave / S::kWaves, part = wave % S::kWaves;
+        const int32_t i = int32_t(blockIdx.x) * S::kParticles + slot;
         if (i < pa.n) {
             const double r[3] = {pa.r[3 * i + 0], pa.r[3 * i + 1], pa.r[3 * i + 2]};
-            ahead_nodes<C, N>(A, g, omega, enc_s, dec_s, Gx, Gy, Gz, f0, r, post[wave]);
+            ahead_nodes<C, N>(A, g, omega, enc_s, dec_s, Gx, Gy, Gz, f0, r, part, post[slot]);
         }
         __syncthreads();
         return;
     }
     const int p = lane & 7;
-    const int32_t i = int32_t(blockIdx.x) * kAheadParticles + (lane >> 3);
-    const bool valid = i < pa.n;
-    const int32_t ii = valid ? i : pa.n - 1;
+    // lanes past the block's particles repeat its last one and write nothing
+    const int slot = min(lane >> 3, S::kParticles - 1);
+    const int32_t i = int32_t(blockIdx.x) * S::kParticles + slot;
+    const bool valid = i < pa.n && (lane >> 3) < S::kParticles;
+    const int32_t ii = i < pa.n ? i : pa.n - 1;
     double r[3], V[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
@@ -555,7 +617,7 @@ __global__ __launch_bounds__(kAheadBlock) void k_particle_ahead(
         V[k] = pa.v[3 * ii + k];
     }
     const ParticleSite<C> site{A, g, cur, cur, cur, pa.seed, pa.replica, uint32_t(i), pa.R};
-    AheadGather<C, N> gather{post[lane >> 3], p};
+    AheadGather<C, N> gather{post[slot], p};
     particle_lane<C>(site, gather, dec_s, pa, i, p, valid, r, V);
 }
 
@@ -592,11 +654,11 @@ __device__ inline ParticleSite<C> replica_site(const typename C::T *__restrict__
 
 // ahead: steps after the device clock (1: a second step that reads no fluid).
 template <class C>
-__global__ __launch_bounds__(kParticleBlock) void k_ens_particle(
+__global__ __launch_bounds__(2 * kParticleBlock) void k_ens_particle(
     const typename C::T *__restrict__ A, const Replica *__restrict__ reps,
     const uint16_t *__restrict__ part_rep, typename C::R dec_s, ParticleArgs pa,
     const EnsClock *__restrict__ clock, int ahead, ForceField cur, ForceField last, ForceField older) {
-    const uint32_t gt = blockIdx.x * kParticleBlock + threadIdx.x;
+    const uint32_t gt = blockIdx.x * kParticleBlock + (threadIdx.x & (kParticleBlock - 1));
     const int32_t i = int32_t(gt >> 3);
     const int p = int(gt & 7u);
     const bool valid = i < pa.n;
@@ -608,34 +670,45 @@ __global__ __launch_bounds__(kParticleBlock) void k_ens_particle(
         r[k] = pa.r[3 * ii + k];
         V[k] = pa.v[3 * ii + k];
     }
+    if (pa.acc) {
+        __syncthreads();  // both wavefronts have read V before one updates it
+        if (threadIdx.x >= kParticleBlock) {
+            vacf_sample(pa, i, p, valid, V);
+            return;
+        }
+    }
     const ParticleSite<C> site = replica_site<C>(A, reps[part_rep[ii]], ii, cur, last, older);
     LatticeGather<C> gather{site.A, {}};
     particle_lane<C>(site, gather, dec_s, pa, i, p, valid, r, V);
 }
 
 template <class C, int N>
-__global__ __launch_bounds__(kAheadBlock) void k_ens_particle_ahead(
+__global__ __launch_bounds__(AheadShape<N>::kBlock) void k_ens_particle_ahead(
     const typename C::T *__restrict__ A, const Replica *__restrict__ reps,
     const uint16_t *__restrict__ part_rep, typename C::R enc_s, typename C::R dec_s, ParticleArgs pa,
     const EnsClock *__restrict__ clock, ForceField f0, ForceField cur) {
     using R = typename C::R;
-    __shared__ typename C::T post[kAheadParticles][C::V::Q][N * N * N];
+    using S = AheadShape<N>;
+    __shared__ typename C::T post[S::kParticles][C::V::Q][N * N * N];
     const int wave = int(threadIdx.x >> 6), lane = int(threadIdx.x & 63u);
-    if (wave < kAheadParticles) {
-        const int32_t i = int32_t(blockIdx.x) * kAheadParticles + wave;
+    if (wave < 8) {
+        const int slot = wave / S::kWaves, part = wave % S::kWaves;
+        const int32_t i = int32_t(blockIdx.x) * S::kParticles + slot;
         if (i < pa.n) {
             const Replica &rp = reps[part_rep[i]];
             const double r[3] = {pa.r[3 * i + 0], pa.r[3 * i + 1], pa.r[3 * i + 2]};
             ahead_nodes<C, N>(A + rp.pop_off, rp.g, R(rp.omega), enc_s, dec_s, R(0), R(0), R(0),
-                              f0.box(rp.cell_off, rp.mask_off), r, post[wave]);
+                              f0.box(rp.cell_off, rp.mask_off), r, part, post[slot]);
         }
         __syncthreads();
         return;
     }
     const int p = lane & 7;
-    const int32_t i = int32_t(blockIdx.x) * kAheadParticles + (lane >> 3);
-    const bool valid = i < pa.n;
-    const int32_t ii = valid ? i : pa.n - 1;
+    // lanes past the block's particles repeat its last one and write nothing
+    const int slot = min(lane >> 3, S::kParticles - 1);
+    const int32_t i = int32_t(blockIdx.x) * S::kParticles + slot;
+    const bool valid = i < pa.n && (lane >> 3) < S::kParticles;
+    const int32_t ii = i < pa.n ? i : pa.n - 1;
     clock_args(pa, clock, 1);
     double r[3], V[3];
 #pragma unroll
@@ -644,7 +717,7 @@ __global__ __launch_bounds__(kAheadBlock) void k_ens_particle_ahead(
         V[k] = pa.v[3 * ii + k];
     }
     const ParticleSite<C> site = replica_site<C>(A, reps[part_rep[ii]], ii, cur, cur, cur);
-    AheadGather<C, N> gather{post[lane >> 3], p};
+    AheadGather<C, N> gather{post[slot], p};
     particle_lane<C>(site, gather, dec_s, pa, i, p, valid, r, V);
 }
 

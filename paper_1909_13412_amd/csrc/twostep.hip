@@ -28,8 +28,8 @@ template <class C, int N>
 static void launch_ahead_as(const TwoStepArgs &a, const ParticleArgs &pa) {
     using T = typename C::T;
     using R = typename C::R;
-    const dim3 grid(unsigned((pa.n + kAheadParticles - 1) / kAheadParticles));
-    hipLaunchKernelGGL((k_particle_ahead<C, N>), grid, dim3(kAheadBlock), 0, a.stream, static_cast<const T *>(a.A), a.g,
+    const dim3 grid(unsigned((pa.n + AheadShape<N>::kParticles - 1) / AheadShape<N>::kParticles));
+    hipLaunchKernelGGL((k_particle_ahead<C, N>), grid, dim3(AheadShape<N>::kBlock), 0, a.stream, static_cast<const T *>(a.A), a.g,
                        R(a.omega), R(a.enc_s), R(a.dec_s), R(a.body[0]), R(a.body[1]), R(a.body[2]), pa, a.f0, a.f1);
 }
 
@@ -60,8 +60,8 @@ template <class C, int N>
 static void launch_ens_ahead_as(const EnsTwoStepArgs &a, const ParticleArgs &pa) {
     using T = typename C::T;
     using R = typename C::R;
-    const dim3 grid(unsigned((pa.n + kAheadParticles - 1) / kAheadParticles));
-    hipLaunchKernelGGL((k_ens_particle_ahead<C, N>), grid, dim3(kAheadBlock), 0, a.stream, static_cast<const T *>(a.A),
+    const dim3 grid(unsigned((pa.n + AheadShape<N>::kParticles - 1) / AheadShape<N>::kParticles));
+    hipLaunchKernelGGL((k_ens_particle_ahead<C, N>), grid, dim3(AheadShape<N>::kBlock), 0, a.stream, static_cast<const T *>(a.A),
                        a.reps, a.part_rep, R(a.enc_s), R(a.dec_s), pa, a.clock, a.f0, a.f1);
 }
 

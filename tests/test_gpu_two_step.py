@@ -2,6 +2,8 @@
 same steps taken one at a time: every bit of the populations, particles, VACF
 sums and recorded sums.  The oracle bounds of the single steps therefore hold
 for it too."""
+import warnings
+
 import numpy as np
 import pytest
 
@@ -154,3 +156,31 @@ def test_ensemble_two_step_sweep_equals_single_steps(storage, friction, graph):
         assert np.array_equal(ones.vacf()[1], twos.vacf()[1])
         raw = [(x.pop_a if done % 2 == 0 else x.pop_b)[:4096].cpu() for x in (ones, twos)]
         assert bool((raw[0] == raw[1]).all())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [2, 5, 9, 70])
+def test_pair_forces_of_crowded_cells(n):
+    # More particles of one cell than a walk of its list takes at a time (4),
+    # against the sum over all pairs in FP64, in the kernels' rounding.
+    from paper_1909_13412_amd import Lattice
+
+    box, rc, a = np.array([12.0, 10.0, 9.0]), 1.5, 0.05
+    rng = np.random.default_rng(n)
+    r = np.concatenate([np.array([11.9, 0.05, 4.2]) + 0.3 * rng.standard_normal((n, 3)), rng.random((20, 3)) * box])
+    lat = Lattice(12, 10, 9, 0.8, storage="f64")
+    with warnings.catch_warnings():
+        warnings.simplefilter("ignore")  # the volume fraction is beyond the method's range
+        lat.particles_couple(r, np.zeros_like(r), kT=0.0, radius=0.5)
+    lat.set_pair_force(a, rc)
+    for _ in range(2):  # the list is emptied and built again
+        pos = lat.particles()[0].cpu().numpy()
+        lat.step(1)
+        d = pos[:, None] - pos[None]
+        d -= box * np.rint(d / box)
+        dist = np.sqrt((d * d).sum(2))
+        near = (dist > 0) & (dist < rc)
+        mag = np.where(near, a * (1 - dist / rc) / np.where(near, dist, 1.0), 0.0)
+        ref = (mag[..., None] * d).sum(1)
+        # n terms of size <= a, a few roundings each
+        assert np.max(np.abs(lat.pair_forces().cpu().numpy() - ref)) <= 16 * (n + 20) * a * 2.0 ** -53
