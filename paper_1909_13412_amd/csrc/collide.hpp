@@ -306,7 +306,7 @@ __device__ inline void node_relax(const typename C::R (&gv)[C::V::Q], const Node
     const R ux = m.ux, uy = m.uy, uz = m.uz;
     const R uu = ux * ux + uy * uy + uz * uz;
     const R base = m.drho - R(1.5) * uu;
-    put(0, gv[0] + omega * (V::template w<R>(0) * base - gv[0]));
+    put(std::integral_constant<int, 0>{}, gv[0] + omega * (V::template w<R>(0) * base - gv[0]));
     static_for<0, (V::Q - 1) / 2>([&](auto pc) {
         constexpr int a = 1 + 2 * decltype(pc)::value;
         constexpr int cx = V::ex[a], cy = V::ey[a], cz = V::ez[a];
@@ -325,11 +325,11 @@ __device__ inline void node_relax(const typename C::R (&gv)[C::V::Q], const Node
         const R anti = w3 * eu;
         if constexpr (FORCE) {
             const R fa = w3 * eF;
-            put(a, gv[a] + omega * ((sym + anti) - gv[a]) + fa);
-            put(a + 1, gv[a + 1] + omega * ((sym - anti) - gv[a + 1]) - fa);
+            put(std::integral_constant<int, a>{}, gv[a] + omega * ((sym + anti) - gv[a]) + fa);
+            put(std::integral_constant<int, a + 1>{}, gv[a + 1] + omega * ((sym - anti) - gv[a + 1]) - fa);
         } else {
-            put(a, gv[a] + omega * ((sym + anti) - gv[a]));
-            put(a + 1, gv[a + 1] + omega * ((sym - anti) - gv[a + 1]));
+            put(std::integral_constant<int, a>{}, gv[a] + omega * ((sym + anti) - gv[a]));
+            put(std::integral_constant<int, a + 1>{}, gv[a + 1] + omega * ((sym - anti) - gv[a + 1]));
         }
     });
 }

@@ -1117,13 +1117,15 @@ lbm_status set_layout(lbm_ctx *c, uint32_t Y) {
 // ---- two-step sweep: tiles and when it is used ----
 
 // Tiles of the two-step sweep for a box, best first by a cost model: a block
-// takes lz + 2 planes, a plane costs a fixed part (its barrier and the latency
-// it exposes) plus the wavefronts' arithmetic and the 128-byte lines its row
-// pieces touch; blocks run one per compute unit (the LDS and registers of a
-// block this size allow no second one), so whole rounds of 256 count.
-// Fitted to probe timings (FP32, us per plane: 128 x 4 tiles 3.7, 64 x 8 3.9,
-// 64 x 10 4.3, 96 x 6 3.95).
-constexpr int kTwoStepCandidates = 4;
+// takes lz planes and a start of some four more, a plane costs a fixed part
+// (its barrier and the latency it exposes) plus the wavefronts' arithmetic and
+// the 128-byte lines its row pieces touch; blocks run one per compute unit (the
+// LDS and registers of a block this size allow no second one), so whole rounds
+// of 256 count.  Fitted to probe timings (FP32, us per plane: 128 x 4 tiles
+// 3.7, 64 x 8 3.9, 64 x 10 4.3, 96 x 6 3.95; 256^3 in slabs of 128 and 64
+// planes: FP32 0.484 and 0.513 ms, BF16 0.317 and 0.328).  lbm_autotune times
+// the first six.
+constexpr int kTwoStepCandidates = 6;
 
 double two_step_plane_cost(uint32_t tx, uint32_t ty, size_t elem) {
     const double lines = (ty + 2) * ((tx + 2) * double(elem) / 128.0 + 1.5);
@@ -1132,6 +1134,7 @@ double two_step_plane_cost(uint32_t tx, uint32_t ty, size_t elem) {
 }
 
 constexpr uint32_t kTwoStepUnits = 256;
+constexpr double kTwoStepStart = 4.0;
 
 // Calls fn(tx, ty, ntx, nty) for every even split of an nx x ny plane into tiles
 // that fit a block (rows of 16 nodes at least, unless nx is shorter).
@@ -1169,7 +1172,7 @@ int two_step_candidates(const lbm_grid_desc *g, TwoStepTiles *out) {
         for (uint64_t r = r0; r < r0 + 8; ++r) {  // rounds of blocks
             const uint32_t ns = uint32_t(std::min<uint64_t>(nz, r * kTwoStepUnits / tiles));
             const uint32_t lz = (nz + ns - 1) / ns;
-            const double cost = double(r) * (lz + 2.0) * plane;
+            const double cost = double(r) * (lz + kTwoStepStart) * plane;
             if (best.cost < 0.0 || cost < best.cost) best = Cand{{tx, ty, lz, ntx, nty, (nz + lz - 1) / lz}, cost};
         }
         all.push_back(best);

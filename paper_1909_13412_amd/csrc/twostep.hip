@@ -9,19 +9,21 @@ template <class C, bool FORCED, bool NTS>
 static void launch_two_steps_as(const TwoStepArgs &a) {
     using T = typename C::T;
     using R = typename C::R;
-    using S = TwoStepShape<T>;
     const dim3 grid(a.tl.ntx * a.tl.nty * a.tl.nslab), block(two_step_threads(a.tl));
-    hipLaunchKernelGGL((k_two_steps<C, FORCED, NTS, S::kNodes, S::kBuffers, S::kEarly>), grid, block, 0, a.stream,
+    hipLaunchKernelGGL((k_two_steps<C, FORCED, NTS>), grid, block, 0, a.stream,
                        static_cast<const T *>(a.A), static_cast<T *>(a.B), a.g, R(a.omega), R(a.enc_s), R(a.dec_s),
                        a.f0, a.f1, R(a.body[0]), R(a.body[1]), R(a.body[2]), a.tl, kOrderXcdSlabs);
 }
 
 template <class C>
 void launch_two_steps(const TwoStepArgs &a) {
-    if (a.forced)
-        a.nts ? launch_two_steps_as<C, true, true>(a) : launch_two_steps_as<C, true, false>(a);
-    else
-        a.nts ? launch_two_steps_as<C, false, true>(a) : launch_two_steps_as<C, false, false>(a);
+    // FP64 reads the (empty) forcing flags of a box without particles too: the
+    // kernel without them needs scratch memory (192^3, ms per sweep: 0.568
+    // against 0.449)
+    if constexpr (sizeof(typename C::T) < 8)
+        if (!a.forced)
+            return a.nts ? launch_two_steps_as<C, false, true>(a) : launch_two_steps_as<C, false, false>(a);
+    a.nts ? launch_two_steps_as<C, true, true>(a) : launch_two_steps_as<C, true, false>(a);
 }
 
 template <class C, int N>
@@ -45,8 +47,7 @@ template <class C, bool NTS>
 static void launch_ens_two_steps_as(const EnsTwoStepArgs &a) {
     using T = typename C::T;
     using R = typename C::R;
-    using S = TwoStepShape<T>;
-    hipLaunchKernelGGL((k_ens_two_steps<C, NTS, S::kNodes, S::kBuffers, S::kEarly>), dim3(a.blocks), dim3(a.threads), 0,
+    hipLaunchKernelGGL((k_ens_two_steps<C, NTS>), dim3(a.blocks), dim3(a.threads), 0,
                        a.stream, static_cast<const T *>(a.A), static_cast<T *>(a.B), a.reps, a.blk_rep, a.f0, a.f1,
                        R(a.enc_s), R(a.dec_s), a.clock, a.vacf_on);
 }

@@ -13,14 +13,27 @@
 
 namespace lbmbp {
 
-// Nodes of a padded tile (lanes of a block and LDS nodes) at most, LDS buffers,
-// and whether the loads of the next plane go out before the first step's
-// arithmetic.
+// How a storage's sweep is built.  A block is one lane per node of the padded
+// tile and one block fills a compute unit: 13 wavefronts leave 128 registers
+// each, FP64 takes 11 for its 168, and the post-collision planes take 126 KB of
+// LDS in FP32.
+//   kBuffers: LDS planes; two need one barrier per plane, one needs two (FP64,
+//     where two planes would not fit);
+//   kPlanes: planes of populations in flight in registers, loaded that many
+//     ahead; 0 loads the next one between the two steps (FP64, for the
+//     registers).  A second plane pays where a plane is short (16-bit, 64 x 8
+//     tiles at 256^3: 0.324 -> 0.310 ms per sweep) and not where HBM is the
+//     limit (FP32 0.484 -> 0.489);
+//   kFront: loads sent off before the first step's arithmetic; the rest go one
+//     at a time between the relaxed pairs.  All at once they fill the address
+//     queue and every wavefront of the block stalls (BF16 0.382 -> 0.324 ms,
+//     FP32 0.518 -> 0.484).
 template <class T>
 struct TwoStepShape {
     static constexpr int kNodes = sizeof(T) == 8 ? 704 : 832;
     static constexpr int kBuffers = sizeof(T) == 8 ? 1 : 2;
-    static constexpr bool kEarly = sizeof(T) != 8;
+    static constexpr int kPlanes = sizeof(T) == 8 ? 0 : (sizeof(T) == 4 ? 1 : 2);
+    static constexpr int kFront = sizeof(T) == 2 ? 10 : 6;
 };
 constexpr uint32_t two_step_nodes(size_t elem) {
     return elem == 8 ? TwoStepShape<double>::kNodes : TwoStepShape<float>::kNodes;
@@ -44,17 +57,19 @@ __device__ inline uint16_t held_copy(uint16_t v) { return v; }  // decoding move
 __device__ inline double held_copy(double v) { return v; }
 
 // One block: the nodes [x0, x0 + w) x [y0, y0 + h) x [z0, z0 + d).
-template <class C, bool FORCED, bool NTS, int NMAX, int BUF, bool EARLY>
+template <class C, bool FORCED, bool NTS>
 __device__ inline void two_steps_block(const typename C::T *__restrict__ A, typename C::T *__restrict__ B,
                                        const Grid &g, typename C::R omega, typename C::R enc_s,
                                        typename C::R dec_s, const ForceField &f0, const ForceField &f1,
                                        typename C::R Gx, typename C::R Gy, typename C::R Gz, uint32_t x0,
                                        uint32_t y0, uint32_t z0, uint32_t w, uint32_t h, uint32_t d,
-                                       typename C::T (&post)[BUF][C::V::Q][NMAX]) {
+                                       typename C::T (&post)[TwoStepShape<typename C::T>::kBuffers][C::V::Q][TwoStepShape<typename C::T>::kNodes]) {
 #pragma clang fp contract(on)  // as node_relax
     using T = typename C::T;
     using R = typename C::R;
     using V = typename C::V;
+    using S = TwoStepShape<T>;
+    constexpr int D = S::kPlanes > 1 ? S::kPlanes : 1;  // sets of load registers
     const uint32_t pw = w + 2;  // row pitch of the padded tile in LDS
 
     auto up = [&](uint32_t z) { return z + 1 == g.nz ? 0u : z + 1; };
@@ -88,24 +103,29 @@ __device__ inline void two_steps_block(const typename C::T *__restrict__ A, type
     const bool second = __builtin_amdgcn_readfirstlane(threadIdx.x) < w * h;  // wavefront-uniform
     const uint32_t from[3] = {(jy + 2) * pw + jx + 1, (jy + 1) * pw + jx + 1, jy * pw + jx + 1};  // rows y - e_y
 
-    // raw populations and flag words of the first step at plane zp, the flag
-    // word of the second step at the plane below
-    T raw[V::Q];
-    uint32_t word1 = 0, word2 = 0;
-    auto load = [&](uint32_t zp) {
+    // raw populations and flag words of the first step at a plane, the flag
+    // word of the second step at the plane below; set i of D
+    T raw[D][V::Q];
+    uint32_t word1[D] = {}, word2[D] = {};
+    const char *src[3];  // planes zp + 1, zp, zp - 1 of the plane being loaded
+    auto load_from = [&](uint32_t zp, auto ic) {
+        constexpr int i = decltype(ic)::value;
         const uint32_t zs[3] = {up(zp), zp, down(zp)};
-        static_for<0, V::Q>([&](auto ac) {
-            constexpr int a = decltype(ac)::value;
-            const char *base = reinterpret_cast<const char *>(A) +
-                               (uint64_t(zs[V::ez[a] + 1]) * plane + uint64_t(uint32_t(a) * popb));
-            uint32_t off = yo[V::ey[a] + 1] + xo[V::ex[a] + 1];
-            asm("" : "+v"(off));
-            raw[a] = *reinterpret_cast<const T *>(base + off);
-        });
+        for (int k = 0; k < 3; ++k) src[k] = reinterpret_cast<const char *>(A) + uint64_t(zs[k]) * plane;
         if constexpr (FORCED) {
-            word1 = f0.mask[(zp * nxy + cell1) >> 5];
-            word2 = f1.mask[(zs[2] * nxy + cell2) >> 5];
+            word1[i] = f0.mask[(zp * nxy + cell1) >> 5];
+            word2[i] = f1.mask[(zs[2] * nxy + cell2) >> 5];
         }
+    };
+    auto load_pop = [&](auto ac, auto ic) {
+        constexpr int a = decltype(ac)::value, i = decltype(ic)::value;
+        uint32_t off = yo[V::ey[a] + 1] + xo[V::ex[a] + 1];
+        asm("" : "+v"(off));  // a lane offset to a scalar base, not a 64-bit lane address
+        raw[i][a] = *reinterpret_cast<const T *>(src[V::ez[a] + 1] + uint64_t(uint32_t(a) * popb) + off);
+    };
+    auto load = [&](uint32_t zp, auto ic) {
+        load_from(zp, ic);
+        static_for<0, V::Q>([&](auto ac) { load_pop(ac, ic); });
     };
     const bool body = Gx != R(0) || Gy != R(0) || Gz != R(0);
     // relaxation at a node of linear index cell with flag bit `flag`
@@ -127,24 +147,36 @@ __device__ inline void two_steps_block(const typename C::T *__restrict__ A, type
     };
     uint32_t zp = down(z0);  // plane of the first step
     uint32_t b = 0;          // LDS buffer it writes
-    // first step at plane zp; w2: the flag word of the second step below it
-    auto first_step = [&](uint32_t &w2) {
+    // first step at plane zp, held in set i; w2: the flag word of the second
+    // step below it
+    auto first_step = [&](uint32_t &w2, auto ic) {
+        constexpr int i = decltype(ic)::value;
         R gv[V::Q];
         static_for<0, V::Q>([&](auto ac) {
             constexpr int a = decltype(ac)::value;
-            gv[a] = C::dec(EARLY ? held_copy(raw[a]) : raw[a], dec_s);
+            gv[a] = C::dec(S::kPlanes > 0 ? held_copy(raw[i][a]) : raw[i][a], dec_s);
         });
-        const uint32_t w1 = held_copy(word1);
-        w2 = held_copy(word2);
-        if constexpr (EARLY) load(up(zp));
+        const uint32_t w1 = held_copy(word1[i]);
+        w2 = held_copy(word2[i]);
         const uint32_t cell = zp * nxy + cell1;
-        relax(gv, (w1 >> (cell & 31)) & 1u, cell, f0, [&](int a, R gn) { post[b][a][lds1] = C::enc(gn, enc_s); });
+        if constexpr (S::kPlanes > 0) {
+            load_from(S::kPlanes > 1 ? up(up(zp)) : up(zp), ic);
+            static_for<0, S::kFront>([&](auto ac) { load_pop(ac, ic); });
+        }
+        relax(gv, (w1 >> (cell & 31)) & 1u, cell, f0, [&](auto ac, R gn) {
+            constexpr int a = decltype(ac)::value;
+            post[b][a][lds1] = C::enc(gn, enc_s);
+            if constexpr (S::kPlanes > 0 && a >= S::kFront) {
+                load_pop(ac, ic);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        });
         __syncthreads();
         zp = up(zp);
-        if constexpr (!EARLY) load(zp);
+        if constexpr (S::kPlanes == 0) load(zp, ic);
     };
     auto flip = [&]() {
-        if constexpr (BUF == 2)
+        if constexpr (S::kBuffers == 2)
             b ^= 1;
         else
             __syncthreads();
@@ -168,48 +200,70 @@ __device__ inline void two_steps_block(const typename C::T *__restrict__ A, type
         });
     };
 
-    load(zp);
-    for (uint32_t k = 0; k < 2; ++k) {
+    using Set0 = std::integral_constant<int, 0>;
+    using Set1 = std::integral_constant<int, D - 1>;
+    load(zp, Set0{});
+    if constexpr (D == 2) load(up(zp), Set1{});
+    // the planes below and at z0
+    auto start = [&](auto ic) {
         uint32_t w2;
-        first_step(w2);
+        first_step(w2, ic);
         if (second) shift();
         flip();
-    }
+    };
+    start(Set0{});
+    start(Set1{});
     __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): the loop's waits then count its own accesses only
-    if (second) {
-        for (uint32_t k = 0; k < d; ++k) {
-            uint32_t w2;
-            first_step(w2);
-            const uint32_t zt = down(down(zp));
-            R gv[V::Q];
-            static_for<0, V::Q>([&](auto ac) {
-                constexpr int a = decltype(ac)::value;
-                if constexpr (V::ez[a] < 0)
-                    gv[a] = C::dec(pulled(ac), dec_s);
-                else
-                    gv[a] = C::dec(pend[a], dec_s);
-            });
-            shift();
-            const uint32_t cell = zt * nxy + cell2;
-            char *row = reinterpret_cast<char *>(B) + uint64_t(zt) * plane;
-            relax(gv, (w2 >> (cell & 31)) & 1u, cell, f1, [&](int a, R gn) {
-                uint32_t off = own;
-                asm("" : "+v"(off));
-                T *p = reinterpret_cast<T *>(row + uint64_t(uint32_t(a) * popb) + off);
-                if constexpr (NTS)
-                    __builtin_nontemporal_store(C::enc(gn, enc_s), p);
-                else
-                    *p = C::enc(gn, enc_s);
-            });
-            flip();
+    // first step one plane above the second step's
+    auto both = [&](auto ic) {
+        uint32_t w2;
+        first_step(w2, ic);
+        const uint32_t zt = down(down(zp));
+        R gv[V::Q];
+        static_for<0, V::Q>([&](auto ac) {
+            constexpr int a = decltype(ac)::value;
+            if constexpr (V::ez[a] < 0)
+                gv[a] = C::dec(pulled(ac), dec_s);
+            else
+                gv[a] = C::dec(pend[a], dec_s);
+        });
+        shift();
+        const uint32_t cell = zt * nxy + cell2;
+        char *row = reinterpret_cast<char *>(B) + uint64_t(zt) * plane;
+        relax(gv, (w2 >> (cell & 31)) & 1u, cell, f1, [&](auto ac, R gn) {
+            constexpr int a = decltype(ac)::value;
+            uint32_t off = own;
+            asm("" : "+v"(off));
+            T *p = reinterpret_cast<T *>(row + uint64_t(uint32_t(a) * popb) + off);
+            if constexpr (NTS)
+                __builtin_nontemporal_store(C::enc(gn, enc_s), p);
+            else
+                *p = C::enc(gn, enc_s);
+        });
+        flip();
+    };
+    // a wavefront past the tile's nodes has the first step only
+    auto first_only = [&](auto ic) {
+        uint32_t w2;
+        first_step(w2, ic);
+        flip();
+    };
+    // d planes, the D register sets in turn; each kind of wavefront has a loop
+    // of its own, so that its waits know the stores in flight behind the loads
+    auto march = [&](auto &&plane_of) {
+        for (uint32_t left = d;;) {
+            plane_of(Set0{});
+            if (--left == 0) break;
+            if constexpr (D == 2) {
+                plane_of(Set1{});
+                if (--left == 0) break;
+            }
         }
-    } else {
-        for (uint32_t k = 0; k < d; ++k) {
-            uint32_t w2;
-            first_step(w2);
-            flip();
-        }
-    }
+    };
+    if (second)
+        march(both);
+    else
+        march(first_only);
 }
 
 // Block b of a box's sweep: tiles in x, then y, then slabs of planes.
@@ -228,26 +282,25 @@ struct TwoStepBlock {
     }
 };
 
-template <class C, bool FORCED, bool NTS, int NMAX, int BUF, bool EARLY>
-__global__ __launch_bounds__(NMAX) void k_two_steps(
+template <class C, bool FORCED, bool NTS>
+__global__ __launch_bounds__(TwoStepShape<typename C::T>::kNodes) void k_two_steps(
     const typename C::T *__restrict__ A, typename C::T *__restrict__ B, Grid g, typename C::R omega,
     typename C::R enc_s, typename C::R dec_s, ForceField f0, ForceField f1, typename C::R Gx,
     typename C::R Gy, typename C::R Gz, TwoStepTiles tl, uint32_t order) {
-    __shared__ typename C::T post[BUF][C::V::Q][NMAX];
+    __shared__ typename C::T post[TwoStepShape<typename C::T>::kBuffers][C::V::Q][TwoStepShape<typename C::T>::kNodes];
     const TwoStepBlock t(tl, g, sweep_block(order));
-    two_steps_block<C, FORCED, NTS, NMAX, BUF, EARLY>(A, B, g, omega, enc_s, dec_s, f0, f1, Gx, Gy, Gz, t.x0, t.y0,
-                                                      t.z0, t.w, t.h, t.d, post);
+    two_steps_block<C, FORCED, NTS>(A, B, g, omega, enc_s, dec_s, f0, f1, Gx, Gy, Gz, t.x0, t.y0, t.z0, t.w, t.h, t.d, post);
 }
 
 // Every box of an ensemble (block -> box table); advances the device clock by
 // the two steps.
-template <class C, bool NTS, int NMAX, int BUF, bool EARLY>
-__global__ __launch_bounds__(NMAX) void k_ens_two_steps(
+template <class C, bool NTS>
+__global__ __launch_bounds__(TwoStepShape<typename C::T>::kNodes) void k_ens_two_steps(
     const typename C::T *__restrict__ A, typename C::T *__restrict__ B, const Replica *__restrict__ reps,
     const uint16_t *__restrict__ blk_rep, ForceField f0, ForceField f1, typename C::R enc_s,
     typename C::R dec_s, EnsClock *clock, int vacf_on) {
     using R = typename C::R;
-    __shared__ typename C::T post[BUF][C::V::Q][NMAX];
+    __shared__ typename C::T post[TwoStepShape<typename C::T>::kBuffers][C::V::Q][TwoStepShape<typename C::T>::kNodes];
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         // the steps' last reader of the clock has finished (previous kernel)
         clock->step += 2;
@@ -256,9 +309,9 @@ __global__ __launch_bounds__(NMAX) void k_ens_two_steps(
     const Replica &rp = reps[blk_rep[blockIdx.x]];
     const Grid g = rp.g;
     const TwoStepBlock t(rp.two, g, blockIdx.x - rp.first_two);
-    two_steps_block<C, true, NTS, NMAX, BUF, EARLY>(A + rp.pop_off, B + rp.pop_off, g, R(rp.omega), enc_s, dec_s,
-                                                    f0.box(rp.cell_off, rp.mask_off), f1.box(rp.cell_off, rp.mask_off),
-                                                    R(0), R(0), R(0), t.x0, t.y0, t.z0, t.w, t.h, t.d, post);
+    two_steps_block<C, true, NTS>(A + rp.pop_off, B + rp.pop_off, g, R(rp.omega), enc_s, dec_s,
+                                  f0.box(rp.cell_off, rp.mask_off), f1.box(rp.cell_off, rp.mask_off),
+                                  R(0), R(0), R(0), t.x0, t.y0, t.z0, t.w, t.h, t.d, post);
 }
 
 }  // namespace lbmbp

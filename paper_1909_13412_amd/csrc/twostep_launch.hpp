@@ -18,8 +18,8 @@ struct TwoStepArgs {
     double omega, enc_s, dec_s, body[3];
     ForceField f0, f1;  // node forces of the first and the second step
     TwoStepTiles tl;
-    bool forced;        // particles attached
-    bool nts;           // non-temporal stores
+    bool forced;  // particles attached
+    bool nts;     // non-temporal stores
     hipStream_t stream;
 };
 
