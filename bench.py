@@ -10,10 +10,11 @@ lags up to 500 and origins every 10 steps; synthetic seeded initial state.
 
 Prints ONE JSON line.  `value` is whole-step MLUPS (nodes x steps / s / 1e6) with
 FP32 population storage; `variants` repeats the timing for shifted BF16 and FP16
-storage; `roofline` prices the stream-collide kernel (the dominant one) against
+storage; `roofline` prices the stream-collide sweeps (the dominant kernels) against
 the 8 TB/s HBM peak from HIP-event timings of every launch in a second timed
 region (events add a few microseconds per step, so `value` comes from a region
-without them);
+without them).  A sweep reads and writes the lattice once, whether it takes one
+step or two (`steps_per_launch` is their mean);
 `cpu_baseline` times the FP64 oracle on a few steps of the same workload.
 """
 from __future__ import annotations
@@ -159,6 +160,7 @@ def time_storage(w, variant, steps, warmup, prof_steps, pair=None, repeats=0):
         "ms_per_step": (t1 - t0) * 1e3 / steps,
         "profiled_ms_per_step": (t3 - t2) * 1e3 / prof_steps,
         "collide_ms": coll_ms,
+        "steps_per_launch": prof_steps / max(prof["collide_launches"], 1),
         "particle_phase_ms": part_ms,
         "collide_GBs": achieved,
         "collide_frac": achieved / HBM_PEAK_GBS,
@@ -550,7 +552,8 @@ def time_large(steps, warmup):
     for storage in ("f32", "bf16"):
         r = time_storage(w, storage, steps, min(warmup, 20), min(steps, 50))
         out[storage] = {"mlups": round(r["mlups"], 1), "ms_per_step": round(r["ms_per_step"], 5),
-                        "collide_ms": round(r["collide_ms"], 5), "collide_GBs": round(r["collide_GBs"], 1),
+                        "collide_ms": round(r["collide_ms"], 5), "steps_per_launch": round(r["steps_per_launch"], 3),
+                        "collide_GBs": round(r["collide_GBs"], 1),
                         "collide_frac": round(r["collide_frac"], 4), "collide_shape": r["collide_shape"],
                         "collide_order": r["collide_order"],
                         "collide_waves_per_simd_cap": r["collide_waves_per_simd_cap"],
@@ -804,7 +807,8 @@ def main():
                    "fp64_sums_every": SERIES_EVERY,
                    "parallelism": "single GPU"},
         "roofline": {
-            "kernel": "k_stream_collide",
+            "kernel": "k_two_steps, k_stream_collide",
+            "steps_per_launch": round(main_res["steps_per_launch"], 3),
             "bound": "hbm",
             "achieved": round(main_res["collide_GBs"], 1),
             "peak": HBM_PEAK_GBS,

@@ -124,7 +124,7 @@ typedef struct lbm_ctx lbm_ctx;
  * this many bytes. */
 lbm_status lbm_lattice_bytes(const lbm_grid_desc *grid, size_t *bytes);
 
-/* Bytes of grid scratch: two node-force fields (24 bytes per node each: the
+/* Bytes of grid scratch: three node-force fields (24 bytes per node each: the
  * reaction force of the first Eq. s2-force, section 2.1) with their one-bit
  * flags, reduction partials and flags. */
 lbm_status lbm_grid_scratch_bytes(const lbm_grid_desc *grid, size_t *bytes);
@@ -265,7 +265,12 @@ lbm_status lbm_vacf_counts(const lbm_ctx *ctx, int64_t *cnt);
  * equilibrium (Eqs. s2-collision, s2-eq) with the forcing term (second Eq.
  * s2-force, Eq. s2-coll) and streaming (Eq. s2-trans); and the Langevin
  * update of the particles (Eqs. s2-langevin, s2-langevin2, dt = 1), with the
- * VACF sample of V^n when configured.  LBM_E_INVAL for nsteps < 0;
+ * VACF sample of V^n when configured.  Where it is faster (large enough boxes
+ * with few enough particles per node, or the choice of lbm_autotune) and
+ * neither step is recorded by lbm_series_config, two consecutive steps of one
+ * call run in one sweep over the lattice, with the same bits as single steps;
+ * the current state after n steps is in the lattice n swaps away as ever, the
+ * spare lattice then holds an older one.  LBM_E_INVAL for nsteps < 0;
  * LBM_E_DEVICE if a launch fails. */
 lbm_status lbm_step(lbm_ctx *ctx, int32_t nsteps);
 
@@ -313,8 +318,8 @@ lbm_status lbm_observables_noalloc(lbm_ctx *ctx, double out[7]);
 lbm_status lbm_profile_enable(lbm_ctx *ctx, int32_t enable);
 
 /* Synchronise the stream and return the accumulated timings, then reset them:
- * out[0] summed stream-collide milliseconds, out[1] stream-collide launches,
- * out[2] summed particle-phase milliseconds, out[3] particle-phase launches. */
+ * out[0] summed stream-collide milliseconds, out[1] stream-collide launches (a
+ * two-step sweep is one launch for two steps), out[2] summed particle-phase milliseconds, out[3] particle-phase launches. */
 lbm_status lbm_profile_read(lbm_ctx *ctx, double out[4]);
 
 /* Launch configurations of the stream-collide (section 2.2, Eqs. s2-coll and
@@ -343,8 +348,11 @@ lbm_status lbm_profile_read(lbm_ctx *ctx, double out[4]);
  * fastest the two fastest configurations with every block order and residency
  * cap (lbm_set_sweep_launch), and the fastest of those in every other layout;
  * finally the three fastest launches of all are timed again in turn, twice
- * each with 2 x iters launches, and the lowest total is kept.  Synchronises
- * the stream.
+ * each with 2 x iters launches, and the lowest total is kept.  Lattices below
+ * 256 MiB keep plain stores (the trials find such a lattice in the last-level
+ * cache, a run does not); the non-temporal configurations are timed for ms
+ * only.  Then up to six tilings of the two-step sweep are timed against two
+ * launches of that choice.  Synchronises the stream.
  * ms (host, LBM_NUM_SHAPES entries, may be NULL) receives per configuration
  * the best mean milliseconds per launch over the options timed with it (-1
  * for a configuration that does not apply, or that repeats another's lane
@@ -371,7 +379,7 @@ lbm_status lbm_autotune(lbm_ctx *ctx, int32_t iters, double *ms, int32_t *chosen
  * to this box; LBM_E_DEVICE if a launch fails. */
 lbm_status lbm_stream_ceiling(lbm_ctx *ctx, int32_t k, int32_t iters, double *ms);
 
-/* Use launch configuration k (0 .. LBM_NUM_SHAPES - 1) for later steps;
+/* Use launch configuration k (0 .. LBM_NUM_SHAPES - 1) for later single steps;
  * LBM_E_INVAL if k is out of range or does not apply to this box.  Every
  * configuration gives bit-identical results. */
 lbm_status lbm_set_shape(lbm_ctx *ctx, int32_t k);
@@ -521,7 +529,7 @@ lbm_status lbm_ens_init(const lbm_ensemble_desc *desc, const lbm_replica_desc *r
 
 /* 1 (default): lbm_ens_step replays a captured graph of LBM_ENS_GRAPH_STEPS
  * steps for every whole group of that many steps from an even step (captured
- * on a private stream, replayed on the context's stream), and launches the
+ * once for each even step number mod 6, on a private stream, replayed on the context's stream), and launches the
  * rest of the steps directly; plain launches throughout if capture is not
  * possible; 0: plain launches. */
 #define LBM_ENS_GRAPH_STEPS 16
@@ -533,14 +541,16 @@ lbm_status lbm_ens_vacf_config(lbm_ens *ens, int32_t max_lag, int32_t stride, do
                                double *origins);
 lbm_status lbm_ens_vacf_counts(const lbm_ens *ens, int64_t *cnt);
 
-/* Advance every replica nsteps steps (asynchronous). */
+/* Advance every replica nsteps steps (asynchronous), two per sweep where that
+ * is faster, with the bits of single steps. */
 lbm_status lbm_ens_step(lbm_ens *ens, int32_t nsteps);
 
 /* Time the stream-collide launch shapes on the ensemble in every layout
  * (lbm_ens_set_layout; state unchanged), then the block orders and
  * residency caps (lbm_ens_set_sweep_launch) of the two fastest in the best
  * layout, and keep the fastest launch in the same four stages as
- * lbm_autotune.  The choice is remembered for ensembles created later on the
+ * lbm_autotune (ensembles below 256 MiB with plain stores), and two-step
+ * sweeps if they are faster than two such launches.  The choice is remembered for ensembles created later on the
  * same device with the same storage and the same box sizes in the same
  * order, which start from it. */
 lbm_status lbm_ens_autotune(lbm_ens *ens, int32_t iters, double *ms, int32_t *chosen);

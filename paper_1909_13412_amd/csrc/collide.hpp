@@ -163,8 +163,8 @@ __device__ inline void lane_coords(const Grid &g, uint32_t lane_cell, uint32_t r
 // Node forces of one step: a dense fixed-point field, written only at the
 // (at most 8 per particle) nodes that receive a reaction force and read only
 // where the one-bit flag is set, so the stream-collide pays 1/8 byte per node.
-// Two of them alternate between steps; each is cleared node by node by the
-// particles that wrote it.
+// Three take turns (step n spreads into field n mod 3); each is cleared node by
+// node by the particles that wrote it, after the sweep that read it.
 struct ForceField {
     long long *f;    // [ncell][3] fixed-point force
     uint32_t *mask;  // one bit per node: node carries a force this step
@@ -578,8 +578,18 @@ constexpr int kRowBlock = 256;
 constexpr bool config_row(int k) { return k >= kNumFlatShapes; }
 // Lanes per block of configuration k.
 constexpr int config_block(int k) { return config_row(k) ? kRowBlock : kShapes[k & 3].bs; }
-// Lattices of at least this many bytes default to non-temporal stores.
+// Whether configuration k stores non-temporally.
+constexpr bool config_nts(int k) { return config_row(k) ? k == kNumFlatShapes + 1 : k >= kNumGeomShapes; }
+// Lattices of at least this many bytes default to non-temporal stores, and only
+// they are tuned to them: trial launches write the same lattice each time and
+// find a smaller one that they read in the last-level cache, where a run reads
+// what its last step wrote (us per step in a run, plain stores / the choice of
+// trials that include non-temporal ones: BF16 128^3 24.5 / 30.2, FP32 96^3 20.9
+// / 27.5, FP64 96^3 42.2 / 51.8, FP32 128^3, 159 MB, 52.2 / 54.5).
 constexpr size_t kStreamStoreBytes = size_t(256) << 20;
+constexpr bool config_tunable(int k, size_t lattice_bytes) {
+    return lattice_bytes >= kStreamStoreBytes || !config_nts(k);
+}
 
 // Residency caps of the sweep, in waves per SIMD (0: none, the kernel's own
 // limit).  A cap is imposed by reserving LDS the kernel never touches, so

@@ -14,6 +14,12 @@
 //                     BGK (Eqs. s2-collision, s2-eq) plus forcing (second
 //                     Eq. s2-force) where the node is flagged, write B_a(x)
 //                     (Eq. s2-coll); A and B swap.
+// Two steps n and n + 1 in one sweep, the same bits (twostep.hpp):
+//   k_particle        step n, as above
+//   k_particle_ahead  step n + 1, on post-collision values of step n that its
+//                     blocks compute around the particles
+//   k_two_steps       every node: both steps' collisions, A read and B written
+//                     once.
 //
 // Layout and the stream-collide kernel: collide.hpp.
 #include <hip/hip_runtime.h>
@@ -1117,33 +1123,44 @@ lbm_status set_layout(lbm_ctx *c, uint32_t Y) {
 // ---- two-step sweep: tiles and when it is used ----
 
 // Tiles of the two-step sweep for a box, best first by a cost model: a block
-// takes lz planes and a start of some four more, a plane costs a fixed part
-// (its barrier and the latency it exposes) plus the wavefronts' arithmetic and
-// the 128-byte lines its row pieces touch; blocks run one per compute unit (the
-// LDS and registers of a block this size allow no second one), so whole rounds
-// of 256 count.  Fitted to probe timings (FP32, us per plane: 128 x 4 tiles
-// 3.7, 64 x 8 3.9, 64 x 10 4.3, 96 x 6 3.95; 256^3 in slabs of 128 and 64
-// planes: FP32 0.484 and 0.513 ms, BF16 0.317 and 0.328).  lbm_autotune times
-// the first six.
+// takes lz planes and a start of two more; a plane costs the wavefronts of its
+// two steps on the busiest of the compute unit's four SIMDs, plus the 128-byte
+// lines that its row pieces touch; blocks run one per compute unit (the LDS and
+// registers of a block this size allow no second one), so whole rounds of 256
+// count.  The weights minimise the time of the model's first choice over 31
+// boxes of every storage, 33 to 512 nodes long, some six tiles measured in
+// each: 1.5% above the fastest tile on average, 7% at most (F16 D3Q15 201 x 150
+// x 117: 51 x 10 tiles 0.065 ms, 101 x 6 0.076).  lbm_autotune times the first
+// six.
 constexpr int kTwoStepCandidates = 6;
 
 double two_step_plane_cost(uint32_t tx, uint32_t ty, size_t elem) {
     const double lines = (ty + 2) * ((tx + 2) * double(elem) / 128.0 + 1.5);
-    const double waves = ((tx + 2) * (ty + 2) + 63) / 64 + (tx * ty + 63) / 64;
-    return 10.0 + 0.6 * lines + 0.6 * waves;
+    const uint32_t first = ((tx + 2) * (ty + 2) + 63) / 64, second = (tx * ty + 63) / 64;  // wavefronts
+    return double((first + 3) / 4 + (second + 3) / 4) + 0.4 * lines;
 }
 
 constexpr uint32_t kTwoStepUnits = 256;
-constexpr double kTwoStepStart = 4.0;
+constexpr double kTwoStepStart = 2.0;
+
+// Whether population rows are whole 128-byte lines.
+bool rows_are_lines(uint32_t nx, size_t elem) { return nx * elem % 128 == 0; }
 
 // Calls fn(tx, ty, ntx, nty) for every even split of an nx x ny plane into tiles
-// that fit a block (rows of 16 nodes at least, unless nx is shorter).
+// that fit a block (rows of 16 nodes at least, unless nx is shorter).  Where
+// rows are whole lines, so are the tiles' pieces of them: a line written by two
+// blocks costs far more than an uneven last tile (256^3 FP32, tiles of 52 x 11
+// and 43 x 13 nodes 0.907 and 1.294 ms, 64 x 8 0.486).
 template <typename Fn>
-void two_step_each_tile(uint32_t nx, uint32_t ny, uint32_t most, Fn &&fn) {
-    for (uint32_t ntx = 1; ntx <= nx; ++ntx) {
-        const uint32_t tx = (nx + ntx - 1) / ntx;
-        if (tx < 16 && ntx > 1) break;
-        if ((tx + 2) * 3 > most || (nx + tx - 1) / tx != ntx) continue;
+void two_step_each_tile(uint32_t nx, uint32_t ny, size_t elem, Fn &&fn) {
+    const uint32_t most = two_step_nodes(elem);
+    const uint32_t line = rows_are_lines(nx, elem) ? uint32_t(128 / elem) : 1;
+    uint32_t last_tx = 0;
+    for (uint32_t split = 1; split <= nx; ++split) {
+        const uint32_t tx = ((nx + split - 1) / split + line - 1) / line * line, ntx = (nx + tx - 1) / tx;
+        if (tx < 16 && split > 1) break;
+        if ((tx + 2) * 3 > most || tx == last_tx) continue;
+        last_tx = tx;
         uint32_t last = 0;
         for (uint32_t top = std::min(ny, most / (tx + 2) - 2); top >= 1; --top) {
             const uint32_t nty = (ny + top - 1) / top, ty = (ny + nty - 1) / nty;
@@ -1156,7 +1173,6 @@ void two_step_each_tile(uint32_t nx, uint32_t ny, uint32_t most, Fn &&fn) {
 int two_step_candidates(const lbm_grid_desc *g, TwoStepTiles *out) {
     const uint32_t nx = uint32_t(g->nx), ny = uint32_t(g->ny), nz = uint32_t(g->nz);
     const size_t elem = elem_size(g->storage);
-    const uint32_t most = two_step_nodes(elem);
     // 32-bit byte offsets within a plane
     if (uint64_t(nx) * ny * uint64_t(velocity_count(g)) * elem >= (uint64_t(1) << 32)) return 0;
     struct Cand {
@@ -1164,7 +1180,7 @@ int two_step_candidates(const lbm_grid_desc *g, TwoStepTiles *out) {
         double cost;
     };
     std::vector<Cand> all;
-    two_step_each_tile(nx, ny, most, [&](uint32_t tx, uint32_t ty, uint32_t ntx, uint32_t nty) {
+    two_step_each_tile(nx, ny, elem, [&](uint32_t tx, uint32_t ty, uint32_t ntx, uint32_t nty) {
         const double plane = two_step_plane_cost(tx, ty, elem);
         const uint64_t tiles = uint64_t(ntx) * nty;
         const uint64_t r0 = (tiles + kTwoStepUnits - 1) / kTwoStepUnits;
@@ -1184,14 +1200,25 @@ int two_step_candidates(const lbm_grid_desc *g, TwoStepTiles *out) {
 }
 
 // Store policy of the two-step sweep: non-temporal once the two lattices
-// outgrow the 256 MB last-level cache (probe, two sweeps in turn, ms plain /
-// non-temporal: BF16 128^3, 80 MB a lattice, 0.0437 / 0.0488; FP32 128^3,
-// 159 MB, 0.0717 / 0.0673; FP32 256^3 0.502 / 0.486).
+// outgrow the 256 MB last-level cache, where rows are whole lines (two sweeps
+// in turn, ms plain / non-temporal: BF16 128^3, 80 MB a lattice, 0.0437 /
+// 0.0488; FP32 128^3, 159 MB, 0.0717 / 0.0673; FP32 256^3 0.502 / 0.486).
+// Other rows leave lines that two tiles write, which a cache has to join (FP32
+// 250^3, 1.19 GB, 0.522 / 0.565; BF16 300 x 200 x 150, 342 MB, 0.214 / 0.220).
 constexpr size_t kTwoStepStreamBytes = size_t(128) << 20;
 
-// Boxes of fewer nodes than this take single steps until tuned.
-// (64^3 with 16 particles, 60 recorded steps: 12.2 us a step against 12.9.)
-constexpr uint64_t kTwoStepMinNodes = uint64_t(1) << 19;
+// Boxes of fewer nodes than this take single steps until tuned: a block's two
+// planes of start are too large a part of its slab (us per step in a run, two-
+// step / single: FP32 64^3 5.8 / 7.0, 80^3 8.8 / 12.0; FP64 64^3 10.9 / 12.3; FP32
+// 56^3 tunes to single steps; BF16 72^3 and 80^3 likewise, 96^3 11.3 / 12.5).
+constexpr uint64_t two_step_min_nodes(size_t elem) { return uint64_t(1) << (elem == 2 ? 19 : 18); }
+
+bool two_step_by_size(const lbm_grid_desc *g) { return ncell_of(g) >= two_step_min_nodes(elem_size(g->storage)); }
+
+// Of two single steps' time, what a trial of the two-step sweep may take on a
+// lattice within the last-level cache: in boxes of that size and more (the
+// trials' error measured up to 1.3), and in smaller ones.
+constexpr double kTwoStepCached = 1.5, kTwoStepGain = 0.9;
 
 // The tiles of choice `two` (1: the model's first); 0 where the box has none.
 TwoStepTiles two_step_tiles(const lbm_grid_desc *g, int &two) {
@@ -1201,12 +1228,25 @@ TwoStepTiles two_step_tiles(const lbm_grid_desc *g, int &two) {
 }
 
 // Nodes per particle from which a two-step sweep pays for its particle update
-// one step ahead.
-constexpr double kTwoStepNodesPerParticle = 300.0;
+// one step ahead, which reads the populations around a 4^3 instead of a 2^3
+// neighbourhood (us per step in a run, two-step / single: FP32 128^3, 512 nodes
+// each 59.8 / 67.2, 304 nodes 73.0 / 73.6, FP64 111 / 127; 16-bit storage saves
+// less per sweep: BF16 256^3, 4096 nodes 198 / 222, 2048 nodes 232 / 231; 128^3
+// 4096 nodes 30.4 / 31.5, 2048 nodes 32.5 / 32.5, 512 nodes 47.7 / 38.1; 192^3
+// 6912 nodes 93.6 / 94.8, 3456 nodes 100 / 95.5), and nodes from which its
+// launch does (16 particles: BF16 96^3 18.7 / 18.2, 128^3 27.0 / 29.8; FP32 72^3
+// 14.6 / 15.7, but 60 recorded steps and their gradient at 64^3 3.66 / 3.56 ms).
+constexpr double two_step_nodes_per_particle(size_t elem) { return elem == 2 ? 4000.0 : 300.0; }
+constexpr uint64_t two_step_particle_nodes(size_t elem) { return elem == 2 ? uint64_t(1) << 20 : uint64_t(5) << 16; }
+
+bool two_step_pays(size_t elem, uint64_t nodes, int64_t particles) {
+    if (particles == 0) return true;
+    if (nodes < two_step_particle_nodes(elem)) return false;
+    return double(nodes) >= two_step_nodes_per_particle(elem) * double(particles);
+}
 
 bool two_step_pays(const lbm_ctx *c) {
-    return c->np == 0 || c->pdesc.friction == LBM_FRICTION_BD ||
-           double(c->g.ncell) >= kTwoStepNodesPerParticle * double(c->np);
+    return c->pdesc.friction == LBM_FRICTION_BD || two_step_pays(c->elem, c->g.ncell, c->np);
 }
 
 // The remembered code of a box holds, above the single-step launch, the
@@ -1255,8 +1295,8 @@ lbm_status lbm_init(const lbm_grid_desc *grid, void *pop_a, void *pop_b, void *g
         // the remembered layout, applied once the lattices are at rest below
         init_rows = uint32_t(1) << ((code / (kNumShapes * int(kNumOrders) * kNumCaps)) % (kMaxRowsLog2 + 1));
         const int two = code / kTuneTwo;  // remembered two-step choice + 1, 0: none
-        c->two = two > 0 ? two - 1 : ncell_of(grid) >= kTwoStepMinNodes;
-        c->two_nts = lat >= kTwoStepStreamBytes;
+        c->two = two > 0 ? two - 1 : two_step_by_size(grid);
+        c->two_nts = lat >= kTwoStepStreamBytes && rows_are_lines(c->g.nx, elem_size(grid->storage));
         c->two_tiles = two_step_tiles(grid, c->two);
         if (grid->ny % int32_t(init_rows) != 0) init_rows = 1;
         // LDS limits of the device, for the residency caps (none if unknown)
@@ -1633,6 +1673,8 @@ lbm_status lbm_autotune(lbm_ctx *ctx, int32_t iters, double *ms, int32_t *chosen
     if (!ctx || iters < 1 || iters > 10000) return LBM_E_INVAL;
     uint32_t ys[kMaxRowsLog2 + 1];
     const int nl = layout_candidates(ctx, ys);
+    size_t lat = 0;
+    lbm_lattice_bytes(&ctx->desc, &lat);
     constexpr int kMaxTrials = kNumShapes * kNumOrders * kNumCaps;
     int ks[kMaxTrials], os[kMaxTrials], cs[kMaxTrials];
     double t[kMaxTrials];
@@ -1648,7 +1690,7 @@ lbm_status lbm_autotune(lbm_ctx *ctx, int32_t iters, double *ms, int32_t *chosen
     auto note = [&](int k, int o, int c, int l, double v) {
         if (v <= 0.0) return;
         if (best_k[k] <= 0.0 || v < best_k[k]) best_k[k] = v;
-        trials.push_back(Trial{k, o, c, l, v});
+        if (config_tunable(k, lat)) trials.push_back(Trial{k, o, c, l, v});
     };
     auto time_one_layout = [&](int l, int n) -> bool {
         if (set_layout(ctx, ys[l]) != LBM_OK) return false;
@@ -1663,9 +1705,9 @@ lbm_status lbm_autotune(lbm_ctx *ctx, int32_t iters, double *ms, int32_t *chosen
         for (int k = 0; k < kNumShapes; ++k) ks[k] = k, os[k] = int(kOrderLinear), cs[k] = 0;
         if (!time_one_layout(l, kNumShapes)) return LBM_E_DEVICE;
         for (int k = 0; k < kNumShapes; ++k) {
-            t1[l][k] = t[k];
+            t1[l][k] = config_tunable(k, lat) ? t[k] : -1.0;
             note(k, int(kOrderLinear), 0, l, t[k]);
-            if (t[k] > 0.0 && (bl < 0 || t[k] < t1[bl][first])) bl = l, first = k;
+            if (t1[l][k] > 0.0 && (bl < 0 || t[k] < t1[bl][first])) bl = l, first = k;
         }
     }
     if (bl < 0) return LBM_E_DEVICE;
@@ -1723,12 +1765,18 @@ lbm_status lbm_autotune(lbm_ctx *ctx, int32_t iters, double *ms, int32_t *chosen
     ctx->shape = best.k;
     ctx->order = best.o;
     ctx->cap = best.c;
-    // Two-step sweep: the fastest of its tiles and store policies, if two
-    // steps in it are faster than two launches of the choice above.
+    // Two-step sweep: the fastest of its tiles, if two steps in it are faster
+    // than two launches of the choice above.  A lattice that the trials read
+    // from the last-level cache favours the single steps, which read twice as
+    // much: boxes large enough for two-step sweeps untuned keep them (FP16
+    // D3Q19 160^3 51 us per step in a run, 59 in single steps that the trials
+    // put first), smaller ones need a clear gain.
     {
         TwoStepTiles tl[kTwoStepCandidates];
         const int nt = two_step_candidates(&ctx->desc, tl);
         double two_best = total[jb];  // two timings of one step each
+        if (lat < kStreamStoreBytes)
+            two_best *= two_step_by_size(&ctx->desc) ? kTwoStepCached : kTwoStepGain;
         ctx->two = 0;
         for (int j = 0; j < nt; ++j) {
             double v = 0.0;
@@ -1925,25 +1973,36 @@ TuneKey ens_tune_key(const lbm_ens *e) {
 
 uint32_t ens_chunk(int32_t nx) { return uint32_t(nx); }  // unpadded, as row_chunk
 
-// Two-step tiles of one box of an ensemble: the boxes' blocks share the units,
-// so the tile is the one of least total cost, and slabs stay at about 24
-// planes (two planes and a start more per slab, against some thousand blocks
-// to even the units out).
-TwoStepTiles ens_two_tiles(const lbm_replica_desc &r, size_t elem) {
+// Two-step tiles of one box of an ensemble of total_cells nodes: the boxes'
+// blocks share the units, so the tile is the one of least total cost, and slabs
+// are of 24 planes (two planes and a start more per slab, against some thousand
+// blocks to even the units out), or as many as give each unit a block where
+// that is fewer, but 4 at least (13 BF16 boxes of 32 to 48 nodes, five steps:
+// 194 us in slabs of 24 planes, 128 in single steps).
+TwoStepTiles ens_two_tiles(const lbm_replica_desc &r, size_t elem, uint64_t total_cells) {
     const uint32_t nx = uint32_t(r.nx), ny = uint32_t(r.ny), nz = uint32_t(r.nz);
-    const uint32_t most = two_step_nodes(elem);
     TwoStepTiles best{};
     double cost = -1.0;
     // 32-bit byte offsets within a plane
     if (uint64_t(nx) * ny * D3Q19::Q * elem >= (uint64_t(1) << 32)) return best;
-    two_step_each_tile(nx, ny, most, [&](uint32_t tx, uint32_t ty, uint32_t ntx, uint32_t nty) {
+    two_step_each_tile(nx, ny, elem, [&](uint32_t tx, uint32_t ty, uint32_t ntx, uint32_t nty) {
         const double c = two_step_plane_cost(tx, ty, elem) * ntx * nty;
         if (cost > 0.0 && c >= cost) return;
-        const uint32_t ns = (nz + 23) / 24, lz = (nz + ns - 1) / ns;
+        const uint64_t share = total_cells / (uint64_t(kTwoStepUnits) * tx * ty);  // planes per unit
+        const uint32_t most = uint32_t(std::min<uint64_t>(24, std::max<uint64_t>(4, share)));
+        const uint32_t ns = (nz + most - 1) / most, lz = (nz + ns - 1) / ns;
         best = TwoStepTiles{tx, ty, lz, ntx, nty, (nz + lz - 1) / lz};
         cost = c;
     });
     return best;
+}
+
+// Ensembles of fewer nodes than 2^21 (16-bit 2^22) take single steps: their
+// blocks' slabs are a few planes (16 steps, us, two-step / single: 13 boxes of 32
+// to 48 nodes FP32 601 / 596, FP64 1221 / 1144, BF16 565 / 413; 40 such boxes
+// FP32 1236 / 1469, 64 BF16 1516 / 1525; 40 of 48 to 96 BF16 3520 / 4048).
+bool ens_two_step_pays(size_t elem, uint64_t nodes, int64_t particles) {
+    return nodes >= uint64_t(1) << (elem == 2 ? 22 : 21) && two_step_pays(elem, nodes, particles);
 }
 
 struct EnsLayout {
@@ -1951,6 +2010,7 @@ struct EnsLayout {
     uint32_t total_blocks[kNumGeomShapes] = {0, 0, 0, 0};
     uint32_t two_blocks = 0, two_threads = 0;  // two-step sweep
     bool two_ok = true;                        // every box has tiles for it
+    std::vector<TwoStepTiles> two;             // per box
     int32_t n = 0;
     size_t lattice_bytes = 0, scratch_bytes = 0;
     // scratch offsets
@@ -1992,11 +2052,19 @@ EnsLayout ens_layout(const lbm_ensemble_desc *d, const lbm_replica_desc *reps) {
             const uint64_t band = (r.ny % kShapes[s].cpt == 0) ? cells / kShapes[s].cpt : 0;
             L.total_blocks[s] += uint32_t((band + kShapes[s].bs - 1) / kShapes[s].bs);
         }
-        const TwoStepTiles tl = ens_two_tiles(r, elem);
+        L.n += r.n;
+    }
+    std::map<std::tuple<int32_t, int32_t, int32_t>, TwoStepTiles> tiles;
+    L.two.reserve(size_t(d->nrep));
+    for (int32_t k = 0; k < d->nrep; ++k) {
+        const lbm_replica_desc &r = reps[k];
+        const auto at = tiles.try_emplace(std::make_tuple(r.nx, r.ny, r.nz));
+        if (at.second) at.first->second = ens_two_tiles(r, elem, L.total_cells);
+        const TwoStepTiles &tl = at.first->second;
+        L.two.push_back(tl);
         L.two_ok = L.two_ok && tl.lz > 0;
         L.two_blocks += tl.ntx * tl.nty * tl.nslab;
         L.two_threads = std::max(L.two_threads, two_step_threads(tl));
-        L.n += r.n;
     }
     L.lattice_bytes = align_up(L.total_pop * elem, kAlign);
     size_t o = 0;
@@ -2442,8 +2510,7 @@ lbm_status lbm_ens_init(const lbm_ensemble_desc *desc, const lbm_replica_desc *r
         e->rows = 1 << ((code / (kNumShapes * int(kNumOrders) * kNumCaps)) % (kMaxRowsLog2 + 1));
         const int two = code / kTuneTwo;  // remembered two-step choice + 1, 0: none
         e->two_possible = ens_two_possible(L);
-        e->two = e->two_possible && (two > 0 ? two - 1 > 0 : L.total_cells >= kTwoStepMinNodes &&
-                                                       double(L.total_cells) >= kTwoStepNodesPerParticle * double(L.n));
+        e->two = e->two_possible && (two > 0 ? two - 1 > 0 : ens_two_step_pays(elem_size(desc->storage), L.total_cells, L.n));
         e->two_nts = L.lattice_bytes >= kTwoStepStreamBytes;
         int v = 0;
         e->lds_cu = (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor,
@@ -2505,7 +2572,7 @@ lbm_status lbm_ens_init(const lbm_ensemble_desc *desc, const lbm_replica_desc *r
             for (uint32_t b = 0; b < nb; ++b) blk[s][first[s] + b] = uint16_t(k);
             first[s] += nb;
         }
-        t.two = ens_two_tiles(rd, e->elem);
+        t.two = L.two[size_t(k)];
         t.first_two = first_two;
         for (uint32_t b = 0; b < t.two.ntx * t.two.nty * t.two.nslab; ++b) two[first_two++] = uint16_t(k);
         for (int32_t q = 0; q < rd.n; ++q) prep[part_off + q] = uint16_t(k);
@@ -2646,6 +2713,7 @@ lbm_status lbm_ens_autotune(lbm_ens *e, int32_t iters, double *ms, int32_t *chos
         double t;
     };
     std::vector<Trial> trials;
+    const size_t lat = size_t(e->total_cells) * D3Q19::Q * e->elem;
     bool ok = err == hipSuccess;
     auto time_in = [&](int l, int k, int o, int c, int32_t n) -> double {
         if (!ok) return -1.0;
@@ -2660,7 +2728,7 @@ lbm_status lbm_ens_autotune(lbm_ens *e, int32_t iters, double *ms, int32_t *chos
     auto note = [&](int k, int o, int c, int l, double v) {
         if (v <= 0.0) return;
         if (best_k[k] <= 0.0 || v < best_k[k]) best_k[k] = v;
-        trials.push_back(Trial{k, o, c, l, v});
+        if (config_tunable(k, lat)) trials.push_back(Trial{k, o, c, l, v});
     };
     // Stage 1: every configuration in linear order without a residency cap,
     // in every layout; keep the layout of the fastest launch.
@@ -2670,6 +2738,7 @@ lbm_status lbm_ens_autotune(lbm_ens *e, int32_t iters, double *ms, int32_t *chos
         for (int k = 0; k < kNumShapes && ok; ++k) {
             t1[l][k] = ens_launch_ok(e, k, 0) ? time_in(l, k, int(kOrderLinear), 0, iters) : -1.0;
             note(k, int(kOrderLinear), 0, l, t1[l][k]);
+            if (!config_tunable(k, lat)) t1[l][k] = -1.0;
             if (t1[l][k] > 0.0 && (bl < 0 || t1[l][k] < t1[bl][first])) bl = l, first = k;
         }
     if (bl < 0) ok = false;
@@ -2721,7 +2790,7 @@ lbm_status lbm_ens_autotune(lbm_ens *e, int32_t iters, double *ms, int32_t *chos
         const double one = ens_time_launch(e, best.k, best.o, best.c, 2 * iters, e0, e1);
         const double both = ens_time_two_steps(e, 2 * iters, e0, e1);
         ok = one > 0.0 && both > 0.0;
-        two = ok && both < 2.0 * one && double(e->total_cells) >= kTwoStepNodesPerParticle * double(e->n);
+        two = ok && both < 2.0 * one && ens_two_step_pays(e->elem, e->total_cells, e->n);
     }
     if (ok) {
         err = hipMemcpyAsync(e->clock, &saved, sizeof(saved), hipMemcpyHostToDevice, e->stream);

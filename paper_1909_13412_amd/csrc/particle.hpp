@@ -482,7 +482,11 @@ __global__ __launch_bounds__(2 * kParticleBlock) void k_particle(const typename 
 // particle computes for every node within one link of the particle's fitting
 // nodes (a 4^3 neighbourhood, 5^3 for the (2 dx)^3 cube), with the node forces
 // of step n, exactly as the sweep does; a ninth wavefront of the block runs
-// the eight particles' update on them.
+// the eight particles' update on them, so that its gather is from LDS.  With
+// few particles the chain of round trips bounds it (64 particles 9-11 us,
+// k_particle 8), with many the lines it touches: 16 row pieces of 16 bytes in
+// each of 19 populations, some 40 KB a particle (4096 particles 31-33 us,
+// k_particle 15-18).
 // ---------------------------------------------------------------------------
 // Particles per block and wavefronts per particle of the N^3 neighbourhood.
 template <int N>

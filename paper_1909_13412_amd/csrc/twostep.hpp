@@ -1,6 +1,24 @@
 // Two lattice steps in one sweep: the populations of step n are read once, the
 // post-collision values of step n stay in LDS, and those of step n + 1 are
-// written.
+// written, in the bits of two single steps (the same node_moments and
+// node_relax, the values in between encoded and decoded as in memory).
+//
+// A single step is bound by HBM: it reads and writes every population (152 B a
+// node in FP32).  Here a block takes a tile in x and y with one halo node
+// around it and marches in z: the first step of plane p from registers into
+// LDS, then the second step of plane p - 1, which pulls its e_z < 0 populations
+// from plane p and has kept the others in registers.  Half the bytes per step
+// are left, plus the halo, whose lines are mostly in the L2 of the XCD that
+// holds the neighbouring tiles (blocks in XCD slabs).  Two steps, ms, against
+// two single ones at 256^3: FP32 0.484 / 0.85, BF16 0.31 / 0.41, FP64 0.96 /
+// 1.73; FP32 128^3 0.067 / 0.110.  FP32 and FP64 reach 5.3 TB/s (a copy 4.8, the
+// single-step sweep 6.3); without its loads the FP32 sweep takes 0.23 ms,
+// without its stores 0.37.  16-bit storage is bound by the arithmetic of both
+// steps on 13 wavefronts a compute unit and the address unit's lines.
+// Slower were: planes brought to LDS by direct loads (FP32 0.548, BF16 0.395),
+// two small blocks per compute unit, non-temporal loads (FP32 0.726, BF16 0.463:
+// the halo's lines come twice), a march in alternate directions so that a
+// sweep first reads what the last one wrote last (under 1%).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -34,6 +52,7 @@ struct TwoStepShape {
     static constexpr int kBuffers = sizeof(T) == 8 ? 1 : 2;
     static constexpr int kPlanes = sizeof(T) == 8 ? 0 : (sizeof(T) == 4 ? 1 : 2);
     static constexpr int kFront = sizeof(T) == 2 ? 10 : 6;
+    static constexpr bool kForceAhead = sizeof(T) == 4;  // see two_steps_block
 };
 constexpr uint32_t two_step_nodes(size_t elem) {
     return elem == 8 ? TwoStepShape<double>::kNodes : TwoStepShape<float>::kNodes;
@@ -57,7 +76,13 @@ __device__ inline uint16_t held_copy(uint16_t v) { return v; }  // decoding move
 __device__ inline double held_copy(double v) { return v; }
 
 // One block: the nodes [x0, x0 + w) x [y0, y0 + h) x [z0, z0 + d).
-template <class C, bool FORCED, bool NTS>
+// AHEAD: the node forces of a plane are loaded with its populations, from flag
+// words loaded a plane before.  Loaded where they are needed they would hold up
+// a wavefront, and with it its block, until the loads and stores sent off
+// before them are done (4096 particles, FP32: ten steps at 128^3 775 -> 745 us,
+// twenty at 256^3 5.80 -> 5.72 ms).  Only FP32 has the 18 registers; the ensembles' sweep,
+// with its box table, would spill them (64 boxes 8.17 -> 8.26 ms per 16 steps).
+template <class C, bool FORCED, bool NTS, bool AHEAD>
 __device__ inline void two_steps_block(const typename C::T *__restrict__ A, typename C::T *__restrict__ B,
                                        const Grid &g, typename C::R omega, typename C::R enc_s,
                                        typename C::R dec_s, const ForceField &f0, const ForceField &f1,
@@ -70,6 +95,7 @@ __device__ inline void two_steps_block(const typename C::T *__restrict__ A, type
     using V = typename C::V;
     using S = TwoStepShape<T>;
     constexpr int D = S::kPlanes > 1 ? S::kPlanes : 1;  // sets of load registers
+    static_assert(!AHEAD || D == 1, "one set of node-force registers");
     const uint32_t pw = w + 2;  // row pitch of the padded tile in LDS
 
     auto up = [&](uint32_t z) { return z + 1 == g.nz ? 0u : z + 1; };
@@ -107,14 +133,31 @@ __device__ inline void two_steps_block(const typename C::T *__restrict__ A, type
     // word of the second step at the plane below; set i of D
     T raw[D][V::Q];
     uint32_t word1[D] = {}, word2[D] = {};
+    // AHEAD: the flag words of the plane after, the node forces at the
+    // flagged nodes of the plane itself
+    uint32_t ahead1 = 0, ahead2 = 0;
+    int64_t force1[3] = {}, force2[3] = {};
+    auto words_of = [&](uint32_t z, uint32_t zbelow, uint32_t &w1, uint32_t &w2) {
+        w1 = f0.mask[(z * nxy + cell1) >> 5];
+        w2 = f1.mask[(zbelow * nxy + cell2) >> 5];
+    };
+    auto force_at = [&](const ForceField &ff, uint32_t word, uint32_t cell, int64_t (&f)[3]) {
+        if ((word >> (cell & 31)) & 1u)
+            for (int k = 0; k < 3; ++k) f[k] = ff.f[3 * uint64_t(cell) + k];
+    };
     const char *src[3];  // planes zp + 1, zp, zp - 1 of the plane being loaded
     auto load_from = [&](uint32_t zp, auto ic) {
         constexpr int i = decltype(ic)::value;
         const uint32_t zs[3] = {up(zp), zp, down(zp)};
         for (int k = 0; k < 3; ++k) src[k] = reinterpret_cast<const char *>(A) + uint64_t(zs[k]) * plane;
-        if constexpr (FORCED) {
-            word1[i] = f0.mask[(zp * nxy + cell1) >> 5];
-            word2[i] = f1.mask[(zs[2] * nxy + cell2) >> 5];
+        if constexpr (FORCED && AHEAD) {
+            word1[i] = ahead1;
+            word2[i] = ahead2;
+            words_of(zs[0], zp, ahead1, ahead2);
+            force_at(f0, word1[i], zp * nxy + cell1, force1);
+            force_at(f1, word2[i], zs[2] * nxy + cell2, force2);
+        } else if constexpr (FORCED) {
+            words_of(zp, zs[2], word1[i], word2[i]);
         }
     };
     auto load_pop = [&](auto ac, auto ic) {
@@ -129,11 +172,17 @@ __device__ inline void two_steps_block(const typename C::T *__restrict__ A, type
     };
     const bool body = Gx != R(0) || Gy != R(0) || Gz != R(0);
     // relaxation at a node of linear index cell with flag bit `flag`
-    auto relax = [&](const R (&gv)[V::Q], bool flag, uint32_t cell, const ForceField &ff, auto &&put) {
+    auto relax = [&](const R (&gv)[V::Q], bool flag, uint32_t cell, const ForceField &ff, const R (&fn)[3], auto &&put) {
         const NodeMoments<C> m = node_moments<C>(gv);
         if (body || (FORCED && __any(flag))) {
             R Fx = Gx, Fy = Gy, Fz = Gz;
-            if constexpr (FORCED) {
+            if constexpr (FORCED && AHEAD) {
+                if (flag) {
+                    Fx += fn[0];
+                    Fy += fn[1];
+                    Fz += fn[2];
+                }
+            } else if constexpr (FORCED) {
                 if (flag) {
                     Fx += R(double(ff.f[3 * uint64_t(cell) + 0]) * kFixInv);
                     Fy += R(double(ff.f[3 * uint64_t(cell) + 1]) * kFixInv);
@@ -149,7 +198,7 @@ __device__ inline void two_steps_block(const typename C::T *__restrict__ A, type
     uint32_t b = 0;          // LDS buffer it writes
     // first step at plane zp, held in set i; w2: the flag word of the second
     // step below it
-    auto first_step = [&](uint32_t &w2, auto ic) {
+    auto first_step = [&](uint32_t &w2, R (&fn2)[3], auto ic) {
         constexpr int i = decltype(ic)::value;
         R gv[V::Q];
         static_for<0, V::Q>([&](auto ac) {
@@ -159,11 +208,18 @@ __device__ inline void two_steps_block(const typename C::T *__restrict__ A, type
         const uint32_t w1 = held_copy(word1[i]);
         w2 = held_copy(word2[i]);
         const uint32_t cell = zp * nxy + cell1;
+        R fn1[3] = {};
+        if constexpr (FORCED && AHEAD) {
+            for (int k = 0; k < 3; ++k) {
+                fn1[k] = R(double(force1[k]) * kFixInv);
+                fn2[k] = R(double(force2[k]) * kFixInv);
+            }
+        }
         if constexpr (S::kPlanes > 0) {
             load_from(S::kPlanes > 1 ? up(up(zp)) : up(zp), ic);
             static_for<0, S::kFront>([&](auto ac) { load_pop(ac, ic); });
         }
-        relax(gv, (w1 >> (cell & 31)) & 1u, cell, f0, [&](auto ac, R gn) {
+        relax(gv, (w1 >> (cell & 31)) & 1u, cell, f0, fn1, [&](auto ac, R gn) {
             constexpr int a = decltype(ac)::value;
             post[b][a][lds1] = C::enc(gn, enc_s);
             if constexpr (S::kPlanes > 0 && a >= S::kFront) {
@@ -202,12 +258,14 @@ __device__ inline void two_steps_block(const typename C::T *__restrict__ A, type
 
     using Set0 = std::integral_constant<int, 0>;
     using Set1 = std::integral_constant<int, D - 1>;
+    if constexpr (FORCED && AHEAD) words_of(zp, down(zp), ahead1, ahead2);
     load(zp, Set0{});
     if constexpr (D == 2) load(up(zp), Set1{});
     // the planes below and at z0
     auto start = [&](auto ic) {
         uint32_t w2;
-        first_step(w2, ic);
+        R fn2[3] = {};
+        first_step(w2, fn2, ic);
         if (second) shift();
         flip();
     };
@@ -217,7 +275,8 @@ __device__ inline void two_steps_block(const typename C::T *__restrict__ A, type
     // first step one plane above the second step's
     auto both = [&](auto ic) {
         uint32_t w2;
-        first_step(w2, ic);
+        R fn2[3] = {};
+        first_step(w2, fn2, ic);
         const uint32_t zt = down(down(zp));
         R gv[V::Q];
         static_for<0, V::Q>([&](auto ac) {
@@ -230,7 +289,7 @@ __device__ inline void two_steps_block(const typename C::T *__restrict__ A, type
         shift();
         const uint32_t cell = zt * nxy + cell2;
         char *row = reinterpret_cast<char *>(B) + uint64_t(zt) * plane;
-        relax(gv, (w2 >> (cell & 31)) & 1u, cell, f1, [&](auto ac, R gn) {
+        relax(gv, (w2 >> (cell & 31)) & 1u, cell, f1, fn2, [&](auto ac, R gn) {
             constexpr int a = decltype(ac)::value;
             uint32_t off = own;
             asm("" : "+v"(off));
@@ -245,7 +304,8 @@ __device__ inline void two_steps_block(const typename C::T *__restrict__ A, type
     // a wavefront past the tile's nodes has the first step only
     auto first_only = [&](auto ic) {
         uint32_t w2;
-        first_step(w2, ic);
+        R fn2[3] = {};
+        first_step(w2, fn2, ic);
         flip();
     };
     // d planes, the D register sets in turn; each kind of wavefront has a loop
@@ -289,7 +349,7 @@ __global__ __launch_bounds__(TwoStepShape<typename C::T>::kNodes) void k_two_ste
     typename C::R Gy, typename C::R Gz, TwoStepTiles tl, uint32_t order) {
     __shared__ typename C::T post[TwoStepShape<typename C::T>::kBuffers][C::V::Q][TwoStepShape<typename C::T>::kNodes];
     const TwoStepBlock t(tl, g, sweep_block(order));
-    two_steps_block<C, FORCED, NTS>(A, B, g, omega, enc_s, dec_s, f0, f1, Gx, Gy, Gz, t.x0, t.y0, t.z0, t.w, t.h, t.d, post);
+    two_steps_block<C, FORCED, NTS, TwoStepShape<typename C::T>::kForceAhead>(A, B, g, omega, enc_s, dec_s, f0, f1, Gx, Gy, Gz, t.x0, t.y0, t.z0, t.w, t.h, t.d, post);
 }
 
 // Every box of an ensemble (block -> box table); advances the device clock by
@@ -309,7 +369,7 @@ __global__ __launch_bounds__(TwoStepShape<typename C::T>::kNodes) void k_ens_two
     const Replica &rp = reps[blk_rep[blockIdx.x]];
     const Grid g = rp.g;
     const TwoStepBlock t(rp.two, g, blockIdx.x - rp.first_two);
-    two_steps_block<C, true, NTS>(A + rp.pop_off, B + rp.pop_off, g, R(rp.omega), enc_s, dec_s,
+    two_steps_block<C, true, NTS, false>(A + rp.pop_off, B + rp.pop_off, g, R(rp.omega), enc_s, dec_s,
                                   f0.box(rp.cell_off, rp.mask_off), f1.box(rp.cell_off, rp.mask_off),
                                   R(0), R(0), R(0), t.x0, t.y0, t.z0, t.w, t.h, t.d, post);
 }

@@ -15,14 +15,14 @@ from helpers import announce
 CASES = [
     ((96, 80, 70), "f32", 19, "stokeslet", 40, {}),
     ((100, 77, 71), "f32", 19, "stokeslet_cube", 60, dict(vacf=True)),
-    ((201, 51, 53), "f16", 15, "stokeslet", 9, dict(body=True)),
-    ((130, 129, 33), "bf16", 19, "stokeslet2dx", 64, dict(series=5)),
+    ((201, 99, 53), "f16", 15, "stokeslet", 9, dict(body=True)),
+    ((130, 129, 65), "bf16", 19, "stokeslet2dx", 64, dict(series=5)),
     ((33, 257, 64), "f64", 19, "pointwise", 50, dict(fext=True)),
     ((257, 33, 65), "f64", 15, "stokeslet_cube", 50, {}),
     ((1030, 260, 2), "f32", 19, "stokeslet", 31, dict(pair=True, vacf=True)),
     ((20, 164, 165), "bf16", 19, "bd", 100, dict(body=True)),
     ((64, 128, 65), "f32", 19, "stokeslet", 0, dict(body=True, series=3)),
-    ((96, 112, 57), "f16", 19, "stokeslet", 400, dict(pair=True)),
+    ((160, 112, 91), "f16", 19, "stokeslet", 400, dict(pair=True)),
 ]
 
 
@@ -129,7 +129,8 @@ def test_ensemble_two_step_sweep_equals_single_steps(storage, friction, graph):
     from paper_1909_13412_amd import Ensemble, _abi
     from paper_1909_13412_amd.inputs import particle_positions, particle_velocities
 
-    boxes = [((96, 48, 60), 0.7, 40), ((9, 7, 5), 0.9, 3), ((130, 33, 51), 0.8, 25), ((50, 51, 25), 0.65, 70)]
+    boxes = [((96, 48, 60), 0.7, 40), ((9, 7, 5), 0.9, 3), ((130, 33, 51), 0.8, 25), ((50, 51, 25), 0.65, 70),
+             ((320, 128, 89), 0.75, 30)]
     reps = [dict(nx=b[0], ny=b[1], nz=b[2], tau=tau, seed=40 + k, replica=k, r=particle_positions(n, b, k),
                  v=particle_velocities(n, 1e-3, k)) for k, (b, tau, n) in enumerate(boxes)]
     kw = dict(storage=storage, kT=1e-4, radius=0.5, friction=friction)
