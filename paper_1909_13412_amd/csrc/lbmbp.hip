@@ -1237,7 +1237,7 @@ TwoStepTiles two_step_tiles(const lbm_grid_desc *g, int &two) {
 // launch does (16 particles: BF16 96^3 18.7 / 18.2, 128^3 27.0 / 29.8; FP32 72^3
 // 14.6 / 15.7, but 60 recorded steps and their gradient at 64^3 3.66 / 3.56 ms).
 constexpr double two_step_nodes_per_particle(size_t elem) { return elem == 2 ? 4000.0 : 300.0; }
-constexpr uint64_t two_step_particle_nodes(size_t elem) { return elem == 2 ? uint64_t(1) << 20 : uint64_t(5) << 16; }
+constexpr uint64_t two_step_particle_nodes(size_t elem) { return elem == 2 ? uint64_t(1) << 21 : uint64_t(5) << 16; }
 
 bool two_step_pays(size_t elem, uint64_t nodes, int64_t particles) {
     if (particles == 0) return true;

@@ -15,14 +15,14 @@ from helpers import announce
 CASES = [
     ((96, 80, 70), "f32", 19, "stokeslet", 40, {}),
     ((100, 77, 71), "f32", 19, "stokeslet_cube", 60, dict(vacf=True)),
-    ((201, 99, 53), "f16", 15, "stokeslet", 9, dict(body=True)),
-    ((130, 129, 65), "bf16", 19, "stokeslet2dx", 64, dict(series=5)),
+    ((201, 201, 53), "f16", 15, "stokeslet", 9, dict(body=True)),
+    ((130, 129, 130), "bf16", 19, "stokeslet2dx", 64, dict(series=5)),
     ((33, 257, 64), "f64", 19, "pointwise", 50, dict(fext=True)),
     ((257, 33, 65), "f64", 15, "stokeslet_cube", 50, {}),
     ((1030, 260, 2), "f32", 19, "stokeslet", 31, dict(pair=True, vacf=True)),
     ((20, 164, 165), "bf16", 19, "bd", 100, dict(body=True)),
     ((64, 128, 65), "f32", 19, "stokeslet", 0, dict(body=True, series=3)),
-    ((160, 112, 91), "f16", 19, "stokeslet", 400, dict(pair=True)),
+    ((160, 112, 120), "f16", 19, "stokeslet", 400, dict(pair=True)),
 ]
 
 
