@@ -270,7 +270,10 @@ lbm_status lbm_vacf_counts(const lbm_ctx *ctx, int64_t *cnt);
  * neither step is recorded by lbm_series_config, two consecutive steps of one
  * call run in one sweep over the lattice, with the same bits as single steps;
  * the current state after n steps is in the lattice n swaps away as ever, the
- * spare lattice then holds an older one.  LBM_E_INVAL for nsteps < 0;
+ * spare lattice then holds an older one.  A call that takes an even number of
+ * steps leaves lattices and scratch in the roles it found them in: captured
+ * into a graph (no series, VACF or noise, which follow the host's step number)
+ * it can be replayed.  LBM_E_INVAL for nsteps < 0;
  * LBM_E_DEVICE if a launch fails. */
 lbm_status lbm_step(lbm_ctx *ctx, int32_t nsteps);
 
@@ -529,7 +532,7 @@ lbm_status lbm_ens_init(const lbm_ensemble_desc *desc, const lbm_replica_desc *r
 
 /* 1 (default): lbm_ens_step replays a captured graph of LBM_ENS_GRAPH_STEPS
  * steps for every whole group of that many steps from an even step (captured
- * once for each even step number mod 6, on a private stream, replayed on the context's stream), and launches the
+ * on a private stream, replayed on the context's stream), and launches the
  * rest of the steps directly; plain launches throughout if capture is not
  * possible; 0: plain launches. */
 #define LBM_ENS_GRAPH_STEPS 16

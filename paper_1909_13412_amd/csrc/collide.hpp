@@ -163,8 +163,8 @@ __device__ inline void lane_coords(const Grid &g, uint32_t lane_cell, uint32_t r
 // Node forces of one step: a dense fixed-point field, written only at the
 // (at most 8 per particle) nodes that receive a reaction force and read only
 // where the one-bit flag is set, so the stream-collide pays 1/8 byte per node.
-// Three take turns (step n spreads into field n mod 3); each is cleared node by
-// node by the particles that wrote it, after the sweep that read it.
+// Steps take turns with them; each is cleared node by node by the particles that
+// wrote it, after the sweep that read it.
 struct ForceField {
     long long *f;    // [ncell][3] fixed-point force
     uint32_t *mask;  // one bit per node: node carries a force this step

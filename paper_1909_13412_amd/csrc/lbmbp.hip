@@ -52,14 +52,14 @@
 namespace lbmbp {
 
 constexpr int kRedBlocks = 1024;
-// Node-force fields of a box: step n spreads into field n mod 3.  A two-step
-// sweep reads the fields of both its steps, so neither can be cleared before
-// it; the next particle update clears both and writes the third.
+// Node-force fields of a box: step n spreads into its own field, n mod 2.  A
+// two-step sweep reads the fields of both its steps, so neither can be cleared
+// before it, and the particle update that follows clears both: where the first
+// of them is that update's own field, it takes the third.  Two sweeps in a row
+// so end with the fields in the roles they started with, and an even number of
+// steps (the lattices' condition) can be captured into a graph and replayed.
 constexpr int kForceFields = 3;
-// A captured graph of an ensemble's steps names the fields (n mod 3) and the
-// particles' node lists (n mod 2), so there is one for each even step number
-// mod 6.
-constexpr int kEnsGraphs = 3;
+constexpr int kThirdField = 2;
 
 template <class C, int CPT, int BS, bool NTS>
 __global__ __launch_bounds__(BS) void k_ens_collide(const typename C::T *__restrict__ A,
@@ -320,7 +320,7 @@ struct lbm_ctx {
     double body[3];  // uniform body force on every node (lbm_set_body_force)
     // grid scratch
     uint32_t *mask[kForceFields];
-    long long *force[kForceFields];  // [ncell][3] fixed-point node forces, step n in field n mod 3
+    long long *force[kForceFields];  // [ncell][3] fixed-point node forces
     uint32_t mask_words;
     double *partials;
     double *result;
@@ -332,7 +332,8 @@ struct lbm_ctx {
     double *r, *v;
     uint32_t *cells[2];  // [n][8] nodes spread to in even and odd steps
     int fields_used;     // a particle update has run since the fields were cleared
-    int after_two;       // the last sweep was a two-step one: two fields to release
+    int last_field;      // the field that the last step spread into
+    int own_held;        // this step's own field still holds the forces of the step before the last
     double *fh, *fr;
     const double *fext;  // given force on each particle (lbm_set_particle_force) or null
     uint32_t warnings;   // LBM_WARN_* of the attached particles
@@ -572,11 +573,9 @@ void launch_collide(lbm_ctx *c, const typename C::T *A, typename C::T *B, ForceF
     launch_stream_collide<C, FORCED>(a);
 }
 
-// Node-force field of step n.
-ForceField field(lbm_ctx *c, int64_t n) {
-    const int k = int(n % kForceFields);
-    return ForceField{c->force[k], c->mask[k]};
-}
+ForceField field(const lbm_ctx *c, int k) { return ForceField{c->force[k], c->mask[k]}; }
+// The field that the step at hand spreads into.
+int step_field(const lbm_ctx *c) { return c->own_held ? kThirdField : int(c->step & 1); }
 
 // Blocks for the neighbour sums: kPairLanes lanes per particle.
 dim3 pair_group_blocks(int32_t n) {
@@ -662,10 +661,11 @@ ParticleArgs step_particle_args(lbm_ctx *c) {
     pa.fh = c->fh;
     pa.fr = c->fr;
     // this step's nodes, and those still to be released: the last step's, and
-    // after a two-step sweep the one's before it (kept where this step's go)
+    // after a two-step sweep the one's before it (kept where this step's go;
+    // none where they have been released)
     pa.cells = c->cells[c->step & 1];
     pa.last_cells = c->cells[(c->step & 1) ^ 1];
-    pa.older_cells = c->after_two ? pa.cells : nullptr;
+    pa.older_cells = pa.cells;
     pa.err = c->err;
     pa.n = c->np;
     pa.friction = c->pdesc.friction;
@@ -687,11 +687,39 @@ ParticleArgs step_particle_args(lbm_ctx *c) {
     return pa;
 }
 
+// The particle update of the step at hand; earlier fields are released with it.
 template <class C>
-void launch_particle(lbm_ctx *c, const typename C::T *A, const ParticleArgs &pa, int64_t n) {
-    c->fields_used = 1;
+void launch_particle(lbm_ctx *c, const typename C::T *A, const ParticleArgs &pa) {
+    const int cur = step_field(c);
     hipLaunchKernelGGL(k_particle<C>, dim3(unsigned(particle_blocks(c->np))), dim3(particle_threads(pa)), 0, c->stream, A,
-                       c->g, typename C::R(c->dec_s), pa, field(c, n), field(c, n + 2), field(c, n + 1));
+                       c->g, typename C::R(c->dec_s), pa, field(c, cur), field(c, c->last_field),
+                       field(c, c->own_held ? int(c->step & 1) : kThirdField));
+    c->fields_used = 1;
+    c->last_field = cur;
+    c->own_held = 0;
+}
+
+// Releases the nodes of the last step and of the one before, lists of n entries.
+__global__ __launch_bounds__(kBlock) void k_release(int32_t n, uint32_t *last_cells, ForceField last,
+                                                    uint32_t *older_cells, ForceField older) {
+    const int32_t i = int32_t(blockIdx.x * kBlock + threadIdx.x);
+    if (i >= n) return;
+    release_node(last, last_cells[i]);
+    release_node(older, older_cells[i]);
+    last_cells[i] = older_cells[i] = kNoNode;
+}
+
+// Leaves the fields as every call finds them: the last step's forces in its own
+// field, those of the step before it in the third or released.  Only steps
+// recorded between two-step sweeps can end otherwise.
+void settle_fields(lbm_ctx *c) {
+    const int last = int(c->step & 1) ^ 1;
+    if (c->np == 0 || (!c->own_held && c->last_field == last)) return;
+    hipLaunchKernelGGL(k_release, dim3(blocks_for(uint64_t(c->np) * 8)), dim3(kBlock), 0, c->stream, c->np * 8,
+                       c->cells[last], field(c, c->last_field), c->cells[last ^ 1],
+                       field(c, c->own_held ? last ^ 1 : kThirdField));
+    c->last_field = last;
+    c->own_held = 0;
 }
 
 template <class C>
@@ -707,15 +735,14 @@ void launch_step(lbm_ctx *c) {
         const int32_t pk = prof_start(c, 1);
         ParticleArgs pa = step_particle_args(c);
         pa.pmom = sample ? c->part_partials : nullptr;
-        launch_particle<C>(c, A, pa, c->step);
-        c->after_two = 0;
+        launch_particle<C>(c, A, pa);
         prof_stop(c, pk);
         const int32_t ck = prof_start(c, 0);
-        launch_collide<C, true>(c, A, B, field(c, c->step), c->shape, mom);
+        launch_collide<C, true>(c, A, B, field(c, c->last_field), c->shape, mom);
         prof_stop(c, ck);
     } else {
         const int32_t ck = prof_start(c, 0);
-        launch_collide<C, false>(c, A, B, field(c, c->step), c->shape, mom);
+        launch_collide<C, false>(c, A, B, field(c, 0), c->shape, mom);
         prof_stop(c, ck);
     }
     if (sample) {
@@ -756,24 +783,26 @@ TwoStepArgs two_step_args(lbm_ctx *c, const TwoStepTiles &tl, bool nts, ForceFie
 // then the two-step sweep.
 template <class C>
 void launch_two_step(lbm_ctx *c) {
-    const TwoStepArgs a = two_step_args(c, c->two_tiles, c->two_nts != 0, field(c, c->step), field(c, c->step + 1));
+    const int f0 = step_field(c), f1 = int(c->step & 1) ^ 1;
+    const TwoStepArgs a = two_step_args(c, c->two_tiles, c->two_nts != 0, field(c, f0), field(c, f1));
     if (c->series_every > 0) c->series_t += 2;
     if (c->np > 0) {
         const typename C::T *A = static_cast<const typename C::T *>(a.A);
         int32_t pk = prof_start(c, 1);
-        launch_particle<C>(c, A, step_particle_args(c), c->step);
+        launch_particle<C>(c, A, step_particle_args(c));
         prof_stop(c, pk);
         c->step += 1;
-        c->after_two = 0;
         pk = prof_start(c, 1);
         ParticleArgs pa = step_particle_args(c);
         pa.last_cells = nullptr;  // the field of step n is still to be read
+        pa.older_cells = nullptr;  // the last update released it
         if (c->pdesc.friction == LBM_FRICTION_BD)
-            launch_particle<C>(c, A, pa, c->step);  // reads no fluid
+            launch_particle<C>(c, A, pa);  // reads no fluid
         else
             launch_particle_ahead<C>(a, pa);
         prof_stop(c, pk);
-        c->after_two = 1;
+        c->last_field = f1;
+        c->own_held = f0 != kThirdField;
     } else {
         c->step += 1;
     }
@@ -800,7 +829,7 @@ void time_launches(lbm_ctx *c, int32_t iters, int n, const int *ks, const int *o
     if (*err == hipSuccess) *err = hipEventCreate(&e1);
     if (*err != hipSuccess) return;
     const bool forced = c->np > 0;
-    const ForceField last = field(c, c->step + 2);  // of step - 1
+    const ForceField last = field(c, c->last_field);
     for (int j = 0; j < n && *err == hipSuccess; ++j) {
         const int k = ks[j], order = orders[j], cap = caps[j];
         ms[j] = -1.0;
@@ -885,7 +914,7 @@ void time_stream_only(lbm_ctx *c, int k, int32_t iters, double *ms, hipError_t *
 // launches (A -> B, as time_launches).
 template <class C>
 void time_two_steps(lbm_ctx *c, const TwoStepTiles &tl, bool nts, int32_t iters, double *ms, hipError_t *err) {
-    const ForceField last = field(c, c->step + 2);
+    const ForceField last = field(c, c->last_field);
     const TwoStepArgs a = two_step_args(c, tl, nts, last, last);
     hipEvent_t e0, e1;
     *err = hipEventCreate(&e0);
@@ -1422,7 +1451,8 @@ lbm_status particles_couple(lbm_ctx *ctx, const lbm_particle_desc *d, double *r,
         if (e != hipSuccess) return LBM_E_DEVICE;
     }
     ctx->fields_used = 0;
-    ctx->after_two = 0;
+    ctx->last_field = int(ctx->step & 1) ^ 1;
+    ctx->own_held = 0;
     ctx->vacf_on = 0;
     ctx->fext = nullptr;
     ctx->pair_on = 0;
@@ -1584,6 +1614,7 @@ void advance(lbm_ctx *c, int32_t n) {
             --left;
         }
     }
+    settle_fields(c);
 }
 
 }  // namespace
@@ -1952,8 +1983,8 @@ struct lbm_ens {
     // graph of LBM_ENS_GRAPH_STEPS steps, captured on a private stream and
     // replayed on `stream`
     int use_graph;
-    hipGraphExec_t graph[kEnsGraphs];  // from a step number 0, 2 and 4 mod 6
-    int graph_valid[kEnsGraphs];
+    hipGraphExec_t graph;
+    int graph_valid;
     hipStream_t cap_stream;
     int graph_replays;  // number of graph launches so far
 };
@@ -2141,11 +2172,7 @@ ParticleArgs ens_particle_args(lbm_ens *e) {
 // SIMD for blocks of bs lanes (0: no cap; -1: not possible on this device).
 long ens_sweep_lds(const lbm_ens *e, int cap, int bs) { return residency_lds(e->lds_cu, e->lds_block, cap, bs); }
 
-// Node-force field of step n.
-ForceField ens_field(const lbm_ens *e, int64_t n) {
-    const int k = int(n % kForceFields);
-    return ForceField{e->force[k], e->mask[k]};
-}
+ForceField ens_field(const lbm_ens *e, int64_t k) { return ForceField{e->force[k], e->mask[k]}; }
 
 template <class C, int CPT, int BS, bool NTS>
 void ens_collide_shape(lbm_ens *e, const typename C::T *A, typename C::T *B, const ForceField &ff) {
@@ -2159,19 +2186,20 @@ void ens_collide_shape(lbm_ens *e, const typename C::T *A, typename C::T *B, con
 }
 
 // The particle update of step n (`ahead` steps after the device clock), and the
-// nodes it has to release: those of the last two steps.  (Where the step two
-// back was released already its nodes are cleared again; its field is idle.)
+// nodes it has to release: those of the last two steps.  held: the step's own
+// field is one of them (kForceFields), it spreads into the third.
 template <class C>
-void ens_launch_particle(lbm_ens *e, const typename C::T *A, int64_t n, int ahead) {
+void ens_launch_particle(lbm_ens *e, const typename C::T *A, int64_t n, int ahead, bool held) {
+    const int own = int(n & 1);
     ParticleArgs pa = ens_particle_args(e);
-    pa.cells = e->cells[n & 1];
+    pa.cells = e->cells[own];
     if (!ahead) {
-        pa.last_cells = e->cells[(n & 1) ^ 1];
+        pa.last_cells = e->cells[own ^ 1];
         pa.older_cells = pa.cells;
     }
     hipLaunchKernelGGL(k_ens_particle<C>, dim3(unsigned(particle_blocks(e->n))), dim3(particle_threads(pa)), 0, e->stream, A,
-                       e->reps, e->part_rep, typename C::R(e->dec_s), pa, e->clock, ahead, ens_field(e, n),
-                       ens_field(e, n + 2), ens_field(e, n + 1));
+                       e->reps, e->part_rep, typename C::R(e->dec_s), pa, e->clock, ahead,
+                       ens_field(e, held ? kThirdField : own), ens_field(e, own ^ 1), ens_field(e, held ? own : kThirdField));
 }
 
 // Step n of every replica, from lattice cur.
@@ -2180,8 +2208,8 @@ void ens_launch_step(lbm_ens *e, int cur, int64_t n) {
     using T = typename C::T;
     const T *A = static_cast<const T *>(e->pop[cur]);
     T *B = static_cast<T *>(e->pop[cur ^ 1]);
-    ens_launch_particle<C>(e, A, n, 0);
-#define LBM_ENS_CALL(CPT, BS, NTS, ROW) ens_collide_shape<C, CPT, BS, NTS>(e, A, B, ens_field(e, n))
+    ens_launch_particle<C>(e, A, n, 0, false);
+#define LBM_ENS_CALL(CPT, BS, NTS, ROW) ens_collide_shape<C, CPT, BS, NTS>(e, A, B, ens_field(e, n & 1))
     LBM_CONFIG_SWITCH(e->shape, LBM_ENS_CALL)
 #undef LBM_ENS_CALL
 }
@@ -2207,13 +2235,15 @@ EnsTwoStepArgs ens_two_step_args(lbm_ens *e, int cur, const ForceField &f0, cons
 }
 
 // Steps n and n + 1 of every replica in one sweep (see launch_two_step).
+// held: steps n - 2 and n - 1 were the first such sweep of a pair.
 template <class C>
-void ens_launch_two_step(lbm_ens *e, int cur, int64_t n) {
-    const EnsTwoStepArgs a = ens_two_step_args(e, cur, ens_field(e, n), ens_field(e, n + 1));
+void ens_launch_two_step(lbm_ens *e, int cur, int64_t n, bool held) {
+    const EnsTwoStepArgs a =
+        ens_two_step_args(e, cur, ens_field(e, held ? kThirdField : n & 1), ens_field(e, (n + 1) & 1));
     const typename C::T *A = static_cast<const typename C::T *>(a.A);
-    ens_launch_particle<C>(e, A, n, 0);
+    ens_launch_particle<C>(e, A, n, 0, held);
     if (e->desc.friction == LBM_FRICTION_BD) {
-        ens_launch_particle<C>(e, A, n + 1, 1);  // reads no fluid
+        ens_launch_particle<C>(e, A, n + 1, 1, false);  // reads no fluid
     } else {
         ParticleArgs pa = ens_particle_args(e);
         pa.cells = e->cells[(n + 1) & 1];
@@ -2223,20 +2253,21 @@ void ens_launch_two_step(lbm_ens *e, int cur, int64_t n) {
 }
 
 template <class C>
-void ens_launch_any(lbm_ens *e, int cur, int64_t n, bool two) {
-    if (two)
-        ens_launch_two_step<C>(e, cur, n);
+void ens_launch_any(lbm_ens *e, int cur, int64_t n, int sweep) {
+    if (sweep)
+        ens_launch_two_step<C>(e, cur, n, sweep == 2);
     else
         ens_launch_step<C>(e, cur, n);
 }
 
-// Step n, or steps n and n + 1 in one sweep, from lattice cur.
-void ens_dispatch_step(lbm_ens *e, int cur, int64_t n, bool two) {
+// Step n (sweep 0), or steps n and n + 1 in the first or the second of a pair of
+// two-step sweeps (1, 2), from lattice cur.
+void ens_dispatch_step(lbm_ens *e, int cur, int64_t n, int sweep) {
     switch (e->desc.storage) {
-        case LBM_STORE_F64: ens_launch_any<F64Q19>(e, cur, n, two); break;
-        case LBM_STORE_F32: ens_launch_any<F32Q19>(e, cur, n, two); break;
-        case LBM_STORE_BF16: ens_launch_any<BF16Q19>(e, cur, n, two); break;
-        case LBM_STORE_F16: ens_launch_any<F16Q19>(e, cur, n, two); break;
+        case LBM_STORE_F64: ens_launch_any<F64Q19>(e, cur, n, sweep); break;
+        case LBM_STORE_F32: ens_launch_any<F32Q19>(e, cur, n, sweep); break;
+        case LBM_STORE_BF16: ens_launch_any<BF16Q19>(e, cur, n, sweep); break;
+        case LBM_STORE_F16: ens_launch_any<F16Q19>(e, cur, n, sweep); break;
     }
 }
 
@@ -2290,24 +2321,21 @@ lbm_status ens_set_layout(lbm_ens *e, int rows) {
 }
 
 void ens_drop_graph(lbm_ens *e) {
-    for (int k = 0; k < kEnsGraphs; ++k) {
-        if (e->graph_valid[k]) (void)hipGraphExecDestroy(e->graph[k]);
-        e->graph_valid[k] = 0;
-    }
+    if (e->graph_valid) (void)hipGraphExecDestroy(e->graph);
+    e->graph_valid = 0;
 }
 
 // Two steps per graph cost about 1.5% over plain launches on the 64-box
 // workload; sixteen amortise the graph launch.
-static_assert(LBM_ENS_GRAPH_STEPS % 4 == 0, "an even number of two-step sweeps, so that the lattices return to their start");
+static_assert(LBM_ENS_GRAPH_STEPS % 4 == 0, "pairs of two-step sweeps, so that lattices and fields return to their start");
 
-// Capture LBM_ENS_GRAPH_STEPS steps from step number 2 * phase mod 6, starting
-// from lattice e->cur, into a graph.
+// Capture LBM_ENS_GRAPH_STEPS steps from an even step number, starting from
+// lattice e->cur, into a graph.
 // Capture runs on a private non-blocking stream (the caller's stream may be
 // the null stream, which cannot be captured); the graph is then launched on
 // the caller's stream.  Returns false when no graph could be made.
-bool ens_capture(lbm_ens *e, int phase) {
-    if (e->graph_valid[phase]) (void)hipGraphExecDestroy(e->graph[phase]);
-    e->graph_valid[phase] = 0;
+bool ens_capture(lbm_ens *e) {
+    ens_drop_graph(e);
     if (!e->cap_stream && hipStreamCreateWithFlags(&e->cap_stream, hipStreamNonBlocking) != hipSuccess) {
         e->cap_stream = nullptr;
         return false;
@@ -2318,7 +2346,7 @@ bool ens_capture(lbm_ens *e, int phase) {
     e->stream = e->cap_stream;
     int cur = e->cur;
     for (int k = 0; k < LBM_ENS_GRAPH_STEPS; k += e->two ? 2 : 1) {
-        ens_dispatch_step(e, cur, 2 * phase + k, e->two != 0);
+        ens_dispatch_step(e, cur, k, e->two ? 1 + (k / 2) % 2 : 0);
         cur ^= 1;
     }
     e->stream = user;
@@ -2328,13 +2356,13 @@ bool ens_capture(lbm_ens *e, int phase) {
         (void)hipGetLastError();
         return false;
     }
-    const hipError_t err = hipGraphInstantiate(&e->graph[phase], g, nullptr, nullptr, 0);
+    const hipError_t err = hipGraphInstantiate(&e->graph, g, nullptr, nullptr, 0);
     (void)hipGraphDestroy(g);
     if (err != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
-    e->graph_valid[phase] = 1;
+    e->graph_valid = 1;
     return true;
 }
 
@@ -2348,7 +2376,7 @@ void ens_time_shape(lbm_ens *e, int k, int o, int c) {
     e->cap = c;
     ens_collide_shape<C, CPT, BS, NTS>(e, static_cast<const typename C::T *>(e->pop[e->cur]),
                                        static_cast<typename C::T *>(e->pop[e->cur ^ 1]),
-                                       ens_field(e, e->step + 2));  // last step's node forces
+                                       ens_field(e, (e->step + 1) & 1));  // last step's node forces
     e->shape = saved[0];
     e->order = saved[1];
     e->cap = saved[2];
@@ -2416,7 +2444,7 @@ void ens_two_steps_any(lbm_ens *e, const EnsTwoStepArgs &a) {
 
 // Mean ms per two-step sweep (A -> B, as ens_time_launch).
 double ens_time_two_steps(lbm_ens *e, int32_t iters, hipEvent_t e0, hipEvent_t e1) {
-    const ForceField last = ens_field(e, e->step + 2);
+    const ForceField last = ens_field(e, (e->step + 1) & 1);
     const EnsTwoStepArgs a = ens_two_step_args(e, e->cur, last, last);
     for (int w = 0; w < 2; ++w) ens_two_steps_any(e, a);
     (void)hipEventRecord(e0, e->stream);
@@ -2655,40 +2683,37 @@ lbm_status lbm_ens_vacf_counts(const lbm_ens *e, int64_t *cnt) {
 lbm_status lbm_ens_step(lbm_ens *e, int32_t nsteps) {
     if (!e || nsteps < 0) return LBM_E_INVAL;
     int32_t left = nsteps;
-    auto eager = [&](bool two) {
-        const int32_t k = two ? 2 : 1;
-        ens_dispatch_step(e, e->cur, e->step, two);
+    auto eager = [&](int sweep) {
+        const int32_t k = sweep ? 2 : 1;
+        ens_dispatch_step(e, e->cur, e->step, sweep);
         e->cur ^= 1;
         e->step += k;
         if (e->vacf_on) e->vacf_t += k;
         left -= k;
     };
     if (e->use_graph) {
-        if (left > 0 && (e->step & 1)) eager(false);
+        if (left > 0 && (e->step & 1)) eager(0);
         constexpr int32_t per = LBM_ENS_GRAPH_STEPS;
-        while (left >= per && e->use_graph) {
-            const int phase = int(e->step % (2 * kEnsGraphs)) / 2;
-            if (!e->graph_valid[phase] && !ens_capture(e, phase)) {
-                e->use_graph = 0;  // plain launches
-                break;
+        if (left >= per && !e->graph_valid && !ens_capture(e)) e->use_graph = 0;  // plain launches
+        if (left >= per && e->graph_valid) {
+            // the graph was captured from lattice parity cur at an even step;
+            // cur and the step parity change together, so they still match
+            while (left >= per) {
+                if (hipGraphLaunch(e->graph, e->stream) != hipSuccess) return LBM_E_DEVICE;
+                e->graph_replays += 1;
+                e->step += per;
+                if (e->vacf_on) e->vacf_t += per;
+                left -= per;
             }
-            // the graph was captured from lattice parity cur at an even step of
-            // this phase; cur and the step parity change together, so they
-            // still match
-            if (hipGraphLaunch(e->graph[phase], e->stream) != hipSuccess) return LBM_E_DEVICE;
-            e->graph_replays += 1;
-            e->step += per;
-            if (e->vacf_on) e->vacf_t += per;
-            left -= per;
         }
     }
     // an even number of two-step sweeps, so that n steps leave the state in the
     // lattice n swaps away
     while (e->two && left >= 4) {
-        eager(true);
-        eager(true);
+        eager(1);
+        eager(2);
     }
-    while (left > 0) eager(false);
+    while (left > 0) eager(0);
     return launch_status();
 }
 

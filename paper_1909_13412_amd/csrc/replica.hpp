@@ -37,7 +37,7 @@ struct Replica {
 };
 
 struct EnsClock {
-    int64_t step;    // Philox first counter word and field parity
+    int64_t step;    // Philox first counter word
     int64_t vacf_t;  // VACF sample clock
 };
 
