@@ -485,13 +485,15 @@ uint32_t pair_buckets(int32_t n) {
 }
 
 size_t pair_list_bytes(int32_t n) {
-    return align_up(size_t(n) * sizeof(PairLink), kAlign) + align_up(size_t(pair_buckets(n)) * 4, kAlign);
+    if (n > kPairMax) return 0;  // lbm_set_pair_force refuses them
+    return 2 * align_up(size_t(n) * sizeof(PairLink), kAlign) + align_up(2 * size_t(pair_buckets(n)) * 4, kAlign);
 }
 
 // Carves the cell list out of pair_list_bytes(n) bytes at s.
 PairList pair_list_at(char *s, int32_t n) {
-    return PairList{reinterpret_cast<PairLink *>(s),
-                    reinterpret_cast<uint32_t *>(s + align_up(size_t(n) * sizeof(PairLink), kAlign))};
+    const size_t links = align_up(size_t(n) * sizeof(PairLink), kAlign);
+    uint32_t *head = reinterpret_cast<uint32_t *>(s + 2 * links);
+    return PairList{reinterpret_cast<PairLink *>(s), reinterpret_cast<PairLink *>(s + links), head, head + pair_buckets(n)};
 }
 
 size_t particle_scratch_size(int32_t n) {
@@ -582,18 +584,23 @@ dim3 pair_group_blocks(int32_t n) {
     return dim3(unsigned((size_t(n) * kPairLanes + kPairBlock - 1) / kPairBlock));
 }
 
-// Pair forces of the positions r: link the cell list, then the neighbour sums.
-// The list heads are none before; the particle update that follows sets them
+// Pair forces of the positions r: link the cell list, order long ones, then the
+// neighbour sums.  The list heads are none before; the particle update that follows sets them
 // back (its pair_list), or pair_list_clear does.
 void launch_pairs(hipStream_t st, const double *r, int32_t n, const PairGrid &pg, const PairList &pl,
                   double *F) {
     const dim3 pblocks(unsigned((n + kPairBlock - 1) / kPairBlock));
     hipLaunchKernelGGL(k_pair_link, pblocks, dim3(kPairBlock), 0, st, r, n, pg, pl);
-    hipLaunchKernelGGL(k_pair_force, pair_group_blocks(n), dim3(kPairBlock), 0, st, r, n, pg, pl, F);
+    if (pg.ordered) {
+        hipLaunchKernelGGL(k_pair_order, pblocks, dim3(kPairBlock), 0, st, n, pg, pl);
+        hipLaunchKernelGGL(k_pair_force<true>, pair_group_blocks(n), dim3(kPairBlock), 0, st, r, n, pg, pl, F);
+    } else {
+        hipLaunchKernelGGL(k_pair_force<false>, pair_group_blocks(n), dim3(kPairBlock), 0, st, r, n, pg, pl, F);
+    }
 }
 
 hipError_t pair_list_clear(hipStream_t st, const PairList &pl, uint32_t T) {
-    return hipMemsetAsync(pl.head, 0xFF, size_t(T) * 4, st);
+    return hipMemsetAsync(pl.head, 0xFF, 2 * size_t(T) * 4, st);  // and `first` behind it
 }
 
 // Returns the start event of a new timing pair (or nullptr when profiling is
@@ -678,7 +685,7 @@ ParticleArgs step_particle_args(lbm_ctx *c) {
     pa.step = uint32_t(c->step);
     pa.fext = c->fext;
     pa.fpair = nullptr;
-    pa.pair_list = PairList{nullptr, nullptr};
+    pa.pair_list = PairList{};
     if (c->pair_on) {
         launch_pairs(c->stream, c->r, c->np, c->pg, c->plist, c->fpair);
         pa.fpair = c->fpair;
@@ -1485,7 +1492,7 @@ lbm_status particles_couple(lbm_ctx *ctx, const lbm_particle_desc *d, double *r,
     ctx->fpair = reinterpret_cast<double *>(s);
     // nodes spread to -> kNoNode (all ones), list heads -> none; forces zero.
     e = hipMemsetAsync(ctx->cells[0], 0xFF, 2 * align_up(size_t(d->n) * 8 * 4, kAlign), ctx->stream);
-    if (e == hipSuccess)
+    if (e == hipSuccess && d->n <= kPairMax)
         e = pair_list_clear(ctx->stream, ctx->plist, pair_buckets(d->n));
     if (e == hipSuccess) e = hipMemsetAsync(ctx->fh, 0, size_t(d->n) * 3 * 8, ctx->stream);
     if (e == hipSuccess) e = hipMemsetAsync(ctx->fr, 0, size_t(d->n) * 3 * 8, ctx->stream);
@@ -1513,6 +1520,7 @@ lbm_status lbm_set_pair_force(lbm_ctx *ctx, double a_f, double r_c) {
     pg.n = uint32_t(ctx->np);
     pg.a = a_f;
     pg.rc = r_c;
+    pg.ordered = pair_list_ordered(pg.n, uint64_t(pg.nc[0]) * pg.nc[1] * pg.nc[2]);
     ctx->pg = pg;
     ctx->pair_on = 1;
     return LBM_OK;
@@ -3253,8 +3261,8 @@ hipError_t adjoint_run(lbm_ctx *c, char *tape, char *work, double *adj_pop, doub
                                    seg(k), c->g, R(c->dec_s), abar[cur], gd, ap, uf[par],
                                    uf[par ^ 1]);
                 if (pairs) {
-                    hipLaunchKernelGGL(k_adj_pair, pair_group_blocks(np), dim3(kPairBlock), 0, st,
-                                       seg_r(k), np, c->rec_pg, plist, fcbar, adj_r);
+                    hipLaunchKernelGGL(c->rec_pg.ordered ? k_adj_pair<true> : k_adj_pair<false>, pair_group_blocks(np),
+                                       dim3(kPairBlock), 0, st, seg_r(k), np, c->rec_pg, plist, fcbar, adj_r);
                     if (e == hipSuccess) e = pair_list_clear(st, plist, c->rec_pg.T);
                 }
                 if (stream_stores)

@@ -7,16 +7,19 @@
 // Neighbours come from a cell list: the box is cut into nc cells per axis
 // of edge L/nc >= r_c and the cells are hashed into T buckets (T a power of
 // two >= 2n).  One pass links every particle into its bucket's list (an atomic
-// exchange of the list head).  Every particle then walks the (up to) 27 cells
-// around its own in a fixed order, each cell's particles in ascending index
-// (entries of other cells hashed to the same bucket are skipped); the 27 cells
-// go to 27 lanes and their sums are combined in a fixed order: the result is
-// bitwise reproducible although the links are not.  The adjoint kernel uses
-// the same walk.
+// exchange of the list head); where cells hold many particles another finds
+// every particle's successor in ascending index.  Every particle then walks the
+// (up to) 27 cells around its own in a fixed order, each cell's particles in
+// ascending index (entries of other cells hashed to the same bucket are
+// skipped); the 27 cells go to 27 lanes and their sums are combined in a fixed
+// order: the result is bitwise reproducible although the first links are not.
+// The adjoint kernel uses the same walk.
 //
-// Both passes are a launch's latency (FP64, 4096 particles: 4.6 and 5 us).  The
-// first design counted, scanned, scattered and sorted the buckets in four
-// passes of 4.6 us each before the walk.
+// For a particle or two per cell each pass is a launch's latency (FP64, 4096
+// particles: 4.6 and 5 us).  For m of them a pass is a chain of some m loads:
+// cutoffs of up to half the box and clusters are accepted, and an insertion sort
+// or a new walk for every few particles made 512 per cell 10.9 and 12.9 ms a
+// step, the pass over the links 0.53.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -55,13 +58,38 @@ __global__ __launch_bounds__(kPairBlock) void k_pair_link(const double *__restri
     pl.link[i] = PairLink{cell, atomicExch(&pl.head[b], uint32_t(i)), b};
 }
 
+// The lists in ascending index: a particle's successor is the smallest index
+// above its own in its bucket.
+__global__ __launch_bounds__(kPairBlock) void k_pair_order(int32_t n, PairGrid pg, PairList pl) {
+    const uint32_t i = blockIdx.x * kPairBlock + threadIdx.x;
+    if (i >= uint32_t(n)) return;
+    const PairLink e = pl.link[i];
+    uint32_t next = kPairNone, hops = 0;
+    bool lowest = true;
+    for (uint32_t j = pl.head[e.bucket]; j != kPairNone && hops < pg.n; ++hops) {
+        lowest = lowest && j >= i;
+        if (j > i) next = min(next, j);
+        j = pl.link[j].next;
+    }
+    pl.sorted[i] = PairLink{e.cell, next, e.bucket};
+    if (lowest) pl.first[e.bucket] = i;
+}
+
 // A group of kPairLanes lanes serves one particle: lane l visits the l-th of
 // its (up to) 27 neighbour cells (offsets in x fastest, then y, z) and calls
 // fn(j, d, |d|^2) for every particle j != i of that cell within the cutoff,
 // d = r_i - r_j at the nearest image, in ascending j.
 constexpr int kPairLanes = 32;
 
-template <typename Fn>
+// Whether m particles of one cell cost more in walks over the links, m^2 / 4
+// dependent loads, than in one pass over all n particles, some in flight at a
+// time (a cluster among 4096 particles, us per step: 64 of them 213 in walks; 128
+// of them 731 in walks, 483 in one pass; 256 of them 1853 and 624).
+// Positions that are not finite all fall into one cell: without the bound a run
+// that diverges would walk n^2 / 4 links per particle.
+__device__ inline bool pair_cluster(uint32_t m, uint32_t n) { return uint64_t(m) * m > 2 * uint64_t(n); }
+
+template <bool ORDERED, typename Fn>
 __device__ inline void pair_cell_visit(const double *__restrict__ r, const PairGrid &pg,
                                        const PairList &pl, int32_t i, uint32_t l, Fn &&fn) {
     const double ri[3] = {r[3 * i + 0], r[3 * i + 1], r[3 * i + 2]};
@@ -78,44 +106,67 @@ __device__ inline void pair_cell_visit(const double *__restrict__ r, const PairG
     const double rc2 = pg.rc * pg.rc;
     const uint64_t cell = pair_cell(pg, q[0], q[1], q[2]);
     const uint32_t b = pair_bucket(cell, pg.T);
-    // the cell's particles in ascending index, kBatch of them per walk of the
-    // bucket's list (a cell holds one or two as a rule)
-    constexpr int kBatch = 4;
-    for (int64_t last = -1;;) {
-        uint32_t id[kBatch];
+    auto meet = [&](int32_t j) {
+        double d[3], rr = 0.0;
 #pragma unroll
-        for (int k = 0; k < kBatch; ++k) id[k] = kPairNone;
-        uint32_t found = 0;
+        for (int k = 0; k < 3; ++k) {
+            d[k] = ri[k] - r[3 * j + k];
+            d[k] -= pg.L[k] * rint(d[k] / pg.L[k]);
+            rr += d[k] * d[k];
+        }
+        if (rr > 0.0 && rr < rc2) fn(j, d, rr);
+    };
+    if constexpr (ORDERED) {
         uint32_t hops = 0;
-        for (uint32_t j = pl.head[b]; j != kPairNone && hops < pg.n; ++hops) {
-            const PairLink e = pl.link[j];
-            if (e.cell == cell && int64_t(j) > last) {
-                ++found;
-                uint32_t v = j;  // into the sorted batch, the largest drops out
+        for (uint32_t next = pl.first[b]; next != kPairNone && hops < pg.n; ++hops) {
+            const int32_t j = int32_t(next);
+            const PairLink e = pl.sorted[j];
+            next = e.next;
+            if (j != i && e.cell == cell) meet(j);
+        }
+    } else {
+        // kPairBatch of the cell's particles per walk of the bucket's list (a
+        // cell holds one or two as a rule)
+        for (int64_t last = -1;;) {
+            uint32_t id[kPairBatch];
 #pragma unroll
-                for (int k = 0; k < kBatch; ++k) {
-                    const uint32_t lo = min(id[k], v);
-                    v = max(id[k], v);
-                    id[k] = lo;
+            for (int k = 0; k < kPairBatch; ++k) id[k] = kPairNone;
+            uint32_t found = 0;
+            uint32_t hops = 0;
+            for (uint32_t j = pl.head[b]; j != kPairNone && hops < pg.n; ++hops) {
+                const PairLink e = pl.link[j];
+                if (e.cell == cell && int64_t(j) > last) {
+                    ++found;
+                    uint32_t v = j;  // into the sorted batch, the largest drops out
+#pragma unroll
+                    for (int k = 0; k < kPairBatch; ++k) {
+                        const uint32_t lo = min(id[k], v);
+                        v = max(id[k], v);
+                        id[k] = lo;
+                    }
                 }
+                j = e.next;
             }
-            j = e.next;
-        }
+            if (pair_cluster(found, pg.n)) {
+                constexpr uint32_t kAhead = 16;
+                for (uint32_t j0 = id[0]; j0 < pg.n; j0 += kAhead) {
+                    uint32_t hit = 0;
 #pragma unroll
-        for (int k = 0; k < kBatch; ++k) {
-            const int32_t j = int32_t(id[k]);
-            if (id[k] == kPairNone || j == i) continue;
-            double d[3], rr = 0.0;
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                d[c] = ri[c] - r[3 * j + c];
-                d[c] -= pg.L[c] * rint(d[c] / pg.L[c]);
-                rr += d[c] * d[c];
+                    for (uint32_t k = 0; k < kAhead; ++k)
+                        hit |= uint32_t(pl.link[min(j0 + k, pg.n - 1)].cell == cell && j0 + k < pg.n) << k;
+                    for (; hit; hit &= hit - 1) {
+                        const int32_t j = int32_t(j0) + __builtin_ctz(hit);
+                        if (j != i) meet(j);
+                    }
+                }
+                break;
             }
-            if (rr > 0.0 && rr < rc2) fn(j, d, rr);
+#pragma unroll
+            for (int k = 0; k < kPairBatch; ++k)
+                if (id[k] != kPairNone && int32_t(id[k]) != i) meet(int32_t(id[k]));
+            if (found <= uint32_t(kPairBatch)) break;
+            last = id[kPairBatch - 1];
         }
-        if (found <= uint32_t(kBatch)) break;
-        last = id[kBatch - 1];
     }
 }
 
@@ -128,6 +179,7 @@ __device__ inline double pair_group_sum(double v) {
 }
 
 // F[i] = sum over neighbours of a_f (1 - |d|/r_c) d/|d|.
+template <bool ORDERED>
 __global__ __launch_bounds__(kPairBlock) void k_pair_force(const double *__restrict__ r, int32_t n,
                                                            PairGrid pg, PairList pl,
                                                            double *__restrict__ F) {
@@ -136,7 +188,7 @@ __global__ __launch_bounds__(kPairBlock) void k_pair_force(const double *__restr
     if (i >= n) return;  // whole groups leave together
     double f[3] = {0.0, 0.0, 0.0};
     if (l < 27)
-        pair_cell_visit(r, pg, pl, i, l, [&](int32_t, const double (&d)[3], double rr) {
+        pair_cell_visit<ORDERED>(r, pg, pl, i, l, [&](int32_t, const double (&d)[3], double rr) {
             const double dist = sqrt(rr);
             const double mag = pg.a * (1.0 - dist / pg.rc) / dist;
 #pragma unroll
@@ -153,6 +205,7 @@ __global__ __launch_bounds__(kPairBlock) void k_pair_force(const double *__restr
 // neighbours of Jac(d) (Fb[i] - Fb[j]), Jac(d) = a_f [(1/|d| - 1/r_c) I -
 // d d^T / |d|^3] (the force of a pair is odd in d, its Jacobian even and
 // symmetric).
+template <bool ORDERED>
 __global__ __launch_bounds__(kPairBlock) void k_adj_pair(const double *__restrict__ r, int32_t n,
                                                          PairGrid pg, PairList pl,
                                                          const double *__restrict__ Fb,
@@ -163,7 +216,7 @@ __global__ __launch_bounds__(kPairBlock) void k_adj_pair(const double *__restric
     const double fi[3] = {Fb[3 * i + 0], Fb[3 * i + 1], Fb[3 * i + 2]};
     double g[3] = {0.0, 0.0, 0.0};
     if (l < 27)
-        pair_cell_visit(r, pg, pl, i, l, [&](int32_t j, const double (&d)[3], double rr) {
+        pair_cell_visit<ORDERED>(r, pg, pl, i, l, [&](int32_t j, const double (&d)[3], double rr) {
             const double dist = sqrt(rr);
             const double diag = pg.a * (1.0 / dist - 1.0 / pg.rc);
             const double outer = pg.a / (rr * dist);

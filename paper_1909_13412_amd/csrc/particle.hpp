@@ -424,7 +424,11 @@ __device__ inline void particle_lane(const ParticleSite<C> &site, Gather &gather
     pa.cells[8 * i + p] = my_cell;
 
     if (p != 0) return;
-    if (pa.pair_list.head) pa.pair_list.head[pa.pair_list.link[i].bucket] = kPairNone;
+    if (pa.pair_list.head) {
+        const uint32_t b = pa.pair_list.link[i].bucket;
+        pa.pair_list.head[b] = kPairNone;
+        pa.pair_list.first[b] = kPairNone;
+    }
     // Eqs. s2-langevin, s2-langevin2 with dt = 1; F_C is the given force (or 0).
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
