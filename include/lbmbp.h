@@ -124,13 +124,14 @@ typedef struct lbm_ctx lbm_ctx;
  * this many bytes. */
 lbm_status lbm_lattice_bytes(const lbm_grid_desc *grid, size_t *bytes);
 
-/* Bytes of grid scratch: three node-force fields (24 bytes per node each: the
+/* Bytes of grid scratch: two node-force fields (24 bytes per node each: the
  * reaction force of the first Eq. s2-force, section 2.1) with their one-bit
  * flags, reduction partials and flags. */
 lbm_status lbm_grid_scratch_bytes(const lbm_grid_desc *grid, size_t *bytes);
 
 /* Bytes of particle scratch for n particles (corner bookkeeping, last-step
- * forces, the pair-force cell list). */
+ * forces, the pair-force cell list; where so many particles take two-step
+ * sweeps in this box (lbm_step), a third node-force field). */
 lbm_status lbm_particle_scratch_bytes(const lbm_grid_desc *grid, int32_t n, size_t *bytes);
 
 /* Bytes of the VACF origin store for n particles: (max_lag/stride + 1) * n * 3

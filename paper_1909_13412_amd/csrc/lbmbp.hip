@@ -55,8 +55,9 @@ constexpr int kRedBlocks = 1024;
 // Node-force fields of a box: step n spreads into its own field, n mod 2.  A
 // two-step sweep reads the fields of both its steps, so neither can be cleared
 // before it, and the particle update that follows clears both: where the first
-// of them is that update's own field, it takes the third.  Two sweeps in a row
-// so end with the fields in the roles they started with, and an even number of
+// of them is that update's own field, it takes the third (kept by boxes whose
+// particles take two-step sweeps only: it is 24 bytes a node).  Two sweeps in a
+// row so end with the fields in the roles they started with, and an even number of
 // steps (the lattices' condition) can be captured into a graph and replayed.
 constexpr int kForceFields = 3;
 constexpr int kThirdField = 2;
@@ -320,7 +321,7 @@ struct lbm_ctx {
     double body[3];  // uniform body force on every node (lbm_set_body_force)
     // grid scratch
     uint32_t *mask[kForceFields];
-    long long *force[kForceFields];  // [ncell][3] fixed-point node forces
+    long long *force[kForceFields];  // [ncell][3] fixed-point node forces; the third in the particle scratch or null
     uint32_t mask_words;
     double *partials;
     double *result;
@@ -446,8 +447,8 @@ size_t fluid_partials_bytes(const lbm_grid_desc *g) {
 size_t grid_scratch_size(const lbm_grid_desc *g) {
     const size_t words = mask_words(ncell_of(g));
     size_t s = 0;
-    s += kForceFields * align_up(words * 4, kAlign);  // bitmasks
-    s += kForceFields * force_field_bytes(g);         // node-force fields
+    s += kThirdField * align_up(words * 4, kAlign);  // bitmasks
+    s += kThirdField * force_field_bytes(g);         // node-force fields
     s += fluid_partials_bytes(g);                    // recorded-moment partials
     s += align_up(size_t(kSeriesBlocks) * 7 * 8, kAlign);
     s += align_up(size_t(kRedBlocks) * 4 * 8, kAlign);  // partials
@@ -496,9 +497,38 @@ PairList pair_list_at(char *s, int32_t n) {
     return PairList{reinterpret_cast<PairLink *>(s), reinterpret_cast<PairLink *>(s + links), head, head + pair_buckets(n)};
 }
 
-size_t particle_scratch_size(int32_t n) {
+// Nodes per particle from which a two-step sweep pays for its particle update
+// one step ahead, which reads the populations around a 4^3 instead of a 2^3
+// neighbourhood (us per step in a run, two-step / single: FP32 128^3, 512 nodes
+// each 59.8 / 67.2, 304 nodes 73.0 / 73.6, FP64 111 / 127; 16-bit storage saves
+// less per sweep: BF16 256^3, 4096 nodes 198 / 222, 2048 nodes 232 / 231; 128^3
+// 4096 nodes 30.4 / 31.5, 2048 nodes 32.5 / 32.5, 512 nodes 47.7 / 38.1; 192^3
+// 6912 nodes 93.6 / 94.8, 3456 nodes 100 / 95.5), and nodes from which its
+// launch does (16 particles: BF16 96^3 18.7 / 18.2, 128^3 27.0 / 29.8; FP32 72^3
+// 14.6 / 15.7, but 60 recorded steps and their gradient at 64^3 3.66 / 3.56 ms).
+constexpr double two_step_nodes_per_particle(size_t elem) { return elem == 2 ? 4000.0 : 300.0; }
+constexpr uint64_t two_step_particle_nodes(size_t elem) { return elem == 2 ? uint64_t(1) << 21 : uint64_t(5) << 16; }
+
+bool two_step_pays(size_t elem, uint64_t nodes, int64_t particles) {
+    if (particles == 0) return true;
+    if (nodes < two_step_particle_nodes(elem)) return false;
+    return double(nodes) >= two_step_nodes_per_particle(elem) * double(particles);
+}
+
+// The sweep's byte offsets within a plane are of 32 bits.
+bool two_step_planes(const lbm_grid_desc *g) {
+    return uint64_t(g->nx) * uint64_t(g->ny) * uint64_t(velocity_count(g)) * elem_size(g->storage) < (uint64_t(1) << 32);
+}
+
+// Bytes of the third node-force field and its flags for n particles (0: none).
+size_t third_field_bytes(const lbm_grid_desc *g, int32_t n) {
+    if (!two_step_planes(g) || !two_step_pays(elem_size(g->storage), ncell_of(g), n)) return 0;
+    return align_up(size_t(mask_words(ncell_of(g))) * 4, kAlign) + force_field_bytes(g);
+}
+
+size_t particle_scratch_size(const lbm_grid_desc *g, int32_t n) {
     if (n <= 0) return 0;
-    size_t s = 0;
+    size_t s = third_field_bytes(g, n);
     s += 2 * align_up(size_t(n) * 8 * 4, kAlign);  // nodes spread to, two steps
     s += align_up(particle_blocks(n) * 3 * 8, kAlign);  // momentum partials
     s += 2 * align_up(size_t(n) * 3 * 8, kAlign);  // fh, fr
@@ -672,7 +702,7 @@ ParticleArgs step_particle_args(lbm_ctx *c) {
     // none where they have been released)
     pa.cells = c->cells[c->step & 1];
     pa.last_cells = c->cells[(c->step & 1) ^ 1];
-    pa.older_cells = pa.cells;
+    pa.older_cells = c->force[kThirdField] ? pa.cells : nullptr;
     pa.err = c->err;
     pa.n = c->np;
     pa.friction = c->pdesc.friction;
@@ -809,7 +839,7 @@ void launch_two_step(lbm_ctx *c) {
             launch_particle_ahead<C>(a, pa);
         prof_stop(c, pk);
         c->last_field = f1;
-        c->own_held = f0 != kThirdField;
+        c->own_held = f0 != kThirdField && c->pdesc.friction != LBM_FRICTION_BD;
     } else {
         c->step += 1;
     }
@@ -1040,7 +1070,7 @@ lbm_status lbm_grid_scratch_bytes(const lbm_grid_desc *grid, size_t *bytes) {
 
 lbm_status lbm_particle_scratch_bytes(const lbm_grid_desc *grid, int32_t n, size_t *bytes) {
     if (!grid_ok(grid) || !bytes || n < 0 || n > (1 << 24)) return LBM_E_INVAL;
-    *bytes = particle_scratch_size(n);
+    *bytes = particle_scratch_size(grid, n);
     return LBM_OK;
 }
 
@@ -1209,8 +1239,7 @@ void two_step_each_tile(uint32_t nx, uint32_t ny, size_t elem, Fn &&fn) {
 int two_step_candidates(const lbm_grid_desc *g, TwoStepTiles *out) {
     const uint32_t nx = uint32_t(g->nx), ny = uint32_t(g->ny), nz = uint32_t(g->nz);
     const size_t elem = elem_size(g->storage);
-    // 32-bit byte offsets within a plane
-    if (uint64_t(nx) * ny * uint64_t(velocity_count(g)) * elem >= (uint64_t(1) << 32)) return 0;
+    if (!two_step_planes(g)) return 0;
     struct Cand {
         TwoStepTiles tl;
         double cost;
@@ -1263,26 +1292,9 @@ TwoStepTiles two_step_tiles(const lbm_grid_desc *g, int &two) {
     return tl[two > 0 ? two - 1 : 0];
 }
 
-// Nodes per particle from which a two-step sweep pays for its particle update
-// one step ahead, which reads the populations around a 4^3 instead of a 2^3
-// neighbourhood (us per step in a run, two-step / single: FP32 128^3, 512 nodes
-// each 59.8 / 67.2, 304 nodes 73.0 / 73.6, FP64 111 / 127; 16-bit storage saves
-// less per sweep: BF16 256^3, 4096 nodes 198 / 222, 2048 nodes 232 / 231; 128^3
-// 4096 nodes 30.4 / 31.5, 2048 nodes 32.5 / 32.5, 512 nodes 47.7 / 38.1; 192^3
-// 6912 nodes 93.6 / 94.8, 3456 nodes 100 / 95.5), and nodes from which its
-// launch does (16 particles: BF16 96^3 18.7 / 18.2, 128^3 27.0 / 29.8; FP32 72^3
-// 14.6 / 15.7, but 60 recorded steps and their gradient at 64^3 3.66 / 3.56 ms).
-constexpr double two_step_nodes_per_particle(size_t elem) { return elem == 2 ? 4000.0 : 300.0; }
-constexpr uint64_t two_step_particle_nodes(size_t elem) { return elem == 2 ? uint64_t(1) << 21 : uint64_t(5) << 16; }
-
-bool two_step_pays(size_t elem, uint64_t nodes, int64_t particles) {
-    if (particles == 0) return true;
-    if (nodes < two_step_particle_nodes(elem)) return false;
-    return double(nodes) >= two_step_nodes_per_particle(elem) * double(particles);
-}
-
 bool two_step_pays(const lbm_ctx *c) {
-    return c->pdesc.friction == LBM_FRICTION_BD || two_step_pays(c->elem, c->g.ncell, c->np);
+    // (BD friction reads no fluid and spreads nothing: no update ahead, no fields)
+    return c->np == 0 || c->pdesc.friction == LBM_FRICTION_BD || c->force[kThirdField];
 }
 
 // The remembered code of a box holds, above the single-step launch, the
@@ -1357,11 +1369,11 @@ lbm_status lbm_init(const lbm_grid_desc *grid, void *pop_a, void *pop_b, void *g
     }
     char *s = static_cast<char *>(grid_scratch);
     c->mask_words = mask_words(c->g.ncell);
-    for (int k = 0; k < kForceFields; ++k) {
+    for (int k = 0; k < kThirdField; ++k) {
         c->mask[k] = reinterpret_cast<uint32_t *>(s);
         s += align_up(size_t(c->mask_words) * 4, kAlign);
     }
-    for (int k = 0; k < kForceFields; ++k) {
+    for (int k = 0; k < kThirdField; ++k) {
         c->force[k] = reinterpret_cast<long long *>(s);
         s += force_field_bytes(grid);
     }
@@ -1452,14 +1464,16 @@ lbm_status particles_couple(lbm_ctx *ctx, const lbm_particle_desc *d, double *r,
     // back to back: the masks, then the forces; lbm_init cleared them first).
     hipError_t e = hipSuccess;
     if (ctx->fields_used) {
-        e = hipMemsetAsync(ctx->mask[0], 0, kForceFields * align_up(size_t(ctx->mask_words) * 4, kAlign), ctx->stream);
+        e = hipMemsetAsync(ctx->mask[0], 0, kThirdField * align_up(size_t(ctx->mask_words) * 4, kAlign), ctx->stream);
         if (e == hipSuccess)
-            e = hipMemsetAsync(ctx->force[0], 0, kForceFields * force_field_bytes(&ctx->desc), ctx->stream);
+            e = hipMemsetAsync(ctx->force[0], 0, kThirdField * force_field_bytes(&ctx->desc), ctx->stream);
         if (e != hipSuccess) return LBM_E_DEVICE;
     }
     ctx->fields_used = 0;
     ctx->last_field = int(ctx->step & 1) ^ 1;
     ctx->own_held = 0;
+    ctx->mask[kThirdField] = nullptr;
+    ctx->force[kThirdField] = nullptr;
     ctx->vacf_on = 0;
     ctx->fext = nullptr;
     ctx->pair_on = 0;
@@ -1490,6 +1504,13 @@ lbm_status particles_couple(lbm_ctx *ctx, const lbm_particle_desc *d, double *r,
     ctx->plist = pair_list_at(s, d->n);
     s += pair_list_bytes(d->n);
     ctx->fpair = reinterpret_cast<double *>(s);
+    s += align_up(size_t(d->n) * 3 * 8, kAlign);
+    if (const size_t third = third_field_bytes(&ctx->desc, d->n)) {
+        ctx->mask[kThirdField] = reinterpret_cast<uint32_t *>(s);
+        ctx->force[kThirdField] = reinterpret_cast<long long *>(s + align_up(size_t(ctx->mask_words) * 4, kAlign));
+        e = hipMemsetAsync(s, 0, third, ctx->stream);
+        if (e != hipSuccess) return LBM_E_DEVICE;
+    }
     // nodes spread to -> kNoNode (all ones), list heads -> none; forces zero.
     e = hipMemsetAsync(ctx->cells[0], 0xFF, 2 * align_up(size_t(d->n) * 8 * 4, kAlign), ctx->stream);
     if (e == hipSuccess && d->n <= kPairMax)
@@ -2048,8 +2069,9 @@ struct EnsLayout {
     uint64_t total_cells = 0, total_pop = 0, total_mask_words = 0;
     uint32_t total_blocks[kNumGeomShapes] = {0, 0, 0, 0};
     uint32_t two_blocks = 0, two_threads = 0;  // two-step sweep
-    bool two_ok = true;                        // every box has tiles for it
+    bool two_ok = true;                        // every box has tiles for it, and it pays
     std::vector<TwoStepTiles> two;             // per box
+    int fields = 0;                            // node-force fields
     int32_t n = 0;
     size_t lattice_bytes = 0, scratch_bytes = 0;
     // scratch offsets
@@ -2105,6 +2127,7 @@ EnsLayout ens_layout(const lbm_ensemble_desc *d, const lbm_replica_desc *reps) {
         L.two_blocks += tl.ntx * tl.nty * tl.nslab;
         L.two_threads = std::max(L.two_threads, two_step_threads(tl));
     }
+    L.two_ok = L.two_ok && ens_two_step_pays(elem, L.total_cells, L.n);
     L.lattice_bytes = align_up(L.total_pop * elem, kAlign);
     size_t o = 0;
     L.o_reps = o;
@@ -2117,11 +2140,12 @@ EnsLayout ens_layout(const lbm_ensemble_desc *d, const lbm_replica_desc *reps) {
     o += align_up(size_t(L.two_blocks) * 2, kAlign);
     L.o_part = o;
     o += align_up(size_t(L.n) * 2, kAlign);
-    for (int k = 0; k < kForceFields; ++k) {
+    L.fields = L.two_ok ? kForceFields : kThirdField;
+    for (int k = 0; k < L.fields; ++k) {
         L.o_mask[k] = o;
         o += align_up(L.total_mask_words * 4, kAlign);
     }
-    for (int k = 0; k < kForceFields; ++k) {
+    for (int k = 0; k < L.fields; ++k) {
         L.o_force[k] = o;
         o += align_up(L.total_cells * 3 * 8, kAlign);
     }
@@ -2144,9 +2168,6 @@ EnsLayout ens_layout(const lbm_ensemble_desc *d, const lbm_replica_desc *reps) {
     L.scratch_bytes = o;
     return L;
 }
-
-// Every box has tiles, and the block table's first block numbers fit.
-bool ens_two_possible(const EnsLayout &L) { return L.two_ok && L.two_blocks > 0; }
 
 ParticleArgs ens_particle_args(lbm_ens *e) {
     ParticleArgs pa;
@@ -2195,7 +2216,7 @@ void ens_collide_shape(lbm_ens *e, const typename C::T *A, typename C::T *B, con
 
 // The particle update of step n (`ahead` steps after the device clock), and the
 // nodes it has to release: those of the last two steps.  held: the step's own
-// field is one of them (kForceFields), it spreads into the third.
+// field is one of them, it spreads into the third.
 template <class C>
 void ens_launch_particle(lbm_ens *e, const typename C::T *A, int64_t n, int ahead, bool held) {
     const int own = int(n & 1);
@@ -2203,7 +2224,7 @@ void ens_launch_particle(lbm_ens *e, const typename C::T *A, int64_t n, int ahea
     pa.cells = e->cells[own];
     if (!ahead) {
         pa.last_cells = e->cells[own ^ 1];
-        pa.older_cells = pa.cells;
+        pa.older_cells = e->two_possible ? pa.cells : nullptr;
     }
     hipLaunchKernelGGL(k_ens_particle<C>, dim3(unsigned(particle_blocks(e->n))), dim3(particle_threads(pa)), 0, e->stream, A,
                        e->reps, e->part_rep, typename C::R(e->dec_s), pa, e->clock, ahead,
@@ -2545,8 +2566,8 @@ lbm_status lbm_ens_init(const lbm_ensemble_desc *desc, const lbm_replica_desc *r
         // applied to every box below (the rest state is all zeros)
         e->rows = 1 << ((code / (kNumShapes * int(kNumOrders) * kNumCaps)) % (kMaxRowsLog2 + 1));
         const int two = code / kTuneTwo;  // remembered two-step choice + 1, 0: none
-        e->two_possible = ens_two_possible(L);
-        e->two = e->two_possible && (two > 0 ? two - 1 > 0 : ens_two_step_pays(elem_size(desc->storage), L.total_cells, L.n));
+        e->two_possible = L.two_ok;
+        e->two = e->two_possible && (two == 0 || two - 1 > 0);
         e->two_nts = L.lattice_bytes >= kTwoStepStreamBytes;
         int v = 0;
         e->lds_cu = (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor,
@@ -2564,7 +2585,7 @@ lbm_status lbm_ens_init(const lbm_ensemble_desc *desc, const lbm_replica_desc *r
     e->two_rep = reinterpret_cast<uint16_t *>(base + L.o_two);
     e->two_blocks = L.two_blocks;
     e->two_threads = L.two_threads;
-    for (int k = 0; k < kForceFields; ++k) {
+    for (int k = 0; k < L.fields; ++k) {
         e->mask[k] = reinterpret_cast<uint32_t *>(base + L.o_mask[k]);
         e->force[k] = reinterpret_cast<long long *>(base + L.o_force[k]);
     }
@@ -2823,7 +2844,7 @@ lbm_status lbm_ens_autotune(lbm_ens *e, int32_t iters, double *ms, int32_t *chos
         const double one = ens_time_launch(e, best.k, best.o, best.c, 2 * iters, e0, e1);
         const double both = ens_time_two_steps(e, 2 * iters, e0, e1);
         ok = one > 0.0 && both > 0.0;
-        two = ok && both < 2.0 * one && ens_two_step_pays(e->elem, e->total_cells, e->n);
+        two = ok && both < 2.0 * one;
     }
     if (ok) {
         err = hipMemcpyAsync(e->clock, &saved, sizeof(saved), hipMemcpyHostToDevice, e->stream);

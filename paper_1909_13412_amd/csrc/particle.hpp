@@ -32,8 +32,9 @@ struct ParticleArgs {
     double *r_out, *v_out;  // and after it (may be r and v)
     double *fh, *fr;
     uint32_t *cells;  // [n][8] out: node each lane spread to this step, or kNoNode
-    // [n][8] nodes spread to in the last step, kNoNode once released, and in the
-    // one before (nullptr: nothing to release there); either may be `cells` itself
+    // [n][8] nodes spread to in the last step and in the one before (nullptr:
+    // nothing to release there), either may be `cells` itself; where the one
+    // before is released too, an entry is kNoNode from its release on
     uint32_t *last_cells;
     const uint32_t *older_cells;
     uint32_t *err;
@@ -312,7 +313,7 @@ __device__ inline void particle_lane(const ParticleSite<C> &site, Gather &gather
     if (valid && pa.older_cells) release_node(site.older, pa.older_cells[8 * i + p]);
     if (valid && pa.last_cells) {
         release_node(site.last, pa.last_cells[8 * i + p]);
-        pa.last_cells[8 * i + p] = kNoNode;
+        if (pa.older_cells) pa.last_cells[8 * i + p] = kNoNode;
     }
     const uint32_t Ln[3] = {g.nx, g.ny, g.nz};
     const int b[3] = {p & 1, (p >> 1) & 1, (p >> 2) & 1};
