@@ -356,7 +356,9 @@ lbm_status lbm_profile_read(lbm_ctx *ctx, double out[4]);
  * 256 MiB keep plain stores (the trials find such a lattice in the last-level
  * cache, a run does not); the non-temporal configurations are timed for ms
  * only.  Then up to six tilings of the two-step sweep are timed against two
- * launches of that choice.  Synchronises the stream.
+ * launches of that choice, each launch with the lattices left in that cache as
+ * a run leaves them (boxes of 2^16 nodes and more, 16-bit storage 2^19).
+ * Synchronises the stream.
  * ms (host, LBM_NUM_SHAPES entries, may be NULL) receives per configuration
  * the best mean milliseconds per launch over the options timed with it (-1
  * for a configuration that does not apply, or that repeats another's lane

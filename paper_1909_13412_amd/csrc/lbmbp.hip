@@ -947,26 +947,75 @@ void time_stream_only(lbm_ctx *c, int k, int32_t iters, double *ms, hipError_t *
     (void)hipEventDestroy(e1);
 }
 
-// Mean time per two-step sweep with these tiles and store policy over iters
-// launches (A -> B, as time_launches).
-template <class C>
-void time_two_steps(lbm_ctx *c, const TwoStepTiles &tl, bool nts, int32_t iters, double *ms, hipError_t *err) {
-    const ForceField last = field(c, c->last_field);
-    const TwoStepArgs a = two_step_args(c, tl, nts, last, last);
+// Leaves lattice A (unchanged) and the other lattice in the last-level cache as a
+// step's sweep does that wrote A and read the other: 16-byte words, n of each.
+__global__ __launch_bounds__(kBlock) void k_as_in_a_run(void *A, const void *other, size_t n, int nts) {
+    typedef uint32_t word __attribute__((ext_vector_type(4)));
+    for (size_t i = size_t(blockIdx.x) * kBlock + threadIdx.x; i < n; i += size_t(gridDim.x) * kBlock) {
+        word a = static_cast<word *>(A)[i];
+        const word b = static_cast<const word *>(other)[i];
+        asm volatile("" : "+v"(a) : "v"(b));  // both are loaded
+        if (nts)
+            __builtin_nontemporal_store(a, static_cast<word *>(A) + i);
+        else
+            static_cast<word *>(A)[i] = a;
+    }
+}
+
+// Mean ms of a sweep A -> B launched by `launch`, each after the lattices (bytes
+// each) have been left as in a run.  Trials that launch the same sweep over and
+// over read from the last-level cache what a run has written past it: by those
+// 16-bit 192^3 (256 MiB) took single steps, 0.129 against 0.143 ms, which a run
+// does in 0.187 and 0.142.  Lattices beyond four times that cache need no such
+// care.
+template <typename Launch>
+double time_as_in_a_run(hipStream_t st, void *A, const void *B, size_t bytes, bool nts, int32_t iters, Launch &&launch,
+                        hipError_t *err) {
     hipEvent_t e0, e1;
     *err = hipEventCreate(&e0);
-    if (*err == hipSuccess) *err = hipEventCreate(&e1);
-    if (*err != hipSuccess) return;
-    for (int w = 0; w < 2; ++w) launch_two_steps<C>(a);
-    (void)hipEventRecord(e0, c->stream);
-    for (int it = 0; it < iters; ++it) launch_two_steps<C>(a);
-    (void)hipEventRecord(e1, c->stream);
-    *err = hipEventSynchronize(e1);
-    float t = 0.0f;
-    if (*err == hipSuccess) *err = hipEventElapsedTime(&t, e0, e1);
-    *ms = double(t) / iters;
+    if (*err != hipSuccess) return -1.0;
+    *err = hipEventCreate(&e1);
+    if (*err != hipSuccess) {
+        (void)hipEventDestroy(e0);
+        return -1.0;
+    }
+    double sum = 0.0;
+    for (int32_t it = -2; it < iters && *err == hipSuccess; ++it) {
+        if (bytes < 4 * kStreamStoreBytes)
+            hipLaunchKernelGGL(k_as_in_a_run, dim3(2048), dim3(kBlock), 0, st, A, B, bytes / 16, int(nts));
+        (void)hipEventRecord(e0, st);
+        launch();
+        (void)hipEventRecord(e1, st);
+        *err = hipEventSynchronize(e1);
+        float t = 0.0f;
+        if (*err == hipSuccess) *err = hipEventElapsedTime(&t, e0, e1);
+        if (it >= 0) sum += double(t);
+    }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
+    return sum / iters;
+}
+
+// Mean ms of two single steps of the context's configuration (tl null), or of one
+// two-step sweep with these tiles, as in a run.
+template <class C>
+void time_two_steps(lbm_ctx *c, const TwoStepTiles *tl, int32_t iters, double *ms, hipError_t *err) {
+    size_t bytes = 0;
+    lbm_lattice_bytes(&c->desc, &bytes);
+    const ForceField last = field(c, c->last_field);
+    void *A = c->pop[c->cur], *B = c->pop[c->cur ^ 1];
+    if (tl) {
+        const TwoStepArgs a = two_step_args(c, *tl, c->two_nts != 0, last, last);
+        *ms = time_as_in_a_run(c->stream, A, B, bytes, c->two_nts != 0, iters, [&] { launch_two_steps<C>(a); }, err);
+    } else {
+        using T = typename C::T;
+        *ms = 2.0 * time_as_in_a_run(c->stream, A, B, bytes, config_nts(c->shape), iters, [&] {
+            if (c->np > 0)
+                launch_collide<C, true>(c, static_cast<const T *>(A), static_cast<T *>(B), last, c->shape);
+            else
+                launch_collide<C, false>(c, static_cast<const T *>(A), static_cast<T *>(B), last, c->shape);
+        }, err);
+    }
 }
 
 template <class C>
@@ -1193,11 +1242,11 @@ lbm_status set_layout(lbm_ctx *c, uint32_t Y) {
 // two steps on the busiest of the compute unit's four SIMDs, plus the 128-byte
 // lines that its row pieces touch; blocks run one per compute unit (the LDS and
 // registers of a block this size allow no second one), so whole rounds of 256
-// count.  The weights minimise the time of the model's first choice over 31
-// boxes of every storage, 33 to 512 nodes long, some six tiles measured in
-// each: 1.5% above the fastest tile on average, 7% at most (F16 D3Q15 201 x 150
-// x 117: 51 x 10 tiles 0.065 ms, 101 x 6 0.076).  lbm_autotune times the first
-// six.
+// count.  In runs of 55 boxes of every storage, 40 to 320 nodes long, the model's
+// first choice takes 2.5% more than the fastest of its first six on average, and
+// 14% at most (FP32 56^3 11.7 and 10.3 us a sweep; of the boxes that take such
+// sweeps untuned BF16 130 x 129 x 130 50.8 and 45.3, F16 D3Q15 250 x 130 x 77 47.9
+// and 43.3).  lbm_autotune times those six.
 constexpr int kTwoStepCandidates = 6;
 
 double two_step_plane_cost(uint32_t tx, uint32_t ty, size_t elem) {
@@ -1274,16 +1323,21 @@ constexpr size_t kTwoStepStreamBytes = size_t(128) << 20;
 
 // Boxes of fewer nodes than this take single steps until tuned: a block's two
 // planes of start are too large a part of its slab (us per step in a run, two-
-// step / single: FP32 64^3 5.8 / 7.0, 80^3 8.8 / 12.0; FP64 64^3 10.9 / 12.3; FP32
-// 56^3 tunes to single steps; BF16 72^3 and 80^3 likewise, 96^3 11.3 / 12.5).
+// step / single: FP32 64^3 5.8 / 7.0, 80^3 8.8 / 12.0; FP64 64^3 10.9 / 12.3; BF16
+// 72^3 7.5 / 6.6, 96^3 11.3 / 12.5).
 constexpr uint64_t two_step_min_nodes(size_t elem) { return uint64_t(1) << (elem == 2 ? 19 : 18); }
 
 bool two_step_by_size(const lbm_grid_desc *g) { return ncell_of(g) >= two_step_min_nodes(elem_size(g->storage)); }
 
-// Of two single steps' time, what a trial of the two-step sweep may take on a
-// lattice within the last-level cache: in boxes of that size and more (the
-// trials' error measured up to 1.3), and in smaller ones.
-constexpr double kTwoStepCached = 1.5, kTwoStepGain = 0.9;
+// Boxes in which lbm_autotune tries the two-step sweep.  In smaller ones a launch
+// is a few us of latency, which trials do not tell apart (two steps in a run /
+// by trial, us, single and two-step: BF16 64^3 10.0 and 12.1 / 19.7 and 14.6, 72^3
+// 13.1 and 14.5 / 25.2 and 17.1; but FP32 48^3 11.3 and 9.4 / 18.6 and 13.5, FP64
+// 48^3 16.3 and 12.9 / 19.1 and 15.4).  In 45 larger ones the trials' choice was the
+// run's fastest or within 4.6% of it.
+bool two_step_trial(const lbm_grid_desc *g) {
+    return ncell_of(g) >= (elem_size(g->storage) == 2 ? two_step_min_nodes(2) : uint64_t(1) << 16);
+}
 
 // The tiles of choice `two` (1: the model's first); 0 where the box has none.
 TwoStepTiles two_step_tiles(const lbm_grid_desc *g, int &two) {
@@ -1826,26 +1880,20 @@ lbm_status lbm_autotune(lbm_ctx *ctx, int32_t iters, double *ms, int32_t *chosen
     ctx->order = best.o;
     ctx->cap = best.c;
     // Two-step sweep: the fastest of its tiles, if two steps in it are faster
-    // than two launches of the choice above.  A lattice that the trials read
-    // from the last-level cache favours the single steps, which read twice as
-    // much: boxes large enough for two-step sweeps untuned keep them (FP16
-    // D3Q19 160^3 51 us per step in a run, 59 in single steps that the trials
-    // put first), smaller ones need a clear gain.
+    // than two launches of the choice above.
     {
         TwoStepTiles tl[kTwoStepCandidates];
-        const int nt = two_step_candidates(&ctx->desc, tl);
-        double two_best = total[jb];  // two timings of one step each
-        if (lat < kStreamStoreBytes)
-            two_best *= two_step_by_size(&ctx->desc) ? kTwoStepCached : kTwoStepGain;
+        const int nt = two_step_trial(&ctx->desc) ? two_step_candidates(&ctx->desc, tl) : 0;
+        double two_best = 0.0;
         ctx->two = 0;
-        for (int j = 0; j < nt; ++j) {
+        for (int j = 0; j <= nt; ++j) {
             double v = 0.0;
-            LBM_DISPATCH(ctx, time_two_steps, tl[j], ctx->two_nts != 0, iters, &v, &err);
+            if (nt > 0) LBM_DISPATCH(ctx, time_two_steps, j > 0 ? &tl[j - 1] : nullptr, iters, &v, &err);
             if (err != hipSuccess || launch_status() != LBM_OK) return LBM_E_DEVICE;
-            if (v > 0.0 && v < two_best) {
+            if (j == 0 || (v > 0.0 && v < two_best)) {
                 two_best = v;
-                ctx->two = j + 1;
-                ctx->two_tiles = tl[j];
+                ctx->two = j;
+                if (j > 0) ctx->two_tiles = tl[j - 1];
             }
         }
     }
@@ -2471,21 +2519,6 @@ void ens_two_steps_any(lbm_ens *e, const EnsTwoStepArgs &a) {
     }
 }
 
-// Mean ms per two-step sweep (A -> B, as ens_time_launch).
-double ens_time_two_steps(lbm_ens *e, int32_t iters, hipEvent_t e0, hipEvent_t e1) {
-    const ForceField last = ens_field(e, (e->step + 1) & 1);
-    const EnsTwoStepArgs a = ens_two_step_args(e, e->cur, last, last);
-    for (int w = 0; w < 2; ++w) ens_two_steps_any(e, a);
-    (void)hipEventRecord(e0, e->stream);
-    for (int32_t it = 0; it < iters; ++it) ens_two_steps_any(e, a);
-    (void)hipEventRecord(e1, e->stream);
-    float f = 0.0f;
-    if (hipEventSynchronize(e1) != hipSuccess || hipEventElapsedTime(&f, e0, e1) != hipSuccess ||
-        launch_status() != LBM_OK)
-        return -1.0;
-    return double(f) / iters;
-}
-
 // Mean ms per launch of configuration k with block order o and cap c over
 // iters launches (after two unrecorded ones); < 0 on a device error.
 double ens_time_launch(lbm_ens *e, int k, int o, int c, int32_t iters, hipEvent_t e0, hipEvent_t e1) {
@@ -2841,9 +2874,16 @@ lbm_status lbm_ens_autotune(lbm_ens *e, int32_t iters, double *ms, int32_t *chos
     // Two-step sweeps, if two steps in one are faster than two of that launch.
     int two = 0;
     if (ok && e->two_possible) {
-        const double one = ens_time_launch(e, best.k, best.o, best.c, 2 * iters, e0, e1);
-        const double both = ens_time_two_steps(e, 2 * iters, e0, e1);
-        ok = one > 0.0 && both > 0.0;
+        void *A = e->pop[e->cur], *B = e->pop[e->cur ^ 1];
+        const ForceField last = ens_field(e, (e->step + 1) & 1);
+        const EnsTwoStepArgs a = ens_two_step_args(e, e->cur, last, last);
+        hipError_t st = hipSuccess;
+        const double one = time_as_in_a_run(e->stream, A, B, lat, config_nts(best.k), 2 * iters,
+                                            [&] { ens_time_any(e, best.k, best.o, best.c); }, &st);
+        ok = st == hipSuccess;
+        double both = -1.0;
+        if (ok) both = time_as_in_a_run(e->stream, A, B, lat, a.nts, 2 * iters, [&] { ens_two_steps_any(e, a); }, &st);
+        ok = st == hipSuccess && launch_status() == LBM_OK && one > 0.0 && both > 0.0;
         two = ok && both < 2.0 * one;
     }
     if (ok) {
