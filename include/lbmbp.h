@@ -556,10 +556,15 @@ lbm_status lbm_ens_step(lbm_ens *ens, int32_t nsteps);
  * residency caps (lbm_ens_set_sweep_launch) of the two fastest in the best
  * layout, and keep the fastest launch in the same four stages as
  * lbm_autotune (ensembles below 256 MiB with plain stores), and two-step
- * sweeps if they are faster than two such launches.  The choice is remembered for ensembles created later on the
- * same device with the same storage and the same box sizes in the same
- * order, which start from it. */
+ * sweeps if they are faster than two such launches.  The choice is remembered
+ * for ensembles created later on the same device with the same storage and the
+ * same box sizes in the same order, which start from it (two-step sweeps where
+ * the later one's particles are few enough for them). */
 lbm_status lbm_ens_autotune(lbm_ens *ens, int32_t iters, double *ms, int32_t *chosen);
+
+/* 1 if lbm_ens_step takes steps two per sweep where it can (of these boxes and
+ * particles, or by lbm_ens_autotune), 0 if one at a time. */
+lbm_status lbm_ens_get_two_step(const lbm_ens *ens, int32_t *two);
 
 /* Block order and residency cap of the ensemble's stream-collide, as
  * lbm_set_sweep_launch: the same node updates whatever the choice (the block

@@ -2901,10 +2901,18 @@ lbm_status lbm_ens_autotune(lbm_ens *e, int32_t iters, double *ms, int32_t *chos
     e->order = best.o;
     e->cap = best.c;
     e->two = two;
-    tune_store(ens_tune_key(e), tune_code(best.k, best.o, best.c, best.l) + kTuneTwo * (two + 1));
+    // the trial's outcome; nothing of it where these particles leave no choice
+    tune_store(ens_tune_key(e),
+               tune_code(best.k, best.o, best.c, best.l) + (e->two_possible ? kTuneTwo * (two + 1) : 0));
     if (ms)
         for (int k = 0; k < kNumShapes; ++k) ms[k] = best_k[k];
     if (chosen) *chosen = best.k;
+    return LBM_OK;
+}
+
+lbm_status lbm_ens_get_two_step(const lbm_ens *e, int32_t *two) {
+    if (!e || !two) return LBM_E_INVAL;
+    *two = e->two;
     return LBM_OK;
 }
 

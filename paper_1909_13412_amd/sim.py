@@ -500,6 +500,13 @@ class Ensemble(_StreamOrder):
             self.ctx, int(iters), ms.ctypes.data_as(ctypes.POINTER(ctypes.c_double)), ctypes.byref(chosen)))
         return chosen.value, ms
 
+    @property
+    def two_step(self) -> bool:
+        """Whether steps are taken two per sweep (see lbm_ens_get_two_step)."""
+        two = ctypes.c_int32()
+        _abi.check("lbm_ens_get_two_step", self.lib.lbm_ens_get_two_step(self.ctx, ctypes.byref(two)))
+        return bool(two.value)
+
     def stream_ceiling(self, iters: int = 20, config: int = -1) -> float:
         """Milliseconds per launch of the ensemble stream-collide's data movement
         alone in launch configuration `config` (-1: the current one); state
