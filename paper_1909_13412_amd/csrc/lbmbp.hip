@@ -506,13 +506,18 @@ PairList pair_list_at(char *s, int32_t n) {
 // 6912 nodes 93.6 / 94.8, 3456 nodes 100 / 95.5), and nodes from which its
 // launch does (16 particles: BF16 96^3 18.7 / 18.2, 128^3 27.0 / 29.8; FP32 72^3
 // 14.6 / 15.7, but 60 recorded steps and their gradient at 64^3 3.66 / 3.56 ms).
-constexpr double two_step_nodes_per_particle(size_t elem) { return elem == 2 ? 4000.0 : 300.0; }
+// 16-bit D3Q15 needs more: its single step moves a fifth less, its sweep with
+// forces spills as D3Q19's (256^3, 16384 nodes each and more 165-175 / 165-175,
+// 4096 nodes 195 / 178; 192^3, 6912 nodes 89 / 83; 128^3, 4096 nodes 28.6 / 27.5).
+constexpr double two_step_nodes_per_particle(size_t elem, int q) {
+    return elem == 2 ? (q == D3Q15::Q ? 32768.0 : 4000.0) : 300.0;
+}
 constexpr uint64_t two_step_particle_nodes(size_t elem) { return elem == 2 ? uint64_t(1) << 21 : uint64_t(5) << 16; }
 
-bool two_step_pays(size_t elem, uint64_t nodes, int64_t particles) {
+bool two_step_pays(size_t elem, int q, uint64_t nodes, int64_t particles) {
     if (particles == 0) return true;
     if (nodes < two_step_particle_nodes(elem)) return false;
-    return double(nodes) >= two_step_nodes_per_particle(elem) * double(particles);
+    return double(nodes) >= two_step_nodes_per_particle(elem, q) * double(particles);
 }
 
 // The sweep's byte offsets within a plane are of 32 bits.
@@ -522,7 +527,7 @@ bool two_step_planes(const lbm_grid_desc *g) {
 
 // Bytes of the third node-force field and its flags for n particles (0: none).
 size_t third_field_bytes(const lbm_grid_desc *g, int32_t n) {
-    if (!two_step_planes(g) || !two_step_pays(elem_size(g->storage), ncell_of(g), n)) return 0;
+    if (!two_step_planes(g) || !two_step_pays(elem_size(g->storage), velocity_count(g), ncell_of(g), n)) return 0;
     return align_up(size_t(mask_words(ncell_of(g))) * 4, kAlign) + force_field_bytes(g);
 }
 
@@ -2112,7 +2117,7 @@ TwoStepTiles ens_two_tiles(const lbm_replica_desc &r, size_t elem, uint64_t tota
 // to 48 nodes FP32 601 / 596, FP64 1221 / 1144, BF16 565 / 413; 40 such boxes
 // FP32 1236 / 1469, 64 BF16 1516 / 1525; 40 of 48 to 96 BF16 3520 / 4048).
 bool ens_two_step_pays(size_t elem, uint64_t nodes, int64_t particles) {
-    return nodes >= uint64_t(1) << (elem == 2 ? 22 : 21) && two_step_pays(elem, nodes, particles);
+    return nodes >= uint64_t(1) << (elem == 2 ? 22 : 21) && two_step_pays(elem, D3Q19::Q, nodes, particles);
 }
 
 struct EnsLayout {

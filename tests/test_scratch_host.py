@@ -5,11 +5,11 @@ import ctypes
 import pytest
 
 
-def _sizes(box, storage, n):
+def _sizes(box, storage, n, q=19):
     from paper_1909_13412_amd import _abi
 
     lib = _abi.load()
-    g = _abi.GridDesc(*box, 0.8, _abi.STORAGE[storage], 16, 19, 0)
+    g = _abi.GridDesc(*box, 0.8, _abi.STORAGE[storage], 16, q, 0)
     grid, part = ctypes.c_size_t(), ctypes.c_size_t()
     assert lib.lbm_grid_scratch_bytes(ctypes.byref(g), ctypes.byref(grid)) == 0
     assert lib.lbm_particle_scratch_bytes(ctypes.byref(g), n, ctypes.byref(part)) == 0
@@ -31,6 +31,13 @@ def test_two_node_force_fields_and_a_third_where_it_is_used(box, storage, n, thi
     assert 2 * field <= grid < 2 * field + cells + 1000000
     assert (part >= field) == third
     assert part < 400 * n + (field + 1000000 if third else 0) + 1
+
+
+@pytest.mark.parametrize("storage,n,third", [("f16", 4096, False), ("bf16", 4096, False), ("bf16", 400, True),
+                                             ("f32", 4096, True)])
+def test_sixteen_bit_fifteen_velocities_take_two_step_sweeps_with_few_particles_only(storage, n, third):
+    _, part = _sizes((256, 256, 256), storage, n, q=15)
+    assert (part >= 24 * 256**3) == third
 
 
 @pytest.mark.parametrize("n,third", [(8, True), (100000, False)])
