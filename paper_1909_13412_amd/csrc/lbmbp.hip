@@ -2127,6 +2127,13 @@ struct EnsLayout {
     bool two_ok = true;                        // every box has tiles for it, and it pays
     std::vector<TwoStepTiles> two;             // per box
     int fields = 0;                            // node-force fields
+    // Rows of whole 32-byte sectors in boxes of half the nodes and more: the sweep
+    // stores non-temporally (ms per 16 steps, plain / non-temporal: 64 FP32 boxes
+    // of 48 to 96 8.79 / 8.41, 100 of 48 3.62 / 3.54, BF16 2.93 / 2.85; but 40 FP32
+    // boxes of 66 3.87 / 4.49, 80 of 50 3.34 / 3.47, 64 of 33, 50, 64 and 70 4.03 / 4.16;
+    // 80 FP64 boxes of 50 6.34 / 6.58).  A tile of a small box is whole rows, so
+    // that rows need not be whole lines.
+    bool two_stream = false;
     int32_t n = 0;
     size_t lattice_bytes = 0, scratch_bytes = 0;
     // scratch offsets
@@ -2170,6 +2177,7 @@ EnsLayout ens_layout(const lbm_ensemble_desc *d, const lbm_replica_desc *reps) {
         }
         L.n += r.n;
     }
+    uint64_t sector_cells = 0;
     std::map<std::tuple<int32_t, int32_t, int32_t>, TwoStepTiles> tiles;
     L.two.reserve(size_t(d->nrep));
     for (int32_t k = 0; k < d->nrep; ++k) {
@@ -2180,8 +2188,10 @@ EnsLayout ens_layout(const lbm_ensemble_desc *d, const lbm_replica_desc *reps) {
         L.two.push_back(tl);
         L.two_ok = L.two_ok && tl.lz > 0;
         L.two_blocks += tl.ntx * tl.nty * tl.nslab;
+        if (size_t(r.nx) * elem % 32 == 0) sector_cells += uint64_t(r.nx) * uint64_t(r.ny) * uint64_t(r.nz);
         L.two_threads = std::max(L.two_threads, two_step_threads(tl));
     }
+    L.two_stream = 2 * sector_cells >= L.total_cells;
     L.two_ok = L.two_ok && ens_two_step_pays(elem, L.total_cells, L.n);
     L.lattice_bytes = align_up(L.total_pop * elem, kAlign);
     size_t o = 0;
@@ -2608,7 +2618,7 @@ lbm_status lbm_ens_init(const lbm_ensemble_desc *desc, const lbm_replica_desc *r
         const int two = code / kTuneTwo;  // remembered two-step choice + 1, 0: none
         e->two_possible = L.two_ok;
         e->two = e->two_possible && (two == 0 || two - 1 > 0);
-        e->two_nts = L.lattice_bytes >= kTwoStepStreamBytes;
+        e->two_nts = L.lattice_bytes >= kTwoStepStreamBytes && L.two_stream;
         int v = 0;
         e->lds_cu = (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor,
                                            e->device) == hipSuccess) ? v : 0;
