@@ -1,0 +1,163 @@
+"""The two-step sweep where its store policy, tiles and layouts differ from the
+small boxes': lattices of 128 MiB and more (non-temporal stores on rows of whole
+lines, plain ones elsewhere), row groups, the tuner's tilings, the headline box,
+non-finite values.  Every bit against the same steps taken one at a time."""
+import warnings
+
+import numpy as np
+import pytest
+
+from helpers import announce
+
+
+def _lattice(box, storage, q, n, *, friction="stokeslet", body=True, rows=1, tune=False, vacf=False, seed=11):
+    from paper_1909_13412_amd import Lattice
+    from paper_1909_13412_amd.inputs import particle_positions, particle_velocities, perturbed_fields
+
+    lat = Lattice(*box, 0.7, storage=storage, velocities=q)
+    lat.set_equilibrium(*perturbed_fields(box[::-1], seed))
+    if rows > 1:
+        lat.set_layout(rows)
+    if body:
+        lat.set_body_force((1e-5, -2e-5, 3e-6))
+    if n:
+        lat.particles_couple(particle_positions(n, box, seed), particle_velocities(n, 1e-3, seed), mass=10.0, gamma=1.0,
+                             kT=1e-4, radius=0.5, seed=seed, friction=friction)
+        if vacf:
+            lat.vacf_config(9, 2)
+    if tune:
+        lat.autotune(3)
+    return lat
+
+
+def _same(a, b):
+    """Bit for bit, NaN in the same places."""
+    import torch
+
+    return torch.equal(a.isnan(), b.isnan()) and torch.equal(a.nan_to_num(1.25, posinf=3e300, neginf=-3e300),
+                                                             b.nan_to_num(1.25, posinf=3e300, neginf=-3e300))
+
+
+def _compare(ones, twos, n):
+    assert _same(ones.populations(), twos.populations()), n
+    if ones.n:
+        for a, b in zip(ones.particles(), twos.particles()):
+            assert _same(a, b), n
+        if ones._vacf is not None:
+            assert _same(ones.vacf()[0], twos.vacf()[0]), n
+
+
+def _march(ones, twos, calls, must=True):
+    taken = 0
+    for n in calls:
+        for _ in range(n):
+            ones.step(1)
+        twos.profile_enable(True)
+        twos.step(n)
+        taken += n - twos.profile_read()["collide_launches"]
+        _compare(ones, twos, n)
+    assert taken > 0 or not must
+
+
+LARGE = [  # box, storage, velocities, particles, options
+    ((128, 128, 128), "f32", 19, 64, dict(vacf=True)),
+    ((128, 128, 128), "f32", 19, 0, dict()),
+    ((160, 130, 120), "f32", 15, 40, dict(friction="stokeslet_cube")),
+    ((130, 129, 130), "f32", 19, 0, dict()),  # rows that are no whole lines
+    ((192, 160, 130), "bf16", 19, 100, dict(friction="stokeslet2dx")),
+    ((256, 256, 80), "f16", 15, 0, dict()),
+    ((256, 200, 100), "f16", 19, 300, dict(friction="pointwise")),
+    ((128, 96, 80), "f64", 19, 50, dict(vacf=True)),
+    ((112, 120, 100), "f64", 15, 0, dict(body=False)),
+    # row groups, tiles that cut them
+    ((128, 96, 130), "f32", 19, 64, dict(rows=32)),
+    ((128, 80, 61), "bf16", 19, 0, dict(rows=16)),
+    ((100, 84, 60), "f64", 19, 20, dict(rows=4)),
+    ((256, 128, 70), "f16", 19, 16, dict(rows=64)),
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", LARGE, ids=lambda c: f"{'x'.join(map(str, c[0]))}-{c[1]}-q{c[2]}-{c[3]}-{c[4]}")
+def test_large_boxes_and_layouts(case):
+    box, storage, q, n, opt = case
+    announce(f"two-step sweep, large boxes: {case}")
+    _march(_lattice(box, storage, q, n, **opt), _lattice(box, storage, q, n, **opt), (4, 5, 8))
+
+
+# sizes of no other test: a tuned choice is remembered for later lattices of its size
+TUNED = [((48, 56, 60), "f32", 19, 0), ((56, 56, 56), "f64", 19, 0), ((201, 150, 117), "f16", 15, 0),
+         ((96, 97, 96), "f32", 19, 30), ((81, 157, 112), "f16", 19, 0), ((250, 130, 77), "f16", 15, 0),
+         ((144, 144, 140), "f32", 19, 0), ((132, 129, 130), "bf16", 19, 16), ((96, 100, 112), "f64", 15, 20),
+         ((256, 64, 60), "bf16", 19, 0)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", TUNED, ids=lambda c: f"{'x'.join(map(str, c[0]))}-{c[1]}-q{c[2]}-{c[3]}")
+def test_tuned_boxes(case):
+    announce(f"two-step sweep, tuned: {case}")
+    box, storage, q, n = case
+    twos = _lattice(box, storage, q, n, tune=True)
+    _march(_lattice(box, storage, q, n), twos, (4, 9), must=False)  # what is taken is the tuner's choice
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("storage", ["f32", "bf16", "f16", "f64"])
+@pytest.mark.parametrize("q", [19, 15])
+def test_headline_box_in_sweeps(storage, q):
+    # the kernels that the benchmark times: 256^3, 4096 particles, tuned
+    announce(f"two-step sweep: 256^3 {storage} q{q} tuned")
+    twos = _lattice((256,) * 3, storage, q, 4096, tune=True, vacf=True)
+    # 16-bit D3Q15 with forces is about as fast either way
+    _march(_lattice((256,) * 3, storage, q, 4096, vacf=True), twos, (5, 4), must=q == 19 or storage in ("f32", "f64"))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("storage,friction", [("f32", "stokeslet"), ("f64", "stokeslet_cube"), ("f32", "pointwise"),
+                                              ("bf16", "stokeslet2dx")])
+def test_non_finite_positions_and_populations(storage, friction):
+    import torch
+
+    box = (96, 96, 96) if storage != "bf16" else (140, 128, 128)
+    announce(f"two-step sweep, non-finite values: {storage} {friction}")
+    lats = []
+    for _ in range(2):
+        lat = _lattice(box, storage, 19, 12, friction=friction)
+        lat.r[3] = float("nan")
+        lat.r[5, 1] = float("inf")
+        lat.r[7, 2] = -float("inf")
+        lat.r[9] = torch.tensor([1e18, -1e300, 4.0], dtype=torch.float64)
+        lats.append(lat)
+    _march(*lats, (4, 5))
+    f = lats[0].populations()
+    f[3, 5, 6, 7] = float("inf")
+    f[0, 90, 90, 90] = float("nan")
+    for lat in lats:
+        lat.set_populations(f)
+    _march(*lats, (4, 5))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("storage", ["f32", "bf16", "f16", "f64"])
+@pytest.mark.parametrize("nx", [96, 130])  # rows of whole sectors, and not
+def test_ensembles_of_either_store_policy(storage, nx):
+    from paper_1909_13412_amd import Ensemble
+    from paper_1909_13412_amd.inputs import particle_positions, particle_velocities
+
+    boxes = [(nx, 120, 130), (nx, 129, 130), (50, 51, 25), (nx, 130, 61)]
+    boxes = boxes * 2 if storage in ("bf16", "f16") or nx == 96 else boxes
+    reps = [dict(nx=b[0], ny=b[1], nz=b[2], tau=0.7, seed=k, replica=k, r=particle_positions(9, b, k),
+                 v=particle_velocities(9, 1e-3, k)) for k, b in enumerate(boxes)]
+    announce(f"ensemble store policy: {storage} nx {nx}")
+    with warnings.catch_warnings():
+        warnings.simplefilter("ignore")
+        ones, twos = (Ensemble(reps, storage=storage, kT=1e-4, radius=0.5) for _ in range(2))
+    ones.use_graph(False)
+    assert twos.two_step
+    for n in (4, 1, 18, 16):
+        for _ in range(n):
+            ones.step(1)
+        twos.step(n)
+        for k in range(len(boxes)):
+            assert _same(ones.populations(k), twos.populations(k)), (n, k)
+        assert _same(ones.r, twos.r) and _same(ones.v, twos.v), n
