@@ -335,6 +335,7 @@ struct lbm_ctx {
     int fields_used;     // a particle update has run since the fields were cleared
     int last_field;      // the field that the last step spread into
     int own_held;        // this step's own field still holds the forces of the step before the last
+    int older_due;       // the forces of the step before the last may have to be released
     double *fh, *fr;
     const double *fext;  // given force on each particle (lbm_set_particle_force) or null
     uint32_t warnings;   // LBM_WARN_* of the attached particles
@@ -621,7 +622,7 @@ dim3 pair_group_blocks(int32_t n) {
 
 // Pair forces of the positions r: link the cell list, order long ones, then the
 // neighbour sums.  The list heads are none before; the particle update that follows sets them
-// back (its pair_list), or pair_list_clear does.
+// back (its pair_head), or pair_list_clear does.
 void launch_pairs(hipStream_t st, const double *r, int32_t n, const PairGrid &pg, const PairList &pl,
                   double *F) {
     const dim3 pblocks(unsigned((n + kPairBlock - 1) / kPairBlock));
@@ -635,7 +636,7 @@ void launch_pairs(hipStream_t st, const double *r, int32_t n, const PairGrid &pg
 }
 
 hipError_t pair_list_clear(hipStream_t st, const PairList &pl, uint32_t T) {
-    return hipMemsetAsync(pl.head, 0xFF, 2 * size_t(T) * 4, st);  // and `first` behind it
+    return hipMemsetAsync(pl.head, 0xFF, size_t(T) * 4, st);
 }
 
 // Returns the start event of a new timing pair (or nullptr when profiling is
@@ -703,11 +704,10 @@ ParticleArgs step_particle_args(lbm_ctx *c) {
     pa.fh = c->fh;
     pa.fr = c->fr;
     // this step's nodes, and those still to be released: the last step's, and
-    // after a two-step sweep the one's before it (kept where this step's go;
-    // none where they have been released)
+    // after a two-step sweep the one's before it (kept where this step's go)
     pa.cells = c->cells[c->step & 1];
     pa.last_cells = c->cells[(c->step & 1) ^ 1];
-    pa.older_cells = c->force[kThirdField] ? pa.cells : nullptr;
+    pa.older_cells = c->older_due ? pa.cells : nullptr;
     pa.err = c->err;
     pa.n = c->np;
     pa.friction = c->pdesc.friction;
@@ -720,11 +720,13 @@ ParticleArgs step_particle_args(lbm_ctx *c) {
     pa.step = uint32_t(c->step);
     pa.fext = c->fext;
     pa.fpair = nullptr;
-    pa.pair_list = PairList{};
+    pa.pair_link = nullptr;
+    pa.pair_head = nullptr;
     if (c->pair_on) {
         launch_pairs(c->stream, c->r, c->np, c->pg, c->plist, c->fpair);
         pa.fpair = c->fpair;
-        pa.pair_list = c->plist;
+        pa.pair_link = c->plist.link;
+        pa.pair_head = c->plist.head;
     }
     return pa;
 }
@@ -739,16 +741,16 @@ void launch_particle(lbm_ctx *c, const typename C::T *A, const ParticleArgs &pa)
     c->fields_used = 1;
     c->last_field = cur;
     c->own_held = 0;
+    c->older_due = 0;
 }
 
 // Releases the nodes of the last step and of the one before, lists of n entries.
-__global__ __launch_bounds__(kBlock) void k_release(int32_t n, uint32_t *last_cells, ForceField last,
-                                                    uint32_t *older_cells, ForceField older) {
+__global__ __launch_bounds__(kBlock) void k_release(int32_t n, const uint32_t *last_cells, ForceField last,
+                                                    const uint32_t *older_cells, ForceField older) {
     const int32_t i = int32_t(blockIdx.x * kBlock + threadIdx.x);
     if (i >= n) return;
     release_node(last, last_cells[i]);
     release_node(older, older_cells[i]);
-    last_cells[i] = older_cells[i] = kNoNode;
 }
 
 // Leaves the fields as every call finds them: the last step's forces in its own
@@ -837,7 +839,6 @@ void launch_two_step(lbm_ctx *c) {
         pk = prof_start(c, 1);
         ParticleArgs pa = step_particle_args(c);
         pa.last_cells = nullptr;  // the field of step n is still to be read
-        pa.older_cells = nullptr;  // the last update released it
         if (c->pdesc.friction == LBM_FRICTION_BD)
             launch_particle<C>(c, A, pa);  // reads no fluid
         else
@@ -845,6 +846,7 @@ void launch_two_step(lbm_ctx *c) {
         prof_stop(c, pk);
         c->last_field = f1;
         c->own_held = f0 != kThirdField && c->pdesc.friction != LBM_FRICTION_BD;
+        c->older_due = c->pdesc.friction != LBM_FRICTION_BD;
     } else {
         c->step += 1;
     }
@@ -1680,6 +1682,10 @@ namespace {
 // even number of two-step sweeps per call keeps the rule that n steps leave
 // the state in the lattice n swaps away.
 void advance(lbm_ctx *c, int32_t n) {
+    // A captured call is replayed after any other of an even number of steps:
+    // its first step always releases the third field (nodes that have been
+    // released are cleared again).
+    c->older_due = c->force[kThirdField] != nullptr;
     int32_t twos = 0;
     if (c->two > 0 && two_step_pays(c)) {
         int64_t count = c->series_count;
@@ -2280,8 +2286,9 @@ void ens_collide_shape(lbm_ens *e, const typename C::T *A, typename C::T *B, con
 }
 
 // The particle update of step n (`ahead` steps after the device clock), and the
-// nodes it has to release: those of the last two steps.  held: the step's own
-// field is one of them, it spreads into the third.
+// nodes it has to release: those of the last two steps (where the step two back
+// was released already its nodes are cleared again in the third field, which is
+// idle).  held: the step's own field is one of them, it spreads into the third.
 template <class C>
 void ens_launch_particle(lbm_ens *e, const typename C::T *A, int64_t n, int ahead, bool held) {
     const int own = int(n & 1);
@@ -3321,7 +3328,8 @@ hipError_t adjoint_run(lbm_ctx *c, char *tape, char *work, double *adj_pop, doub
                 if (pairs) {
                     launch_pairs(st, seg_r(k), np, c->rec_pg, plist, fpair);
                     pa.fpair = fpair;
-                    pa.pair_list = plist;
+                    pa.pair_link = plist.link;
+                    pa.pair_head = plist.head;
                 }
                 hipLaunchKernelGGL(k_particle<C>, dim3(pgrid), dim3(kParticleBlock), 0, st, seg(k),
                                    c->g, R(c->dec_s), pa, ff[par], ff[par ^ 1], ff[par]);

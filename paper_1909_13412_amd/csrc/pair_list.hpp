@@ -29,8 +29,8 @@ struct alignas(16) PairLink {
 struct PairList {
     PairLink *link;    // [n] as they came
     PairLink *sorted;  // [n] ascending
-    uint32_t *head;    // [T] first of `link` or kPairNone; with `first` all none between builds
-    uint32_t *first;   // [T] first of `sorted`, follows head in memory
+    uint32_t *head;    // [T] first of `link` or kPairNone (all none between builds)
+    uint32_t *first;   // [T] first of `sorted` where head is one
 };
 
 // Particles that a walk of a list takes at a time.

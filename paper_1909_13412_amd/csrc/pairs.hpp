@@ -118,7 +118,7 @@ __device__ inline void pair_cell_visit(const double *__restrict__ r, const PairG
     };
     if constexpr (ORDERED) {
         uint32_t hops = 0;
-        for (uint32_t next = pl.first[b]; next != kPairNone && hops < pg.n; ++hops) {
+        for (uint32_t next = pl.head[b] == kPairNone ? kPairNone : pl.first[b]; next != kPairNone && hops < pg.n; ++hops) {
             const int32_t j = int32_t(next);
             const PairLink e = pl.sorted[j];
             next = e.next;

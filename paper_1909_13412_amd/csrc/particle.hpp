@@ -33,10 +33,8 @@ struct ParticleArgs {
     double *fh, *fr;
     uint32_t *cells;  // [n][8] out: node each lane spread to this step, or kNoNode
     // [n][8] nodes spread to in the last step and in the one before (nullptr:
-    // nothing to release there), either may be `cells` itself; where the one
-    // before is released too, an entry is kNoNode from its release on
-    uint32_t *last_cells;
-    const uint32_t *older_cells;
+    // nothing to release there); either may be `cells` itself
+    const uint32_t *last_cells, *older_cells;
     uint32_t *err;
     int32_t n;
     int32_t friction;
@@ -59,7 +57,8 @@ struct ParticleArgs {
     // pair forces of this step, [n][3] (nullptr: none); F_C = fext + fpair
     const double *fpair;
     // the cell list they came from, to be emptied (head nullptr: none)
-    PairList pair_list;
+    const PairLink *pair_link;
+    uint32_t *pair_head;
 };
 
 // v of another lane of the same eight, moved in the vector unit (DPP), without
@@ -310,11 +309,8 @@ __device__ inline void particle_lane(const ParticleSite<C> &site, Gather &gather
     // Release this lane's nodes from the fields of earlier steps (their
     // stream-collide has consumed them).  Issued first, so that the stores are
     // in flight together with the gather below.
+    if (valid && pa.last_cells) release_node(site.last, pa.last_cells[8 * i + p]);
     if (valid && pa.older_cells) release_node(site.older, pa.older_cells[8 * i + p]);
-    if (valid && pa.last_cells) {
-        release_node(site.last, pa.last_cells[8 * i + p]);
-        if (pa.older_cells) pa.last_cells[8 * i + p] = kNoNode;
-    }
     const uint32_t Ln[3] = {g.nx, g.ny, g.nz};
     const int b[3] = {p & 1, (p >> 1) & 1, (p >> 2) & 1};
     double d[3];
@@ -425,11 +421,7 @@ __device__ inline void particle_lane(const ParticleSite<C> &site, Gather &gather
     pa.cells[8 * i + p] = my_cell;
 
     if (p != 0) return;
-    if (pa.pair_list.head) {
-        const uint32_t b = pa.pair_list.link[i].bucket;
-        pa.pair_list.head[b] = kPairNone;
-        pa.pair_list.first[b] = kPairNone;
-    }
+    if (pa.pair_head) pa.pair_head[pa.pair_link[i].bucket] = kPairNone;
     // Eqs. s2-langevin, s2-langevin2 with dt = 1; F_C is the given force (or 0).
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
