@@ -84,7 +84,7 @@ constexpr int kPairLanes = 32;
 // Whether m particles of one cell cost more in walks over the links, m^2 / 4
 // dependent loads, than in one pass over all n particles, some in flight at a
 // time (a cluster among 4096 particles, us per step: 64 of them 213 in walks; 128
-// of them 731 in walks, 483 in one pass; 256 of them 1853 and 624).
+// of them 731 in walks, 403 in one pass; 256 of them 1853 and 552).
 // Positions that are not finite all fall into one cell: without the bound a run
 // that diverges would walk n^2 / 4 links per particle.
 __device__ inline bool pair_cluster(uint32_t m, uint32_t n) { return uint64_t(m) * m > 2 * uint64_t(n); }
@@ -147,8 +147,8 @@ __device__ inline void pair_cell_visit(const double *__restrict__ r, const PairG
                 }
                 j = e.next;
             }
-            if (pair_cluster(found, pg.n)) {
-                constexpr uint32_t kAhead = 16;
+            if (__builtin_expect(pair_cluster(found, pg.n), 0)) {
+                constexpr uint32_t kAhead = 8;
                 for (uint32_t j0 = id[0]; j0 < pg.n; j0 += kAhead) {
                     uint32_t hit = 0;
 #pragma unroll
