@@ -35,19 +35,19 @@ ELEM = {"f64": 8, "f32": 4, "bf16": 2, "f16": 2}
 METRIC = "MLUPS & % HBM roofline, FP32 vs shifted-BF16 storage at stated VACF error"
 
 
-PMC_PROFILE = os.path.join(ROOT, "profiles", "k_stream_collide_suspension256.md")
+PMC_PROFILE = os.path.join(ROOT, "profiles", "k_two_steps_suspension256.md")
 
 
 def kernel_source_hash() -> str:
-    """SHA-256 over the sources the stream-collide kernel is compiled from (its
-    header, the codecs, the lattice constants) and the hipcc flags: the PMC
+    """SHA-256 over the sources the stream-collide kernels are compiled from (their
+    headers, the codecs, the lattice constants) and the hipcc flags: the PMC
     traffic figure is reported only while this matches the profiled build."""
     import hashlib
 
     from paper_1909_13412_amd import build as hip_build
 
     h = hashlib.sha256()
-    for name in ("collide.hpp", "codec.hpp", "velocities.hpp"):
+    for name in ("collide.hpp", "twostep.hpp", "codec.hpp", "velocities.hpp"):
         h.update(name.encode())
         with open(os.path.join(ROOT, "paper_1909_13412_amd", "csrc", name), "rb") as fh:
             h.update(fh.read())
@@ -55,8 +55,9 @@ def kernel_source_hash() -> str:
     return h.hexdigest()
 
 
-def pmc_traffic(storage: str):
-    """HBM bytes per stream-collide launch from the committed counter profile:
+def pmc_traffic(storage: str, steps_per_launch: float = 1.0):
+    """HBM bytes per stream-collide launch (two-step sweeps and single steps as
+    steps_per_launch mixes them) from the committed counter profile:
     the L2's read requests to memory counted by size (32 x TCC_EA0_RDREQ_32B +
     64 x TCC_EA0_RDREQ_64B + 128 x TCC_EA0_RDREQ_128B) plus its write requests
     (64 x TCC_EA0_WRREQ_64B + 32 x the rest), the rule that gives a plain
@@ -71,7 +72,13 @@ def pmc_traffic(storage: str):
     if rec.get("source_sha256") != kernel_source_hash() or not rec.get(storage):
         return None
     c = rec[storage]
-    return float(c["read_bytes"] + c["write_bytes"])
+    one, share = float(c["read_bytes"] + c["write_bytes"]), steps_per_launch - 1.0  # of two-step sweeps
+    if share <= 0.0:
+        return one
+    if "two_steps" not in c:
+        return None
+    two = c["two_steps"]
+    return one * (1.0 - share) + share * (two["read_bytes"] + two["write_bytes"])
 
 
 def parse_variant(name: str):
@@ -727,7 +734,7 @@ def main():
         print(f"[bench] timing storage={s}", file=sys.stderr, flush=True)
         r = time_storage(w, s, args.steps, args.warmup, args.prof_steps)
         r["speedup_vs_main"] = r["mlups"] / main_res["mlups"]
-        r["traffic"] = pmc_traffic(s)
+        r["traffic"] = pmc_traffic(s, r["steps_per_launch"])
         variants[s] = r
     large = None
     if args.large_steps > 0 and args.workload == "suspension256":
@@ -784,7 +791,7 @@ def main():
 
     ncell = w["L"] ** 3
     regions = [main_res["mlups"]] + main_res["mlups_more_regions"]
-    traffic = pmc_traffic(args.storage)
+    traffic = pmc_traffic(args.storage, main_res["steps_per_launch"])
     out = {
         "metric": METRIC,
         "value": round(main_res["mlups"], 1),
