@@ -1342,8 +1342,9 @@ bool two_step_by_size(const lbm_grid_desc *g) { return ncell_of(g) >= two_step_m
 // is a few us of latency, which trials do not tell apart (two steps in a run /
 // by trial, us, single and two-step: BF16 64^3 10.0 and 12.1 / 19.7 and 14.6, 72^3
 // 13.1 and 14.5 / 25.2 and 17.1; but FP32 48^3 11.3 and 9.4 / 18.6 and 13.5, FP64
-// 48^3 16.3 and 12.9 / 19.1 and 15.4).  In 45 larger ones the trials' choice was the
-// run's fastest or within 4.6% of it.
+// 48^3 16.3 and 12.9 / 19.1 and 15.4).  In 44 of 45 larger ones the trials' choice was
+// the run's fastest or within 5% of it (F16 201 x 150 x 117, a tie by trial, went to
+// the slower side by 21% in one of three sets).
 bool two_step_trial(const lbm_grid_desc *g) {
     return ncell_of(g) >= (elem_size(g->storage) == 2 ? two_step_min_nodes(2) : uint64_t(1) << 16);
 }

@@ -11,10 +11,12 @@
 // are left, plus the halo, whose lines are mostly in the L2 of the XCD that
 // holds the neighbouring tiles (blocks in XCD slabs).  Two steps, ms, against
 // two single ones at 256^3: FP32 0.484 / 0.85, BF16 0.31 / 0.41, FP64 0.96 /
-// 1.73; FP32 128^3 0.067 / 0.110.  FP32 and FP64 reach 5.3 TB/s (a copy 4.8, the
-// single-step sweep 6.3); without its loads the FP32 sweep takes 0.23 ms,
-// without its stores 0.37.  16-bit storage is bound by the arithmetic of both
-// steps on 13 wavefronts a compute unit and the address unit's lines.
+// 1.73; FP32 128^3 0.067 / 0.110.  The halo costs 7 to 12% of the lattice in reads
+// from memory; with it FP32 and FP64 move 5.6 TB/s (a copy 5.2, the single-step
+// sweep 6.4), the address unit busy 70% of the time; without its loads the FP32
+// sweep takes 0.23 ms, without its stores 0.37.  16-bit storage moves 3.9 TB/s, the
+// vector unit busy 65-70% and the address unit 62% of the time, on 11 to 13
+// wavefronts a compute unit; D3Q19 spills 23 to 25 registers.
 // Slower were: planes brought to LDS by direct loads (FP32 0.548, BF16 0.395),
 // two small blocks per compute unit, non-temporal loads (FP32 0.726, BF16 0.463:
 // the halo's lines come twice), a march in alternate directions so that a
