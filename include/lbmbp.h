@@ -130,8 +130,9 @@ lbm_status lbm_lattice_bytes(const lbm_grid_desc *grid, size_t *bytes);
 lbm_status lbm_grid_scratch_bytes(const lbm_grid_desc *grid, size_t *bytes);
 
 /* Bytes of particle scratch for n particles (corner bookkeeping, last-step
- * forces, the pair-force cell list; where so many particles take two-step
- * sweeps in this box (lbm_step), a third node-force field). */
+ * forces, the pair-force cell list; in boxes large enough for two-step sweeps
+ * with particles (lbm_step), room for a third node-force field).  Scratch for n
+ * particles serves any fewer. */
 lbm_status lbm_particle_scratch_bytes(const lbm_grid_desc *grid, int32_t n, size_t *bytes);
 
 /* Bytes of the VACF origin store for n particles: (max_lag/stride + 1) * n * 3

@@ -55,8 +55,9 @@ constexpr int kRedBlocks = 1024;
 // Node-force fields of a box: step n spreads into its own field, n mod 2.  A
 // two-step sweep reads the fields of both its steps, so neither can be cleared
 // before it, and the particle update that follows clears both: where the first
-// of them is that update's own field, it takes the third (kept by boxes whose
-// particles take two-step sweeps only: it is 24 bytes a node).  Two sweeps in a
+// of them is that update's own field, it takes the third (24 bytes a
+// node, in the particle scratch of boxes that can take two-step sweeps with
+// particles).  Two sweeps in a
 // row so end with the fields in the roles they started with, and an even number of
 // steps (the lattices' condition) can be captured into a graph and replayed.
 constexpr int kForceFields = 3;
@@ -487,7 +488,7 @@ uint32_t pair_buckets(int32_t n) {
 }
 
 size_t pair_list_bytes(int32_t n) {
-    if (n > kPairMax) return 0;  // lbm_set_pair_force refuses them
+    n = std::min(n, kPairMax);  // more have no lists, but their scratch serves fewer
     return 2 * align_up(size_t(n) * sizeof(PairLink), kAlign) + align_up(2 * size_t(pair_buckets(n)) * 4, kAlign);
 }
 
@@ -526,15 +527,17 @@ bool two_step_planes(const lbm_grid_desc *g) {
     return uint64_t(g->nx) * uint64_t(g->ny) * uint64_t(velocity_count(g)) * elem_size(g->storage) < (uint64_t(1) << 32);
 }
 
-// Bytes of the third node-force field and its flags for n particles (0: none).
-size_t third_field_bytes(const lbm_grid_desc *g, int32_t n) {
-    if (!two_step_planes(g) || !two_step_pays(elem_size(g->storage), velocity_count(g), ncell_of(g), n)) return 0;
+// Bytes of the third node-force field and its flags (0: this box never has one).
+// Room for it does not depend on the number of particles: scratch for many
+// serves fewer, too, and it is they that take two-step sweeps.
+size_t third_field_bytes(const lbm_grid_desc *g) {
+    if (!two_step_planes(g) || !two_step_pays(elem_size(g->storage), velocity_count(g), ncell_of(g), 1)) return 0;
     return align_up(size_t(mask_words(ncell_of(g))) * 4, kAlign) + force_field_bytes(g);
 }
 
 size_t particle_scratch_size(const lbm_grid_desc *g, int32_t n) {
     if (n <= 0) return 0;
-    size_t s = third_field_bytes(g, n);
+    size_t s = third_field_bytes(g);
     s += 2 * align_up(size_t(n) * 8 * 4, kAlign);  // nodes spread to, two steps
     s += align_up(particle_blocks(n) * 3 * 8, kAlign);  // momentum partials
     s += 2 * align_up(size_t(n) * 3 * 8, kAlign);  // fh, fr
@@ -1569,7 +1572,8 @@ lbm_status particles_couple(lbm_ctx *ctx, const lbm_particle_desc *d, double *r,
     s += pair_list_bytes(d->n);
     ctx->fpair = reinterpret_cast<double *>(s);
     s += align_up(size_t(d->n) * 3 * 8, kAlign);
-    if (const size_t third = third_field_bytes(&ctx->desc, d->n)) {
+    const size_t third = third_field_bytes(&ctx->desc);
+    if (third && two_step_pays(ctx->elem, ctx->q, ctx->g.ncell, d->n)) {
         ctx->mask[kThirdField] = reinterpret_cast<uint32_t *>(s);
         ctx->force[kThirdField] = reinterpret_cast<long long *>(s + align_up(size_t(ctx->mask_words) * 4, kAlign));
         e = hipMemsetAsync(s, 0, third, ctx->stream);

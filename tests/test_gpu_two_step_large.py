@@ -161,3 +161,71 @@ def test_ensembles_of_either_store_policy(storage, nx):
         for k in range(len(boxes)):
             assert _same(ones.populations(k), twos.populations(k)), (n, k)
         assert _same(ones.r, twos.r) and _same(ones.v, twos.v), n
+
+
+@pytest.mark.gpu
+def test_scratch_for_many_particles_holds_fewer():
+    # one buffer for two particle sets: 262 nodes per particle (no two-step
+    # sweeps), then 1e5 (sweeps, with the third node-force field in that buffer)
+    import ctypes
+
+    import torch
+
+    from paper_1909_13412_amd import _abi
+    from paper_1909_13412_amd.inputs import particle_positions, particle_velocities
+
+    box, many, few = (128, 100, 96), 4700, 12
+    announce("one scratch buffer for two particle sets")
+    ones, twos = (_lattice(box, "f32", 19, 0, body=False) for _ in range(2))
+    lib, sz = _abi.load(), ctypes.c_size_t()
+    _abi.check("bytes", lib.lbm_particle_scratch_bytes(ctypes.byref(twos.desc), many, ctypes.byref(sz)))
+    guard = 4096
+    buf = torch.full((sz.value + guard,), 0x5A, dtype=torch.uint8, device="cuda:0")
+    for n in (many, few, many, few):
+        r, v = particle_positions(n, box, n), particle_velocities(n, 1e-3, n)
+        kw = dict(mass=10.0, gamma=1.0, kT=1e-4, radius=0.5, seed=n)
+        with warnings.catch_warnings():
+            warnings.simplefilter("ignore")
+            ones.particles_couple(r, v, **kw)
+            twos.particles_couple(r, v, **kw)
+        p = lambda t: ctypes.c_void_p(t.data_ptr())  # noqa: E731
+        _abi.check("couple", lib.particles_couple(twos.ctx, ctypes.byref(twos.pdesc), p(twos.r), p(twos.v), p(buf)))
+        _march(ones, twos, (4, 5), must=n == few)
+    torch.cuda.synchronize()
+    assert bool((buf[sz.value:] == 0x5A).all())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("storage", ["bf16", "f32"])
+def test_lattices_beyond_2_32_elements(storage):
+    # 640 x 640 x 560: 4.36e9 populations; the lattices themselves are compared
+    import torch
+
+    from paper_1909_13412_amd import Lattice
+    from paper_1909_13412_amd.inputs import particle_positions, particle_velocities
+
+    box, n = (640, 640, 560), 64
+    announce(f"two-step sweep beyond 2^32 elements: {storage}")
+    k = [2.0 * np.pi / L * torch.arange(L, dtype=torch.float64, device="cuda:0") for L in box[::-1]]
+    u = torch.zeros((3,) + box[::-1], dtype=torch.float64, device="cuda:0")
+    u[0] += 0.01 * torch.sin(3 * k[1])[None, :, None]
+    u[1] += 0.01 * torch.sin(2 * k[2])[None, None, :]
+    u[2] += 0.01 * torch.sin(5 * k[0])[:, None, None]
+    lats = []
+    for _ in range(2):
+        lat = Lattice(*box, 0.7, storage=storage)
+        lat.set_equilibrium(None, u)
+        lat._u_in = None
+        lat.particles_couple(particle_positions(n, box, 5), particle_velocities(n, 1e-3, 5), kT=1e-4, radius=0.5, seed=5)
+        lats.append(lat)
+    del u
+    ones, twos = lats
+    for _ in range(4):
+        ones.step(1)
+    twos.profile_enable(True)
+    twos.step(4)
+    assert twos.profile_read()["collide_launches"] == 2
+    size = ones.lattice_bytes
+    assert size // (2 if storage == "bf16" else 4) > 1 << 32
+    assert torch.equal(ones.pop_a[:size], twos.pop_a[:size])
+    assert _same(ones.r, twos.r) and _same(ones.v, twos.v)
