@@ -6,7 +6,7 @@ import warnings
 import numpy as np
 import pytest
 
-from helpers import announce
+from helpers import announce, nmax_err
 
 
 def _lattice(r, L, storage="f32"):
@@ -90,3 +90,32 @@ def test_particles_all_in_one_cell(where):
     # n loads of 1 us, one after another, would be 33 ms; n^2 / 4 of 0.1 us 13 s
     assert t < 1.0
     assert torch.count_nonzero(lat.pair_forces()).item() == 0  # no direction at distance zero
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,rc,spread", [(34, 4.5, None), (12, 1.2, 1.0)])
+def test_adjoint_of_crowded_cells_matches_oracle(oracle_mod, n, rc, spread):
+    # lists put in order (34 particles in 8 cells) and a cluster in a sparse box
+    from oracle import adjoint as A
+    from paper_1909_13412_amd import Lattice
+    from test_gpu_adjoint import BOX, _case
+
+    f0, r0, v0, cf, cr, cv = _case(oracle_mod, 21, n=n)
+    rng = np.random.default_rng(21)
+    r0 = rng.random((n, 3)) * np.array(BOX) if spread is None else 3.0 + spread * rng.random((n, 3))
+    cells = np.prod(np.floor(np.array(BOX) / rc))
+    assert (n > 4 * cells) == (spread is None)
+    theta, N, every, seed = (0.05, 0.8, 10.0, 1e-4), 4, 3, 14  # weak friction: many particles share nodes
+    announce(f"adjoint of crowded cells: {n} particles, cutoff {rc}")
+    nx, ny, nz = BOX
+    lat = Lattice(nx, ny, nz, theta[1], storage="f64")
+    lat.set_populations(f0)
+    with warnings.catch_warnings():
+        warnings.simplefilter("ignore")
+        lat.particles_couple(r0, v0, mass=theta[2], gamma=theta[0], kT=theta[3], seed=seed)
+    lat.set_pair_force(0.02, rc)
+    g = {k: t.cpu().numpy() for k, t in lat.adjoint(lat.record(N, every), cf, cr, cv).items()}
+    ref = A.vjp(f0, r0, v0, np.array(theta), A.noise(n, N, seed), cf, cr, cv, pair=(0.02, rc))
+    errs = [nmax_err(g[k], x) for k, x in zip(("pop", "r", "v", "params"), ref)]
+    announce(f"  errors {errs}")
+    assert max(errs) < 1e-10  # the bound of the sparse case, over fewer steps
